@@ -590,21 +590,18 @@ __global__ __launch_bounds__(512, 1) void babai_kernel(
     if (lane < ng && mask != 0)
       base = atomicAdd(&gcount[((size_t)(i0 + lane) * kSubLists + sub) * kCtrStride],
                        (uint32_t)__popc(mask));
-    if (lane < RT && r0 + lane < rows) {
-      const int bits = racc_s[lane];
-      const int lrow_r = map_row(rowmap, r0 + lane);
-      for (int p = 0; p < ng; ++p) {
-        const int mp = __shfl(mask, p);
-        const uint32_t bp = __shfl(base, p);
-        if ((bits >> p) & 1)
-          glist[((size_t)(i0 + p) * kSubLists + sub) * list_cap + bp +
-                (uint32_t)__popc(mp & ((1 << lane) - 1))] = lrow_r;
-      }
-    } else {
-      for (int p = 0; p < ng; ++p) {  // the shuffles need every lane
-        (void)__shfl(mask, p);
-        (void)__shfl(base, p);
-      }
+    // Every lane takes part in the shuffles (a shuffle from a lane that is
+    // switched off gives 0): lane p holds group i0 + p's reservation also where
+    // the tile has fewer than ng rows.
+    const bool row_live = lane < RT && r0 + lane < rows;
+    const int acc = row_live ? racc_s[lane] : 0;
+    const int lrow_r = map_row(rowmap, row_live ? r0 + lane : r0);
+    for (int p = 0; p < ng; ++p) {
+      const int mp = __shfl(mask, p);
+      const uint32_t bp = __shfl(base, p);
+      if ((acc >> p) & 1)
+        glist[((size_t)(i0 + p) * kSubLists + sub) * list_cap + bp +
+              (uint32_t)__popc(mp & ((1 << lane) - 1))] = lrow_r;
     }
   }
 

@@ -505,3 +505,23 @@ def test_full_size_layer(cfg_id):
     assert np.all(np.abs(F_dev[wide] - F_gpu) <= OBJ_RTOL * F_gpu)
     L = st["objective_after_scales"]
     assert all(L[k + 1] <= L[k] * (1 + 1e-6) for k in range(len(L) - 1))
+
+
+@pytest.mark.parametrize("rows,cols,g", [(1025, 512, 64), (1029, 512, 64), (2051, 1024, 128),
+                                         (1033, 512, 32)])
+def test_changed_row_lists_of_a_short_last_tile(rows, cols, g):
+    """The last tile of 16 rows has fewer rows than a panel has groups: the
+    incremental Gram builds, which read the lists the code update writes, leave
+    the same bits as full rebuilds at every sweep."""
+    W, H, q, s, z = random_layer(rows, cols, g, 3, seed=rows)
+    K = 12
+    gk = GpuLayer(W, H, q, s, z, g, 3, sweeps=K)
+    st = jq.sweeps(gk.p, gk.W, gk.H, gk.codes, gk.scales, gk.zeros, gk.ws)
+    assert any(st["gram_listed"])
+    qg, sg = gk.state()
+    step = GpuLayer(W, H, q, s, z, g, 3)
+    for _ in range(K):
+        step.scale_step()
+        step.code_step(trace=False)
+    qs, ss = step.state()
+    assert np.array_equal(qg, qs) and np.array_equal(sg, ss)
