@@ -29,7 +29,6 @@ Layout make_layout(int rows, int cols, int g) {
     return at;
   };
   L.lfac = take(G * gg * sizeof(double));
-  L.rinv = take(G * gg * sizeof(float));
   L.rcol = take(G * gg * sizeof(float));
   L.rdinv = take(G * g * sizeof(float));
   L.rdsq = take(G * g * sizeof(float));

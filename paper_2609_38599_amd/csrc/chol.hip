@@ -4,10 +4,9 @@
 // no column permutation).  Only R_i enters the code update, and
 // R_i^T R_i = A_i^T A_i = H_ii, so R_i is the upper Cholesky factor of H_ii
 // (the Babai proposal does not depend on the row signs of R_i).  One work-group
-// factors one g x g block in LDS in fp64, inverts the lower factor L_i = R_i^T
-// column by column, and writes the fp32 forms the sweep kernels read (and
-// keeps L_i^{-1} in fp64 in place of L_i):
-//   rinv  row n = row n of L_i^{-1}       (u = R_i^{-T} he = L_i^{-1} he)
+// factors one g x g block in LDS in fp64, inverts the lower factor L_i = R_i^T,
+// and writes the forms the later kernels read:
+//   lfac  L_i^{-1} in fp64 (zero above the diagonal), for M = blockdiag(L^{-1}) H
 //   rcol  column l, chunk c, lane j, w: R_i(m, l) / R_i(m, m) for m < l, 0
 //         for m >= l, with m = j + 16 (W c + w), W = min(4, g / 16) (column l
 //         of R_i above the diagonal with each row scaled by its inverse
@@ -16,109 +15,156 @@
 //         and read one chunk each with one W-float access); only the chunks
 //         a back-substitution step reads are kept (RcolLayout)
 //   rdinv 1 / R_i(l, l),  rdsq R_i(l, l)^2,  rmat R_i (row-major).
-#include "jarq_internal.h"
+//
+// The block is one 64 x 64 (or 32 x 32) factorization of chol64.h, or for
+// g = 128 two of them joined by matrix-core products:
+//   L21 = A21 L11^{-T},  A22 -= L21 L21^T,  X21 = -X22 (L21 X11).
+// What bounds it is the serial chain of one work-group (there are only G of
+// them): 57 us at g = 128 and 21 us at g = 64, against 1062 and 229 us for a
+// column loop over the whole block with barriers and fp64 divisions.
+#include "chol64.h"
 
 namespace jarq {
 
 template <int G_SIZE>
 __global__ __launch_bounds__(256) void chol_groups_kernel(const float* __restrict__ H, int cols,
                                                           double* __restrict__ lfac,
-                                                          float* __restrict__ rinv,
                                                           float* __restrict__ rcol,
                                                           float* __restrict__ rdinv,
                                                           float* __restrict__ rdsq,
                                                           float* __restrict__ rmat,
                                                           Flags* __restrict__ flags) {
   constexpr int g = G_SIZE;
-  constexpr int LD = g + 1;
-  constexpr int NT = g / 16;
-  extern __shared__ double A[];  // g x LD
+  constexpr int n = g < 64 ? g : 64;   // edge of an LDS block
+  extern __shared__ double sm[];
+  double* B0 = sm;                     // A11, L11, then X22
+  double* B1 = sm + kCholBlock;        // X11
+  double* B2 = sm + 2 * kCholBlock;    // A21, L21 (g = 128)
+  double* B3 = sm + 3 * kCholBlock;    // A22, L22 (g = 128)
+  __shared__ double dinv[128];
   __shared__ int fail;
   const int blk = blockIdx.x;
-  const int tid = threadIdx.x;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const float* Hb = H + (size_t)blk * g * cols + (size_t)blk * g;
-  for (int e = tid; e < g * g; e += blockDim.x) {
-    const int r = e / g, c = e % g;
-    A[r * LD + c] = (double)Hb[(size_t)r * cols + c];
-  }
-  if (tid == 0) fail = 0;
-  __syncthreads();
-  // Right-looking Cholesky H_ii = L L^T on the lower triangle.
-  for (int k = 0; k < g; ++k) {
-    if (tid == 0) {
-      double piv = A[k * LD + k];
-      if (!(piv > 0.0) || !isfinite(piv)) {
-        fail = 1;
-        piv = 1.0;
-      }
-      A[k * LD + k] = sqrt(piv);
-    }
-    __syncthreads();
-    const double d = A[k * LD + k];
-    for (int i = k + 1 + tid; i < g; i += blockDim.x) A[i * LD + k] /= d;
-    __syncthreads();
-    const int n = g - k - 1;
-    for (int e = tid; e < n * n; e += blockDim.x) {
-      const int i = k + 1 + e / n, j = k + 1 + e % n;
-      if (j <= i) A[i * LD + j] -= A[i * LD + k] * A[j * LD + k];
-    }
-    __syncthreads();
-  }
-  double* Lb = lfac + (size_t)blk * g * g;
-  for (int e = tid; e < g * g; e += blockDim.x) {
-    const int r = e / g, c = e % g;
-    Lb[e] = (c <= r) ? A[r * LD + c] : 0.0;
-  }
-  __syncthreads();
-  // Column j of L^{-1}: Linv(i, j) = (delta_ij - sum_{j<=k<i} L(i,k) Linv(k,j)) / L(i,i).
-  // Thread j owns column j of A, which now receives L^{-1}; L is read back from lfac.
-  if (tid < g) {
-    const int j = tid;
-    for (int i = 0; i < g; ++i) {
-      double v = 0.0;
-      if (i >= j) {
-        double acc = (i == j) ? 1.0 : 0.0;
-        for (int k = j; k < i; ++k) acc -= Lb[i * g + k] * A[k * LD + j];
-        v = acc / Lb[i * g + i];
-      }
-      A[i * LD + j] = v;
-    }
-  }
-  __syncthreads();
-  float* rinv_b = rinv + (size_t)blk * g * g;
+  double* lfac_b = lfac + (size_t)blk * g * g;
   float* rcol_b = rcol + (size_t)blk * g * g;
-  for (int e = tid; e < g * g; e += blockDim.x) {
-    const int r = e / g, c = e % g;
-    rinv_b[e] = (float)A[r * LD + c];
-    // column l, chunk c, lane j, w for e = ((l NC + c) 16 + j) W + w:
-    // R(m, l) / R(m, m), m = j + 16 (W c + w), R = L^T; kept where the back
-    // substitution reads it (c < RcolLayout<g>::chunks(l))
+  float* rmat_b = rmat + (size_t)blk * g * g;
+
+  auto load = [&](double* B, int r0, int c0) {
+    for (int e = tid; e < n * n / 4; e += 256) {
+      const int i = e / (n / 4), j = 4 * (e % (n / 4));
+      const f32x4 v = *(const f32x4*)(Hb + (size_t)(r0 + i) * cols + c0 + j);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) B[i * kCholLd + j + u] = (double)v[u];
+    }
+  };
+  // rcol and rmat entries of the block of L at (r0, c0)
+  auto out_l = [&](const double* B, int r0, int c0) {
     using RL = RcolLayout<g>;
     constexpr int W = RL::W;
-    const int l = e / (16 * NT);
-    const int rem = e % (16 * NT);
-    const int j = (rem / W) % 16;
-    const int cc = rem / (16 * W);
-    const int t = cc * W + rem % W;
-    const int m = j + 16 * t;
-    if (cc < RL::chunks(l))
-      rcol_b[RL::offset(l) + (cc * 16 + j) * W + rem % W] =
-          (float)(m < l ? Lb[l * g + m] / Lb[m * g + m] : 0.0);
+    for (int e = tid; e < n * n; e += 256) {
+      // W consecutive lanes' positions of one column: m = j + 16 (W c + w)
+      const int i = e / n, rem = e % n;
+      const int jj = rem / W, m = c0 + (jj & 15) + 16 * (W * (jj >> 4) + rem % W);
+      const int l = r0 + i;
+      const int cc = (m >> 4) / W;
+      rcol_b[RL::offset(l) + (cc * 16 + (m & 15)) * W + (m >> 4) % W] =
+          (float)(m < l ? B[i * kCholLd + m - c0] * dinv[m] : 0.0);
+    }
+    for (int e = tid; e < n * n; e += 256) {
+      const int j = e / n, i = e % n;
+      rmat_b[(size_t)(c0 + j) * g + r0 + i] =
+          (float)(r0 + i >= c0 + j ? B[i * kCholLd + j] : 0.0);
+    }
+  };
+  // the diagonal block of L^{-1} at (r0, r0)
+  auto out_x = [&](const double* X, int r0) {
+    for (int e = tid; e < n * n; e += 256) {
+      const int i = e / n, j = e % n;
+      lfac_b[(size_t)(r0 + i) * g + r0 + j] = j <= i ? X[i * kCholLd + j] : 0.0;
+    }
+  };
+
+  if (tid == 0) fail = 0;
+  load(B0, 0, 0);
+  if constexpr (g == 128) {
+    load(B2, 64, 0);
+    load(B3, 64, 64);
   }
-  // R_i = L_i^T in fp32, row m: rmat[m][n] = L_i(n, m) (zero below the diagonal).
-  float* rmat_b = rmat + (size_t)blk * g * g;
-  for (int e = tid; e < g * g; e += blockDim.x) {
-    const int m = e / g, n = e % g;
-    rmat_b[e] = (float)(n >= m ? Lb[n * g + m] : 0.0);
+  __syncthreads();
+  chol64_factor(B0, n, dinv, &fail);
+  out_l(B0, 0, 0);
+  chol64_invert(B0, n, dinv, B1);
+  out_x(B1, 0);
+  if constexpr (g == 128) {
+    // L21 = A21 X11^T: wave = 16 rows, all read before any is written
+    {
+      double a[16];
+#pragma unroll
+      for (int ks = 0; ks < 16; ++ks) a[ks] = frag_a(B2, 16 * wave, 0, ks);
+#pragma unroll
+      for (int bj = 0; bj < 4; ++bj) {
+        f64x4 c = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int ks = 0; ks < 4 * (bj + 1); ++ks) c = mfma_f64(a[ks], frag_a(B1, 16 * bj, 0, ks), c);
+        store_c(B2, 16 * wave, 16 * bj, c);
+      }
+    }
+    __syncthreads();
+    // A22 -= L21 L21^T, lower blocks
+    int id = 0;
+    for (int bi = 0; bi < 4; ++bi)
+      for (int bj = 0; bj <= bi; ++bj, ++id) {
+        if ((id & 3) != wave) continue;
+        f64x4 c = load_c(B3, 16 * bi, 16 * bj);
+#pragma unroll
+        for (int ks = 0; ks < 16; ++ks)
+          c = mfma_f64(-frag_a(B2, 16 * bi, 0, ks), frag_a(B2, 16 * bj, 0, ks), c);
+        store_c(B3, 16 * bi, 16 * bj, c);
+      }
+    out_l(B2, 64, 0);
+    __syncthreads();
+    chol64_factor(B3, 64, dinv + 64, &fail);
+    out_l(B3, 64, 64);
+    chol64_invert(B3, 64, dinv + 64, B0);
+    out_x(B0, 64);
+    // X21 = -X22 (L21 X11): wave = 16 columns; T = L21 X11 stays in registers
+    {
+      f64x4 t[4];
+#pragma unroll
+      for (int bi = 0; bi < 4; ++bi) t[bi] = f64x4{0.0, 0.0, 0.0, 0.0};
+      for (int q = wave; q < 4; ++q)
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) {
+          const double b = frag_b(B1, 16 * q, 16 * wave, ks);
+#pragma unroll
+          for (int bi = 0; bi < 4; ++bi)
+            t[bi] = mfma_f64(frag_a(B2, 16 * bi, 16 * q, ks), b, t[bi]);
+        }
+#pragma unroll
+      for (int bi = 0; bi < 4; ++bi) {
+        f64x4 x = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int u = 0; u <= bi; ++u)
+#pragma unroll
+          for (int ks = 0; ks < 4; ++ks)
+            x = mfma_f64(-frag_a(B0, 16 * bi, 16 * u, ks), t[u][ks], x);
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+          lfac_b[(size_t)(64 + 16 * bi + 4 * v + (lane >> 4)) * g + 16 * wave + (lane & 15)] = x[v];
+      }
+    }
+    // the zero blocks above the diagonal of L^{-1} and below that of R
+    for (int e = tid; e < 64 * 64; e += 256) {
+      const int i = e / 64, j = e % 64;
+      lfac_b[(size_t)i * g + 64 + j] = 0.0;
+      rmat_b[(size_t)(64 + i) * g + j] = 0.f;
+    }
   }
-  for (int l = tid; l < g; l += blockDim.x) {
-    const double d = Lb[l * g + l];
-    rdinv[(size_t)blk * g + l] = (float)(1.0 / d);
-    rdsq[(size_t)blk * g + l] = (float)(d * d);
+  for (int l = tid; l < g; l += 256) {
+    rdinv[(size_t)blk * g + l] = (float)dinv[l];
+    rdsq[(size_t)blk * g + l] = (float)(1.0 / (dinv[l] * dinv[l]));
   }
-  __syncthreads();  // every read of L is done
-  // Keep L_i^{-1} in fp64 (it replaces L_i in lfac) for M = blockdiag(L^{-1}) H.
-  for (int e = tid; e < g * g; e += blockDim.x) Lb[e] = A[(e / g) * LD + e % g];
   if (tid == 0 && fail) atomicAdd(&flags->not_spd, 1);
 }
 
@@ -126,12 +172,12 @@ template <int G_SIZE>
 static hipError_t launch_chol_t(hipStream_t st, int cols, const float* H, char* ws,
                                 const Layout& lay) {
   const int G = cols / G_SIZE;
-  const size_t lds = (size_t)G_SIZE * (G_SIZE + 1) * sizeof(double);
+  const size_t lds = (size_t)(G_SIZE == 128 ? 4 : 2) * kCholBlock * sizeof(double);
   static std::atomic<unsigned long long> lds_set{0};
   hipError_t e = allow_dynamic_lds((const void*)chol_groups_kernel<G_SIZE>, lds, lds_set);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(chol_groups_kernel<G_SIZE>, dim3(G), dim3(256), lds, st, H, cols,
-                     (double*)(ws + lay.lfac), (float*)(ws + lay.rinv), (float*)(ws + lay.rcol),
+                     (double*)(ws + lay.lfac), (float*)(ws + lay.rcol),
                      (float*)(ws + lay.rdinv), (float*)(ws + lay.rdsq), (float*)(ws + lay.rmat),
                      (Flags*)(ws + lay.flags));
   return hipGetLastError();

@@ -106,8 +106,7 @@ inline hipError_t allow_dynamic_lds(const void* fn, size_t bytes,
 
 // Offsets (bytes) of the workspace regions for one problem size.
 struct Layout {
-  size_t lfac;      // [G][g][g] f64: L_i^{-1} (holds L_i while it is factored)
-  size_t rinv;      // [G][g][g] f32: row n = row n of L_i^{-1} = column n of R_i^{-1}
+  size_t lfac;      // [G][g][g] f64: L_i^{-1}
   size_t rcol;      // [G][g][g/(16 W)][16][W] f32: R~_i columns in lane chunks (W = min(4, g/16))
   size_t rdinv;     // [G][g] f32: 1 / R_i(l,l)
   size_t rdsq;      // [G][g] f32: R_i(l,l)^2
