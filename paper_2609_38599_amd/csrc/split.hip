@@ -14,20 +14,11 @@
 namespace jarq {
 
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+typedef double f64x4 __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ void atomic_max_abs(float* dst, float v) {
   // |v| >= 0: IEEE ordering of non-negative floats equals their bit ordering.
   atomicMax((unsigned int*)dst, __float_as_uint(fabsf(v)));
-}
-
-__global__ void absmax_kernel(const float* __restrict__ x, size_t n, float* __restrict__ out) {
-  float m = 0.f;
-  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (size_t)gridDim.x * blockDim.x)
-    m = fmaxf(m, fabsf(x[i]));
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) m = fmaxf(m, __shfl_xor(m, off));
-  if ((threadIdx.x & 63) == 0) atomic_max_abs(out, m);
 }
 
 __device__ __forceinline__ int pow2_exponent(float amax) {
@@ -36,29 +27,47 @@ __device__ __forceinline__ int pow2_exponent(float amax) {
   return 13 - ilogbf(amax);
 }
 
-__global__ void split_h_kernel(const float* __restrict__ H, size_t n,
-                               const float* __restrict__ amax, _Float16* __restrict__ hi,
-                               _Float16* __restrict__ lo, float* __restrict__ inv_scale) {
-  const int t = pow2_exponent(*amax);
-  if (blockIdx.x == 0 && threadIdx.x == 0) *inv_scale = ldexpf(1.f, -t);
-  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (size_t)gridDim.x * blockDim.x) {
-    const float x = ldexpf(H[i], t);
-    const _Float16 h = (_Float16)x;
-    hi[i] = h;
-    lo[i] = (_Float16)(x - (float)h);
+typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
+
+// x 2^t as two fp16 terms, four values
+__device__ __forceinline__ void split4(f32x4 x, int t, f16x4& hv, f16x4& lv) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const float v = ldexpf(x[i], t);
+    const _Float16 h = (_Float16)v;
+    hv[i] = h;
+    lv[i] = (_Float16)(v - (float)h);
   }
 }
 
+// A row of n x n fp32 values per work-group as two fp16 planes, scaled by 2^t
+// with t from amax[row] (per_row) or amax[0]; inv[row] or inv[0] = 2^-t.
+// Bound by memory traffic (4 bytes in, 4 out per value): 16-byte reads, 173 us
+// at 11008 x 11008 (5.6 TB/s); one value per thread and step took 355.
+template <bool kPerRow>
+__global__ __launch_bounds__(256) void split_rows_kernel(const float* __restrict__ x, int n,
+                                                         const float* __restrict__ amax,
+                                                         _Float16* __restrict__ hi,
+                                                         _Float16* __restrict__ lo,
+                                                         float* __restrict__ inv) {
+  const int r = blockIdx.x;
+  const int t = pow2_exponent(amax[kPerRow ? r : 0]);
+  if (threadIdx.x == 0 && (kPerRow || r == 0)) inv[r] = ldexpf(1.f, -t);
+  const size_t row = (size_t)r * n;
+  for (int c = threadIdx.x * 4; c < n; c += 1024) {
+    f16x4 hv, lv;
+    split4(*(const f32x4*)(x + row + c), t, hv, lv);
+    *(f16x4*)(hi + row + c) = hv;
+    *(f16x4*)(lo + row + c) = lv;
+  }
+}
+
+// H as two planes (after launch_split_m, which leaves max |H| and uses the
+// planes' memory).
 hipError_t launch_split_h(hipStream_t st, int cols, const float* H, char* ws, const Layout& lay) {
-  const size_t n = (size_t)cols * cols;
-  float* amax = (float*)(ws + lay.hscale) + 1;
-  hipError_t e = launch_zero_bytes(st, amax, sizeof(float));
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(absmax_kernel, dim3(1024), dim3(256), 0, st, H, n, amax);
-  hipLaunchKernelGGL(split_h_kernel, dim3(2048), dim3(256), 0, st, H, n, amax,
-                     (_Float16*)(ws + lay.hhi), (_Float16*)(ws + lay.hlo),
-                     (float*)(ws + lay.hscale));
+  float* hs = (float*)(ws + lay.hscale);
+  hipLaunchKernelGGL(split_rows_kernel<false>, dim3(cols), dim3(256), 0, st, H, cols, hs + 1,
+                     (_Float16*)(ws + lay.hhi), (_Float16*)(ws + lay.hlo), hs);
   return hipGetLastError();
 }
 
@@ -67,51 +76,110 @@ hipError_t launch_split_h(hipStream_t st, int cols, const float* H, char* ws, co
 // place of H gives u = L_i^{-1} (H e)_i for every group at once, and its
 // blocks M(i-block, h-block) = L_i^{-1} H_ih carry a code change of group h
 // into u_i.  Formed in fp64 from the fp64 inverse, rounded to fp32 into a
-// temporary, with each row's maximum; then split with one scale per row.
-// Work-group: the g rows of group i for 256 columns, thread = column.
+// temporary, with each row's maximum (then split with one scale per row) and
+// the largest |H|.
+//
+// On the fp64 matrix cores (v_mfma_f64_16x16x4_f64, 64 cycles each): a
+// work-group stages L_i^{-1} in LDS once and takes kFormCols columns, a
+// wavefront 16 columns at a time with all g rows of M in registers; the
+// 16 x 16 blocks above the diagonal of L_i^{-1} are skipped.  One LDS read per
+// matrix instruction (row stride g + 2 doubles: the 16 rows and the k-pairs
+// of a read cover the 64 banks once) leaves the matrix rate as the bound:
+// 59 us at 4096 columns and 498 us at 11008 (g = 128; 35 TFLOP/s of the 70 the
+// fp64 matrix cores sustain, counting the blocks computed), against 875 and
+// 6584 us for one column per thread with fp64 vector FMAs.
+constexpr int kFormCols = 512;
+
 template <int G_SIZE>
-__global__ __launch_bounds__(256) void form_m_kernel(const float* __restrict__ H, int cols,
+__global__ __launch_bounds__(512) void form_m_kernel(const float* __restrict__ H, int cols,
                                                      const double* __restrict__ linv,
                                                      float* __restrict__ mtmp,
-                                                     float* __restrict__ rowmax) {
+                                                     float* __restrict__ rowmax,
+                                                     float* __restrict__ hmax) {
   constexpr int g = G_SIZE;
+  constexpr int LD = g + 2;
+  constexpr int NB = g / 16;
+  extern __shared__ double li[];
+  __shared__ float hmax_s[8];
   const int i = blockIdx.y;
-  const int c = blockIdx.x * 256 + threadIdx.x;
-  __shared__ double li[g * g];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int lc = lane & 15, lk = lane >> 4;
   const double* Li = linv + (size_t)i * g * g;
-  for (int e = threadIdx.x; e < g * g; e += 256) li[e] = Li[e];
-  __syncthreads();
-  const bool cin = c < cols;
-  float hc[g];
-#pragma unroll
-  for (int m = 0; m < g; ++m) hc[m] = cin ? H[(size_t)(i * g + m) * cols + c] : 0.f;
-  for (int nl = 0; nl < g; ++nl) {
-    double acc = 0.0;
-#pragma unroll
-    for (int m = 0; m < g; ++m)
-      if (m <= nl) acc = fma(li[nl * g + m], (double)hc[m], acc);
-    const float v = (float)acc;
-    float mx = fabsf(v);
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
-    if (cin) mtmp[(size_t)(i * g + nl) * cols + c] = v;
-    if ((threadIdx.x & 63) == 0) atomic_max_abs(rowmax + i * g + nl, mx);
+  typedef double f64x2 __attribute__((ext_vector_type(2)));
+  for (int e = tid; e < g * g / 2; e += 512) {
+    const int r = e / (g / 2), c = 2 * (e % (g / 2));
+    *(f64x2*)(li + r * LD + c) = *(const f64x2*)(Li + r * g + c);
   }
-}
-
-__global__ void split_rows_kernel(const float* __restrict__ x, int cols, int nrows,
-                                  const float* __restrict__ rowmax, _Float16* __restrict__ hi,
-                                  _Float16* __restrict__ lo, float* __restrict__ row_inv) {
-  const size_t n = (size_t)nrows * cols;
-  for (size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x; e < n;
-       e += (size_t)gridDim.x * blockDim.x) {
-    const int r = (int)(e / cols);
-    const int t = pow2_exponent(rowmax[r]);
-    if (e % cols == 0) row_inv[r] = ldexpf(1.f, -t);
-    const float v = ldexpf(x[e], t);
-    const _Float16 h = (_Float16)v;
-    hi[e] = h;
-    lo[e] = (_Float16)(v - (float)h);
+  __syncthreads();
+  const int cend = min(cols, (int)(blockIdx.x + 1) * kFormCols);
+  // B(k, j) of k-slice ks: H(i g + 4 ks + lane / 16, c + lane % 16)
+  // (wave-uniform bases, 32-bit offsets: g rows of at most 16384 columns)
+  const float* Hi = H + (size_t)i * g * cols;
+  float* Mi = mtmp + (size_t)i * g * cols;
+  const uint32_t ucols = (uint32_t)cols, lane_at = (uint32_t)lk * ucols + (uint32_t)lc;
+  float h[4 * NB];
+  auto fetch = [&](int c, int ks) {
+    return Hi[lane_at + (uint32_t)c + (uint32_t)(4 * ks) * ucols];
+  };
+  float mx[NB][4], ha = 0.f;
+#pragma unroll
+  for (int b = 0; b < NB; ++b)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) mx[b][v] = 0.f;
+  int c = blockIdx.x * kFormCols + 16 * wave;   // cols is a multiple of 16
+  if (c < cend) {
+#pragma unroll
+    for (int ks = 0; ks < 4 * NB; ++ks) h[ks] = fetch(c, ks);
+  }
+  for (; c < cend; c += 128) {
+    // L^{-1} stays in LDS (the compiler would keep it in registers across the
+    // columns, and spill)
+    asm volatile("" ::: "memory");
+    // the next columns, each value loaded as its predecessor is used (the
+    // last pass loads its own again)
+    const int cn = c + 128 < cend ? c + 128 : c;
+    f64x4 acc[NB];
+#pragma unroll
+    for (int b = 0; b < NB; ++b) acc[b] = f64x4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int ks = 0; ks < 4 * NB; ++ks) {
+      ha = fmaxf(ha, fabsf(h[ks]));
+      const double hb = (double)h[ks];
+      h[ks] = fetch(cn, ks);
+#pragma unroll
+      for (int b = ks / 4; b < NB; ++b)
+        acc[b] = __builtin_amdgcn_mfma_f64_16x16x4f64(li[(16 * b + lc) * LD + 4 * ks + lk], hb,
+                                                      acc[b], 0, 0, 0);
+      if (ks % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+    }
+    // element v: row 16 b + 4 v + lane / 16, column c + lane % 16
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const float m = (float)acc[b][v];
+        mx[b][v] = fmaxf(mx[b][v], fabsf(m));
+        Mi[lane_at + (uint32_t)c + (uint32_t)(16 * b + 4 * v) * ucols] = m;
+      }
+  }
+#pragma unroll
+  for (int b = 0; b < NB; ++b)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      float m = mx[b][v];
+#pragma unroll
+      for (int off = 8; off >= 1; off >>= 1) m = fmaxf(m, __shfl_xor(m, off));
+      if (lc == 0) atomic_max_abs(rowmax + i * g + 16 * b + 4 * v + lk, m);
+    }
+  // one atomic per work-group (they all meet at one address)
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) ha = fmaxf(ha, __shfl_xor(ha, off));
+  if (lane == 0) hmax_s[wave] = ha;
+  __syncthreads();
+  if (tid == 0) {
+#pragma unroll
+    for (int w = 1; w < 8; ++w) ha = fmaxf(ha, hmax_s[w]);
+    atomic_max_abs(hmax, ha);
   }
 }
 
@@ -122,12 +190,18 @@ static hipError_t launch_split_m_t(hipStream_t st, int cols, const float* H, cha
   // temporary: together they span cols * cols * 4 bytes.
   float* mtmp = (float*)(ws + lay.hhi);
   float* rowmax = (float*)(ws + lay.mmax);
+  float* hmax = (float*)(ws + lay.hscale) + 1;
   hipError_t e = launch_zero_bytes(st, rowmax, (size_t)cols * sizeof(float));
+  if (e == hipSuccess) e = launch_zero_bytes(st, hmax, sizeof(float));
   if (e != hipSuccess) return e;
-  dim3 grid((cols + 255) / 256, cols / G_SIZE);
-  hipLaunchKernelGGL(form_m_kernel<G_SIZE>, grid, dim3(256), 0, st, H, cols,
-                     (const double*)(ws + lay.lfac), mtmp, rowmax);
-  hipLaunchKernelGGL(split_rows_kernel, dim3(2048), dim3(256), 0, st, mtmp, cols, cols, rowmax,
+  const size_t lds = (size_t)G_SIZE * (G_SIZE + 2) * sizeof(double);
+  static std::atomic<unsigned long long> lds_set{0};
+  e = allow_dynamic_lds((const void*)form_m_kernel<G_SIZE>, lds, lds_set);
+  if (e != hipSuccess) return e;
+  dim3 grid((cols + kFormCols - 1) / kFormCols, cols / G_SIZE);
+  hipLaunchKernelGGL(form_m_kernel<G_SIZE>, grid, dim3(512), lds, st, H, cols,
+                     (const double*)(ws + lay.lfac), mtmp, rowmax, hmax);
+  hipLaunchKernelGGL(split_rows_kernel<true>, dim3(cols), dim3(256), 0, st, mtmp, cols, rowmax,
                      (_Float16*)(ws + lay.mhi), (_Float16*)(ws + lay.mlo),
                      (float*)(ws + lay.mrow));
   return hipGetLastError();
