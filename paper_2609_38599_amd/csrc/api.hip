@@ -209,16 +209,15 @@ jarq_status prepare_impl(const jarq_params* p, const float* W, const float* H, v
   JQ_HIP(launch_split_r(c.st, c.cols, c.g, c.ws, c.lay));
   JQ_HIP(launch_split_m(c.st, c.cols, c.g, H, c.ws, c.lay));
   JQ_HIP(launch_split_h(c.st, c.cols, H, c.ws, c.lay));
-  JQ_HIP(launch_gemm_ah(c.st, c.rows, c.cols, c.g, false, W, nullptr, nullptr, nullptr, H, c.wh(),
-                        nullptr));
   // T = W M^T and RW = W_i L_i, the constant parts of the residual product
-  // and of the objective; W's two fp16 planes borrow P's memory
+  // and of the objective, and W H from T; W's two fp16 planes borrow P's memory
   _Float16* whi = (_Float16*)c.pbuf();
   _Float16* wlo = whi + (size_t)c.rows * c.cols;
   float* wrow = (float*)(c.ws + c.lay.wrow);
   JQ_HIP(launch_split_w(c.st, c.rows, c.cols, W, whi, wlo, wrow));
   JQ_HIP(launch_wm_product(c.st, c.rows, c.cols, c.ws, c.lay, whi, wlo, wrow));
   JQ_HIP(launch_rw_product(c.st, c.rows, c.cols, c.g, c.ws, c.lay, whi, wlo, wrow));
+  JQ_HIP(launch_wh(c.st, c.rows, c.cols, c.g, c.ws, c.lay));
   Flags f{};
   JQ_HIP(hipMemcpyAsync(&f, c.flags(), sizeof(Flags), hipMemcpyDeviceToHost, c.st));
   JQ_HIP(hipStreamSynchronize(c.st));
@@ -621,8 +620,8 @@ jarq_status jarq_objective(const jarq_params* p, const float* W, const float* H,
   jarq_status s = check_ws(p, workspace, workspace_bytes);
   if (s != JARQ_OK) return s;
   Ctx c = make_ctx(p, workspace, stream);
-  if (launch_gemm_ah(c.st, c.rows, c.cols, c.g, true, W, codes, scales, zeros, H, nullptr,
-                     c.objpart()) != hipSuccess)
+  if (launch_row_products(c.st, c.rows, c.cols, c.g, W, codes, scales, zeros, H, c.objpart()) !=
+      hipSuccess)
     return JARQ_EHIP;
   if (launch_row_objective(c.st, c.rows, c.nt(), c.objpart(), row_objective) != hipSuccess)
     return JARQ_EHIP;

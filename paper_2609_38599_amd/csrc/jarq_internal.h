@@ -159,12 +159,13 @@ hipError_t launch_chol_groups(hipStream_t st, int cols, int g, const float* H, c
 // R_i rows as two fp16 terms with per-row power-of-two scales (rph, rpl, rrow).
 hipError_t launch_split_r(hipStream_t st, int cols, int g, char* ws, const Layout& lay);
 
-// C = A H with A = W (quant == false) or A = W - What (quant == true).  When
-// objpart is non-null, objpart[row][col/64] receives sum over the 64-column
-// slice of A(row, c) * C(row, c) in fp64.  C may be null (objective only).
-hipError_t launch_gemm_ah(hipStream_t st, int rows, int cols, int g, bool quant,
-                          const float* W, const uint8_t* codes, const float* scales,
-                          const int32_t* zeros, const float* H, float* C, double* objpart);
+// objpart[row][col / 64] = sum over the 64-column slice of E(row, c) (E H)(row, c)
+// in fp64, E = W - What.
+hipError_t launch_row_products(hipStream_t st, int rows, int cols, int g, const float* W,
+                               const uint8_t* codes, const float* scales, const int32_t* zeros,
+                               const float* H, double* objpart);
+// W H (lay.wh) from T = W M^T and R_i.
+hipError_t launch_wh(hipStream_t st, int rows, int cols, int g, char* ws, const Layout& lay);
 
 hipError_t launch_split_h(hipStream_t st, int cols, const float* H, char* ws, const Layout& lay);
 // M = blockdiag(L_i^{-1}) H as two fp16 planes with per-row scales (after
