@@ -11,107 +11,150 @@
 //   column k is rounded from  w_k + (sum_{i<k} M_ki e_i) / M_kk,
 // and the compensated weights of a whole group G at its first column are
 //   w_G + M_GG^{-1} (M_GP e_P),   P = the columns before G
-// (the group's block of the triangular system restricted to the prefix).  The
-// product M_GP e_P for every row is one fp64 matrix product per group (split
-// over k into partial slices, summed in a fixed order); the triangular parts
-// run per row, sixteen lanes per row.
+// (the group's block of the triangular system restricted to the prefix).
+//
+// comp [rows][cols] holds sum_i M_ki e_i over the columns i handled so far.
+// Columns go in panels of kPanel: before a group the contributions of the
+// panel's earlier groups are added (one product of at most kPanel columns),
+// after a panel those of the whole panel to every later column, so most of the
+// rows cols^2 work is in a few large products (linalg.hip).  A group's errors
+// take the place of its sums.  The triangular parts run per row, sixteen lanes
+// per row.
 #include "jarq_internal.h"
 
 namespace jarq {
 
 namespace {
-constexpr int kGptqKSlice = 512;   // k-slice of the per-group products
+constexpr int kPanel = 512;   // columns per panel, a multiple of every group size
+
+template <int V>
+struct Step {
+  static constexpr int value = V;
+};
+template <int K, int N>
+struct Steps {
+  template <typename F>
+  static __device__ __forceinline__ void run(F&& f) {
+    if constexpr (K < N) {
+      f(Step<K>{});
+      Steps<K + 1, N>::run(f);
+    }
+  }
+};
+
+// Value of lane JL of each row of 16 lanes, in every lane of that row.
+template <int JL>
+__device__ __forceinline__ double row_share(double v) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)u, 0x150 + JL, 0xf, 0xf, false);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)(u >> 32), 0x150 + JL, 0xf, 0xf, false);
+  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
 }
+}  // namespace
 
 size_t gptq_workspace_bytes(int rows, int cols, int g) {
   const size_t R = rows, C = cols;
-  const int kmax = cols - g;
-  const size_t ns = kmax > 0 ? (size_t)((kmax + kGptqKSlice - 1) / kGptqKSlice) : 1;
   auto a = [](size_t x) { return (x + 255) & ~size_t(255); };
-  return a(C * C * 8) + a(C * C * 8) + a(R * C * 8) + a(ns * R * g * 8) + a(64 * 64 * 8) + a(4);
+  return a(C * C * 8) + a(C * C * 8) + a(R * C * 8) + a(2 * 64 * 64 * 8) + a(4);
 }
 
-// Sixteen lanes per row (16 rows per 256-thread work-group): lane j owns the
-// group positions n = j + 16 t (t = 0 .. g/16 - 1) and keeps their values in
-// registers.  Each of the g sequential steps m forms sum_{n<m} M_mn v_n as
-// per-lane partial sums reduced over the row's lanes; the owner of m takes
-// the step.  Pass 1: y = M_GG^{-1} c and the group's grid from w + y (0 forced
-// into the range); pass 2: the columns in order, each rounded from
+// Sixteen lanes per row (blockDim / 16 rows per work-group): lane j owns the
+// group positions n = j + 16 t (t = 0 .. g/16 - 1) and keeps their sums in
+// registers.  The g sequential steps are column-oriented: at step n every lane
+// forms the candidate value of its own position, that of the owner reaches the
+// row by a DPP broadcast, and each lane subtracts or adds M(m, n) times it to
+// the sums of its positions m > n.  (A dot product over the row's lanes at
+// every step, with an fp64 division on it, made a chain about six times as
+// long: 86 us for 4096 rows at g = 128, now @GROUPT@.)  Nothing is recorded at a
+// step: a position's sum is final once its step has come, so its value is
+// formed again from it afterwards.
+// Pass 1: y = M_GG^{-1} c and the group's grid from w + y (0 forced into the
+// range); pass 2: the columns in order, each rounded from
 // w_m + (c_m + sum_{n<m} M_mn e_n) / M_mm.
+// M_GG sits in LDS column by column (element (m, n) at n (g + 1) + m, zero on
+// and above the diagonal), so the lanes of a row read consecutive values.
+//
+// x / s of the rounding is the correctly rounded quotient, as a division
+// gives it: q0 = x (1 / s), then q0 + (x - q0 s) (1 / s) with fused
+// multiply-adds; q0 is held to the codes' range first, so that an infinite x
+// keeps its sign (a NaN rounds to code 0 either way).
 template <int G_SIZE>
-__global__ __launch_bounds__(256) void gptq_group_kernel(int rows, int cols, int bits, int grp,
+__global__ __launch_bounds__(512) void gptq_group_kernel(int rows, int cols, int bits, int grp,
                                                          const float* __restrict__ W,
                                                          const double* __restrict__ M,
-                                                         const double* __restrict__ comp,
-                                                         int nsplit, double* __restrict__ E,
+                                                         double* __restrict__ comp, int has_comp,
                                                          uint8_t* __restrict__ codes,
                                                          float* __restrict__ scales,
                                                          int32_t* __restrict__ zeros) {
   constexpr int g = G_SIZE;
   constexpr int NT = g / 16;
-  const int j = threadIdx.x & 15;
-  const int r = blockIdx.x * 16 + (threadIdx.x >> 4);
+  constexpr int LD = g + 1;
+  extern __shared__ double mc[];     // g x LD, then 1 / M_mm
+  double* minv = mc + g * LD;
+  const int tid = threadIdx.x;
+  const int j = tid & 15;
+  const int r = blockIdx.x * (blockDim.x >> 4) + (tid >> 4);
   const bool live = r < rows;
   const int rr = live ? r : rows - 1;
   const int b0 = grp * g;
   const int G = cols / g;
   const double qmax = (double)((1 << bits) - 1);
-  const double* Mg = M + (long long)b0 * cols + b0;   // M_GG: Mg[m * cols + n], n <= m
-  const float* w = W + (long long)rr * cols + b0;
-  const long long cstride = (long long)rows * g;
-  double cl[NT], wl[NT], vl[NT];
+  double cl[NT], wl[NT], acc[NT], inv[NT];
+  {
+    const float* w = W + (long long)rr * cols + b0 + j;
+    const double* c = comp + (long long)rr * cols + b0 + j;
 #pragma unroll
-  for (int t = 0; t < NT; ++t) {
-    const int n = j + 16 * t;
-    double c = 0.0;
-    for (int z = 0; z < nsplit; ++z) c += comp[z * cstride + (long long)rr * g + n];
-    cl[t] = c;
-    wl[t] = (double)w[n];
-    vl[t] = 0.0;
+    for (int t = 0; t < NT; ++t) {
+      wl[t] = (double)w[16 * t];
+      cl[t] = has_comp ? c[16 * t] : 0.0;
+    }
   }
-  // Row m of M_GG at this lane's positions, loaded one step ahead into the
-  // buffer of the other step parity (no register copies: a copy would wait
-  // for the loads in flight).  The last step reloads row g - 1 (in bounds).
-  double ma[NT], mb[NT];
-  auto load_row = [&](int m, double (&dst)[NT]) __attribute__((always_inline)) {
-    const double* mrow = Mg + (long long)(m < g ? m : g - 1) * cols + j;
+  {
+    // M_GG by rows, two values a load, eight loads in flight a thread (the
+    // part above the diagonal is read and dropped)
+    typedef double f64x2 __attribute__((ext_vector_type(2)));
+    constexpr int NE = g * g / 2, BATCH = NE < 2048 ? NE / 256 : 8;
+    const double* Mg = M + (long long)b0 * cols + b0;
+    for (int e0 = tid; e0 < NE; e0 += BATCH * blockDim.x) {
+      f64x2 v[BATCH];
 #pragma unroll
-    for (int t2 = 0; t2 < NT; ++t2) dst[t2] = mrow[16 * t2];
-  };
-  // sum_{n < m} M_mn v_n over the row's lanes (positions of earlier blocks, and
-  // of block t those before m), with mrow = row m at this lane's positions
-  auto row_dot = [&](int t, int i, const double (&mrow)[NT]) __attribute__((always_inline)) {
-    double part = 0.0;
+      for (int u = 0; u < BATCH; ++u) {
+        const int e = min(e0 + u * (int)blockDim.x, NE - 1);
+        v[u] = *(const f64x2*)(Mg + (long long)(e / (g / 2)) * cols + 2 * (e % (g / 2)));
+      }
 #pragma unroll
-    for (int t2 = 0; t2 < NT; ++t2)
-      if (t2 < t) part = fma(mrow[t2], vl[t2], part);
-    if (j < i) part = fma(mrow[t], vl[t], part);
+      for (int u = 0; u < BATCH; ++u) {
+        const int e = e0 + u * (int)blockDim.x;
+        if (e < NE) {
+          const int m = e / (g / 2), n = 2 * (e % (g / 2));
 #pragma unroll
-    for (int off = 8; off >= 1; off >>= 1) part += __shfl_xor(part, off);
-    return part;
-  };
-
-  // pass 1: y = M_GG^{-1} c, grid from w + y
-  double lo = 0.0, hi = 0.0;
-  auto step1 = [&](int t, int i, const double (&mrow)[NT]) __attribute__((always_inline)) {
-    const double part = row_dot(t, i, mrow);
-    if (j == i) {
-      const double y = (cl[t] - part) / mrow[t];   // the owner's mrow[t] is M_mm
-      vl[t] = y;
-      const double v = wl[t] + y;
-      lo = fmin(lo, v);
-      hi = fmax(hi, v);
+          for (int q = 0; q < 2; ++q) {
+            mc[(n + q) * LD + m] = n + q < m ? v[u][q] : 0.0;
+            if (n + q == m) minv[m] = 1.0 / v[u][q];
+          }
+        }
+      }
     }
-  };
-  load_row(0, ma);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int t = 0; t < NT; ++t) inv[t] = minv[j + 16 * t];
+
+  // pass 1: y = M_GG^{-1} c
+#pragma unroll
+  for (int t = 0; t < NT; ++t) acc[t] = cl[t];
+  Steps<0, g>::run([&](auto nc) __attribute__((always_inline)) {
+    constexpr int n = decltype(nc)::value;
+    const double y = row_share<n % 16>(acc[n / 16] * inv[n / 16]);
+#pragma unroll
+    for (int t = n / 16; t < NT; ++t) acc[t] = fma(-mc[n * LD + j + 16 * t], y, acc[t]);
+  });
+  double lo = 0.0, hi = 0.0;
 #pragma unroll
   for (int t = 0; t < NT; ++t) {
-    for (int i = 0; i < 16; i += 2) {
-      load_row(16 * t + i + 1, mb);
-      step1(t, i, ma);
-      load_row(16 * t + i + 2, ma);
-      step1(t, i + 1, mb);
-    }
+    const double v = wl[t] + acc[t] * inv[t];
+    lo = fmin(lo, v);
+    hi = fmax(hi, v);
   }
 #pragma unroll
   for (int off = 8; off >= 1; off >>= 1) {
@@ -122,37 +165,33 @@ __global__ __launch_bounds__(256) void gptq_group_kernel(int rows, int cols, int
   const float s32 = (float)s;
   const double s64 = (double)s32;
   const double zp = fmin(fmax(rint(-lo / s64), 0.0), qmax);
+  const double sinv = 1.0 / s64;
+  const double qlo = -zp - 1.0, qhi = qmax - zp + 1.0;
 
-  // pass 2: the columns in order (vl now takes the errors e = w - s (q - z))
-  uint8_t ql[NT];
-#pragma unroll
-  for (int t = 0; t < NT; ++t) ql[t] = 0;
-  auto step2 = [&](int t, int i, const double (&mrow)[NT]) __attribute__((always_inline)) {
-    const double part = row_dot(t, i, mrow);
-    if (j == i) {
-      const double x = wl[t] + (cl[t] + part) / mrow[t];
-      const double q = fmin(fmax(rint(x / s64) + zp, 0.0), qmax);
-      vl[t] = wl[t] - s64 * (q - zp);
-      ql[t] = (uint8_t)q;
-    }
+  // pass 2: the columns in order
+  auto code_of = [&](int t) __attribute__((always_inline)) {
+    const double x = fma(acc[t], inv[t], wl[t]);
+    const double q0 = fmin(fmax(x * sinv, qlo), qhi);
+    const double q1 = fma(fma(-q0, s64, x), sinv, q0);
+    return fmin(fmax(rint(q1) + zp, 0.0), qmax);
   };
-  load_row(0, ma);
 #pragma unroll
-  for (int t = 0; t < NT; ++t) {
-    for (int i = 0; i < 16; i += 2) {
-      load_row(16 * t + i + 1, mb);
-      step2(t, i, ma);
-      load_row(16 * t + i + 2, ma);
-      step2(t, i + 1, mb);
-    }
-  }
+  for (int t = 0; t < NT; ++t) acc[t] = cl[t];
+  Steps<0, g>::run([&](auto nc) __attribute__((always_inline)) {
+    constexpr int n = decltype(nc)::value;
+    const double q = code_of(n / 16);
+    const double e = row_share<n % 16>(fma(-s64, q - zp, wl[n / 16]));
+#pragma unroll
+    for (int t = n / 16; t < NT; ++t) acc[t] = fma(mc[n * LD + j + 16 * t], e, acc[t]);
+  });
   if (live) {
-    uint8_t* q_out = codes + (long long)r * cols + b0;
-    double* e_out = E + (long long)r * cols + b0;
+    uint8_t* q_out = codes + (long long)r * cols + b0 + j;
+    double* e_out = comp + (long long)r * cols + b0 + j;
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
-      q_out[j + 16 * t] = ql[t];
-      e_out[j + 16 * t] = vl[t];
+      const double q = code_of(t);
+      q_out[16 * t] = (uint8_t)q;
+      e_out[16 * t] = fma(-s64, q - zp, wl[t]);
     }
     if (j == 0) {
       scales[(long long)r * G + grp] = s32;
@@ -163,18 +202,26 @@ __global__ __launch_bounds__(256) void gptq_group_kernel(int rows, int cols, int
 
 template <int G_SIZE>
 static hipError_t launch_gptq_group_t(hipStream_t st, int rows, int cols, int bits, int grp,
-                                      const float* W, const double* M, const double* comp,
-                                      int nsplit, double* E, uint8_t* codes, float* scales,
-                                      int32_t* zeros) {
-  hipLaunchKernelGGL(gptq_group_kernel<G_SIZE>, dim3((rows + 15) / 16), dim3(256), 0, st, rows,
-                     cols, bits, grp, W, M, comp, nsplit, E, codes, scales, zeros);
+                                      const float* W, const double* M, double* comp, int has_comp,
+                                      uint8_t* codes, float* scales, int32_t* zeros) {
+  const size_t lds = ((size_t)G_SIZE * (G_SIZE + 1) + G_SIZE) * sizeof(double);
+  static std::atomic<unsigned long long> lds_set{0};
+  hipError_t e = allow_dynamic_lds((const void*)gptq_group_kernel<G_SIZE>, lds, lds_set);
+  if (e != hipSuccess) return e;
+  // One work-group's copy of M_GG fills most of a compute unit's LDS at
+  // g = 128: up to 16 rows for each of 256 units the rows are spread over all of
+  // them; with more, 32 rows share a copy and two wavefronts a SIMD hide each
+  // other's latency.
+  const int threads = rows <= 4096 ? 256 : 512;
+  hipLaunchKernelGGL(gptq_group_kernel<G_SIZE>, dim3((rows + threads / 16 - 1) / (threads / 16)),
+                     dim3(threads), lds, st, rows, cols, bits, grp, W, M, comp, has_comp, codes,
+                     scales, zeros);
   return hipGetLastError();
 }
 
-// The whole host: factor the reversed Hessian, form M, then group by group the
-// product M_GP e_P and the per-row triangular passes.  Returns the HIP error
-// of the first failed launch; *flag (device) is set when H is not positive
-// definite.
+// The whole host: factor the reversed Hessian, form M, then the groups in
+// order.  Returns the HIP error of the first failed launch; *flag (device) is
+// set when H is not positive definite.
 hipError_t launch_gptq(hipStream_t st, int rows, int cols, int g, int bits, const float* W,
                        const float* H, char* ws, uint8_t* codes, float* scales, int32_t* zeros,
                        int** flag_out) {
@@ -182,12 +229,9 @@ hipError_t launch_gptq(hipStream_t st, int rows, int cols, int g, int bits, cons
   const size_t CC = (size_t)cols * cols * 8;
   double* Cf = (double*)ws;
   double* M = (double*)(ws + a(CC));
-  double* E = (double*)(ws + 2 * a(CC));
-  double* comp = (double*)(ws + 2 * a(CC) + a((size_t)rows * cols * 8));
-  const int kmax = cols - g;
-  const size_t ns = kmax > 0 ? (size_t)((kmax + kGptqKSlice - 1) / kGptqKSlice) : 1;
-  double* Linv = (double*)((char*)comp + a(ns * rows * g * 8));
-  int* flag = (int*)((char*)Linv + a(64 * 64 * 8));
+  double* comp = (double*)(ws + 2 * a(CC));
+  double* Linv = (double*)((char*)comp + a((size_t)rows * cols * 8));
+  int* flag = (int*)((char*)Linv + a(2 * 64 * 64 * 8));
   *flag_out = flag;
   hipError_t e = launch_zero_bytes(st, flag, sizeof(int));
   if (e != hipSuccess) return e;
@@ -197,23 +241,30 @@ hipError_t launch_gptq(hipStream_t st, int rows, int cols, int g, int bits, cons
   if (e != hipSuccess) return e;
   e = launch_antitranspose_lower(st, Cf, cols, M);
   if (e != hipSuccess) return e;
-  const int G = cols / g;
-  for (int grp = 0; grp < G; ++grp) {
-    const int b0 = grp * g;
-    const int nsplit = b0 > 0 ? (b0 + kGptqKSlice - 1) / kGptqKSlice : 0;
-    if (b0 > 0) {
-      // comp[z][r][m] = sum_{t in slice z} E[r][t] M[b0 + m][t]
-      e = launch_gemm_nt_f64(st, false, rows, g, b0, kGptqKSlice, 1.0, E, cols,
-                             M + (long long)b0 * cols, cols, comp, g, (long long)rows * g, false);
+  const long long d = cols;
+  for (int p0 = 0; p0 < cols; p0 += kPanel) {
+    const int p1 = p0 + kPanel < cols ? p0 + kPanel : cols;
+    for (int b0 = p0; b0 < p1; b0 += g) {
+      const int grp = b0 / g;
+      if (b0 > p0) {
+        // comp_G (+)= E(panel so far) M(G, panel so far)^T
+        e = launch_gemm_nt_f64(st, rows, g, b0 - p0, 1.0, comp + p0, d, M + b0 * d + p0, d,
+                               comp + b0, d, p0 > 0);
+        if (e != hipSuccess) return e;
+      }
+      switch (g) {
+        case 32: e = launch_gptq_group_t<32>(st, rows, cols, bits, grp, W, M, comp, b0 > 0, codes, scales, zeros); break;
+        case 64: e = launch_gptq_group_t<64>(st, rows, cols, bits, grp, W, M, comp, b0 > 0, codes, scales, zeros); break;
+        case 128: e = launch_gptq_group_t<128>(st, rows, cols, bits, grp, W, M, comp, b0 > 0, codes, scales, zeros); break;
+        default: return hipErrorInvalidValue;
+      }
       if (e != hipSuccess) return e;
     }
-    switch (g) {
-      case 32: e = launch_gptq_group_t<32>(st, rows, cols, bits, grp, W, M, comp, nsplit, E, codes, scales, zeros); break;
-      case 64: e = launch_gptq_group_t<64>(st, rows, cols, bits, grp, W, M, comp, nsplit, E, codes, scales, zeros); break;
-      case 128: e = launch_gptq_group_t<128>(st, rows, cols, bits, grp, W, M, comp, nsplit, E, codes, scales, zeros); break;
-      default: return hipErrorInvalidValue;
+    if (p1 < cols) {
+      e = launch_gemm_nt_f64(st, rows, cols - p1, p1 - p0, 1.0, comp + p0, d, M + p1 * d + p0, d,
+                             comp + p1, d, p0 > 0);
+      if (e != hipSuccess) return e;
     }
-    if (e != hipSuccess) return e;
   }
   return hipSuccess;
 }

@@ -333,18 +333,16 @@ hipError_t launch_rtn(hipStream_t st, const float* W, int rows, int cols, int g,
                       uint8_t* codes, float* scales, int32_t* zeros);
 
 // Dense fp64 building blocks (linalg.hip).
-hipError_t launch_gemm_nt_f64(hipStream_t st, bool lower, int M, int N, int K, int kslice,
-                              double alpha, const double* A, long long lda, const double* B,
-                              long long ldb, double* C, long long ldc, long long cz,
-                              bool accumulate);
-// C_z = alpha A B over k-slice z (B k-major [K][N]), slice z stored at C + z cz.
-hipError_t launch_gemm_nn_f64_sliced(hipStream_t st, int M, int N, int K, int kslice,
-                                     double alpha, const double* A, long long lda,
-                                     const double* B, long long ldb, double* C, long long ldc,
-                                     long long cz);
+// C (+)= alpha A B over M x N, K a multiple of 16, N even: nt takes B [N][K],
+// nn B [K][N]; `batch` products at strides az, bz, cz.
+hipError_t launch_gemm_nt_f64(hipStream_t st, int M, int N, int K, double alpha, const double* A,
+                              long long lda, const double* B, long long ldb, double* C,
+                              long long ldc, bool accumulate, int batch = 1, long long az = 0,
+                              long long bz = 0, long long cz = 0);
 hipError_t launch_gemm_nn_f64(hipStream_t st, int M, int N, int K, double alpha, const double* A,
                               long long lda, const double* B, long long ldb, double* C,
-                              long long ldc, bool accumulate);
+                              long long ldc, bool accumulate, int batch = 1, long long az = 0,
+                              long long bz = 0, long long cz = 0);
 hipError_t launch_potrf_f64(hipStream_t st, double* A, int d, long long lda, double* Linv,
                             int* flag, bool keep_inverses);
 hipError_t launch_copy_lower(hipStream_t st, const float* H, int d, bool reverse, double* C);

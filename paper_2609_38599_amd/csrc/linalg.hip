@@ -1,261 +1,376 @@
 // Dense fp64 kernels of the per-layer set-up: a blocked Cholesky factorization
-// and the matrix products it and the GPTQ-style host are built from.
-//
-// Cholesky (right-looking, 64-column blocks): for each diagonal block,
-// factor it in LDS and invert its factor (one work-group), scale the panel
-// below by the inverse transpose, and subtract the panel's outer product from
-// the lower triangle of the trailing matrix.  Everything is fp64; the MI355X
-// runs fp64 vector FMAs at the rate of its fp64 matrix cores, so the products
-// are register-blocked vector code.
-#include "jarq_internal.h"
+// and the matrix products it, the GPTQ-style host and the corrected target are
+// built from.  Products run on the fp64 matrix cores
+// (v_mfma_f64_16x16x4_f64, 64 cycles each: 70 TFLOP/s sustained); a vector
+// version of the same tiles reached about a third of that, bound by its LDS
+// reads (eight operands for sixteen FMAs, where a matrix instruction takes two
+// per lane for its 1024).
+#include "chol64.h"
 
 namespace jarq {
 
 namespace {
-constexpr int LT = 64;   // output tile edge of the products, and the Cholesky block size
-constexpr int LK = 16;   // k-step of the products
-constexpr int LP = LT + 4;
+constexpr int LT = 64;   // Cholesky block size
+constexpr int KB = 16;   // k-step of the products
+// two doubles from an address that is only 8-byte aligned
+typedef double f64x2 __attribute__((ext_vector_type(2)));
+typedef double f64x2_u __attribute__((ext_vector_type(2), aligned(8)));
 }  // namespace
 
-// C[i][j] (+)= alpha sum_{k in slice z} A[i][k] B(j, k) for i < M, j < N, with
-// B(j, k) = B[j][k] (B row-major over j) or, when BK, B[k][j] (row-major over k),
-// the k range split into slices of `kslice` (slice z = blockIdx.z writes
-// C + z * cz).  LOWER: only j <= i is computed and written (tiles wholly above
-// the diagonal exit at once).  A work-group reads rows i0..i0+63 of A and
-// j0..j0+63 of B for its own k range before it writes its tile, so A may
-// alias C when N <= 64 and the tile's k range is all of K (the panel step).
-template <bool LOWER, bool BK>
-__global__ __launch_bounds__(256) void gemm_nt_f64_kernel(int M, int N, int K, int kslice,
-                                                          double alpha, const double* A,
-                                                          long long lda, const double* B,
-                                                          long long ldb, double* C,
+// C[i][j] (+)= alpha sum_k A[i][k] B(j, k) for i < M, j < N, with B(j, k) =
+// B[j][k], or B[k][j] when BK.  K is a multiple of 16.  blockIdx.z picks one of
+// a batch of products (strides az, bz, cz).  C must not overlap A or B.
+//
+// TM x TN output tile per 256-thread work-group, 2 x 2 wavefronts, k in steps
+// of 16 through two LDS stages; the next step's values are loaded into
+// registers during the current one's products.  Row-major operand tiles have
+// rows of 18 doubles and k-major ones rows of TN + 16: a fragment read (16 rows
+// or columns at four k) covers the 64 banks once per half wave.
+template <int TM, int TN, bool BK>
+__global__ __launch_bounds__(256, 2) void gemm_f64_kernel(int M, int N, int K, double alpha,
+                                                          const double* __restrict__ A,
+                                                          long long lda, long long az,
+                                                          const double* __restrict__ B,
+                                                          long long ldb, long long bz, double* C,
                                                           long long ldc, long long cz,
                                                           int accumulate) {
-  const int i0 = blockIdx.y * LT, j0 = blockIdx.x * LT;
-  if (LOWER && j0 > i0 + LT - 1) return;
-  __shared__ double as[LK][LP];
-  __shared__ double bs[LK][LP];
-  const int tid = threadIdx.x;
-  const int tx = tid & 15, ty = tid >> 4;
-  const int k_begin = blockIdx.z * kslice;
-  const int k_end = min(K, k_begin + kslice);
+  constexpr int LDR = KB + 2;                  // row stride of a row-major tile
+  constexpr int LDK = TN + 16;                 // row stride of a k-major tile
+  constexpr int ASZ = TM * LDR, BSZ = BK ? KB * LDK : TN * LDR;
+  constexpr int MB = TM / 32, NB = TN / 32;    // 16 x 16 blocks per wavefront
+  constexpr int APT = TM * KB / 512, BPT = TN * KB / 512;  // 16-byte loads per thread
+  __shared__ __attribute__((aligned(16))) double as[2][ASZ];
+  __shared__ __attribute__((aligned(16))) double bs[2][BSZ];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int wm = wave >> 1, wn = wave & 1;
+  const int lc = lane & 15, lk = lane >> 4;
+  const int i0 = blockIdx.y * TM, j0 = blockIdx.x * TN;
+  A += (long long)blockIdx.z * az;
+  B += (long long)blockIdx.z * bz;
   C += (long long)blockIdx.z * cz;
-  double acc[4][4];
+  // rows and columns past the edge repeat the last one; their results are not
+  // stored
+  const double* ap[APT];
+  const double* bp[BPT];
 #pragma unroll
-  for (int u = 0; u < 4; ++u)
+  for (int u = 0; u < APT; ++u) {
+    const int e = tid + 256 * u;
+    ap[u] = A + (long long)min(i0 + (e >> 3), M - 1) * lda + 2 * (e & 7);
+  }
 #pragma unroll
-    for (int v = 0; v < 4; ++v) acc[u][v] = 0.0;
-  // Loads: thread t takes row t / 4 of the tile and 4 consecutive k at 4 (t % 4).
-  const int lr = tid >> 2, lk = (tid & 3) * 4;
-  for (int k0 = k_begin; k0 < k_end; k0 += LK) {
-    double ra[4], rb[4];
+  for (int u = 0; u < BPT; ++u) {
+    const int e = tid + 256 * u;
+    if (BK)
+      bp[u] = B + (long long)(e / (TN / 2)) * ldb + min(j0 + 2 * (e % (TN / 2)), N - 2);
+    else
+      bp[u] = B + (long long)min(j0 + (e >> 3), N - 1) * ldb + 2 * (e & 7);
+  }
+  f64x2 ra[APT], rb[BPT];
+  auto load = [&](int k0) {
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int k = k0 + lk + u;
-      const bool kin = k < k_end;
-      ra[u] = (kin && i0 + lr < M) ? A[(long long)(i0 + lr) * lda + k] : 0.0;
-      if (BK) {
-        // thread t: k row t / 16, four consecutive j at 4 (t % 16)
-        const int kb = k0 + (tid >> 4), jb = j0 + (tid & 15) * 4 + u;
-        rb[u] = (kb < k_end && jb < N) ? B[(long long)kb * ldb + jb] : 0.0;
-      } else {
-        rb[u] = (kin && j0 + lr < N) ? B[(long long)(j0 + lr) * ldb + k] : 0.0;
-      }
+    for (int u = 0; u < APT; ++u) ra[u] = *(const f64x2_u*)(ap[u] + k0);
+#pragma unroll
+    for (int u = 0; u < BPT; ++u)
+      rb[u] = *(const f64x2_u*)(bp[u] + (BK ? (long long)k0 * ldb : (long long)k0));
+  };
+  auto stage = [&](int s) {
+#pragma unroll
+    for (int u = 0; u < APT; ++u) {
+      const int e = tid + 256 * u;
+      *(f64x2*)&as[s][(e >> 3) * LDR + 2 * (e & 7)] = ra[u];
     }
-    __syncthreads();
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      as[lk + u][lr] = ra[u];
+    for (int u = 0; u < BPT; ++u) {
+      const int e = tid + 256 * u;
       if (BK)
-        bs[tid >> 4][(tid & 15) * 4 + u] = rb[u];
+        *(f64x2*)&bs[s][(e / (TN / 2)) * LDK + 2 * (e % (TN / 2))] = rb[u];
       else
-        bs[lk + u][lr] = rb[u];
+        *(f64x2*)&bs[s][(e >> 3) * LDR + 2 * (e & 7)] = rb[u];
     }
-    __syncthreads();
+  };
+  f64x4 acc[MB][NB];
 #pragma unroll
-    for (int k = 0; k < LK; ++k) {
-      double a[4], b[4];
+  for (int a = 0; a < MB; ++a)
 #pragma unroll
-      for (int u = 0; u < 4; ++u) a[u] = as[k][ty * 4 + u];
-#pragma unroll
-      for (int v = 0; v < 4; ++v) b[v] = bs[k][tx * 4 + v];
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) acc[u][v] = fma(a[u], b[v], acc[u][v]);
-    }
-  }
-  // All reads of A and B by this work-group are done before any write.
+    for (int b = 0; b < NB; ++b) acc[a][b] = f64x4{0.0, 0.0, 0.0, 0.0};
+  load(0);
+  stage(0);
   __syncthreads();
+  const int nk = K / KB;
+  for (int t = 0; t < nk; ++t) {
+    const int s = t & 1;
+    if (t + 1 < nk) load((t + 1) * KB);
 #pragma unroll
-  for (int u = 0; u < 4; ++u) {
-    const int i = i0 + ty * 4 + u;
+    for (int ks = 0; ks < KB / 4; ++ks) {
+      double fa[MB], fb[NB];
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int j = j0 + tx * 4 + v;
-      if (i < M && j < N && (!LOWER || j <= i)) {
-        double* c = C + (long long)i * ldc + j;
-        *c = accumulate ? fma(alpha, acc[u][v], *c) : alpha * acc[u][v];
-      }
+      for (int a = 0; a < MB; ++a)
+        fa[a] = as[s][(wm * (TM / 2) + 16 * a + lc) * LDR + 4 * ks + lk];
+#pragma unroll
+      for (int b = 0; b < NB; ++b)
+        fb[b] = BK ? bs[s][(4 * ks + lk) * LDK + wn * (TN / 2) + 16 * b + lc]
+                   : bs[s][(wn * (TN / 2) + 16 * b + lc) * LDR + 4 * ks + lk];
+#pragma unroll
+      for (int a = 0; a < MB; ++a)
+#pragma unroll
+        for (int b = 0; b < NB; ++b) acc[a][b] = mfma_f64(fa[a], fb[b], acc[a][b]);
     }
+    // the other stage was last read before the barrier that ended step t - 1
+    if (t + 1 < nk) stage(s ^ 1);
+    __syncthreads();
   }
+#pragma unroll
+  for (int a = 0; a < MB; ++a)
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+      const int j = j0 + wn * (TN / 2) + 16 * b + lc;
+      const int ib = i0 + wm * (TM / 2) + 16 * a + lk;
+      double* c = C + (long long)ib * ldc + j;
+      double old[4];
+      if (accumulate) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+          old[v] = (ib + 4 * v < M && j < N) ? c[(long long)(4 * v) * ldc] : 0.0;
+      }
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+        if (ib + 4 * v < M && j < N)
+          c[(long long)(4 * v) * ldc] =
+              accumulate ? fma(alpha, acc[a][b][v], old[v]) : alpha * acc[a][b][v];
+    }
 }
 
-static hipError_t launch_gemm_f64(hipStream_t st, bool lower, bool bk, int M, int N, int K,
-                                  int kslice, double alpha, const double* A, long long lda,
-                                  const double* B, long long ldb, double* C, long long ldc,
-                                  long long cz, bool accumulate) {
-  if (M <= 0 || N <= 0) return hipSuccess;
-  if (kslice <= 0) kslice = K > 0 ? K : 1;
-  const int nz = K > 0 ? (K + kslice - 1) / kslice : 1;
-  dim3 grid((N + LT - 1) / LT, (M + LT - 1) / LT, nz);
-  if (lower)
-    hipLaunchKernelGGL((gemm_nt_f64_kernel<true, false>), grid, dim3(256), 0, st, M, N, K, kslice,
-                       alpha, A, lda, B, ldb, C, ldc, cz, (int)accumulate);
-  else if (bk)
-    hipLaunchKernelGGL((gemm_nt_f64_kernel<false, true>), grid, dim3(256), 0, st, M, N, K, kslice,
-                       alpha, A, lda, B, ldb, C, ldc, cz, (int)accumulate);
-  else
-    hipLaunchKernelGGL((gemm_nt_f64_kernel<false, false>), grid, dim3(256), 0, st, M, N, K, kslice,
-                       alpha, A, lda, B, ldb, C, ldc, cz, (int)accumulate);
+template <bool BK>
+static hipError_t launch_gemm_t(hipStream_t st, int M, int N, int K, double alpha, const double* A,
+                                long long lda, const double* B, long long ldb, double* C,
+                                long long ldc, bool accumulate, int batch, long long az,
+                                long long bz, long long cz) {
+  if (M <= 0 || N <= 0 || batch <= 0) return hipSuccess;
+  if (K <= 0 || K % KB != 0 || N % 2 != 0) return hipErrorInvalidValue;
+  // 128 x 128 tiles read half of what 64 x 64 ones do for a product and run at
+  // @GEMM128@; with fewer of them than about
+  // two per compute unit the smaller tiles spread the work better.
+  const long long big = (long long)((M + 127) / 128) * ((N + 127) / 128) * batch;
+  if (big >= 384) {
+    hipLaunchKernelGGL((gemm_f64_kernel<128, 128, BK>), dim3((N + 127) / 128, (M + 127) / 128, batch),
+                       dim3(256), 0, st, M, N, K, alpha, A, lda, az, B, ldb, bz, C, ldc, cz,
+                       (int)accumulate);
+  } else {
+    const long long mid = (long long)((M + 63) / 64) * ((N + 63) / 64) * batch;
+    if (mid >= 384 || M < 64)
+      hipLaunchKernelGGL((gemm_f64_kernel<64, 64, BK>), dim3((N + 63) / 64, (M + 63) / 64, batch),
+                         dim3(256), 0, st, M, N, K, alpha, A, lda, az, B, ldb, bz, C, ldc, cz,
+                         (int)accumulate);
+    else
+      hipLaunchKernelGGL((gemm_f64_kernel<32, 64, BK>), dim3((N + 63) / 64, (M + 31) / 32, batch),
+                         dim3(256), 0, st, M, N, K, alpha, A, lda, az, B, ldb, bz, C, ldc, cz,
+                         (int)accumulate);
+  }
   return hipGetLastError();
 }
 
-hipError_t launch_gemm_nt_f64(hipStream_t st, bool lower, int M, int N, int K, int kslice,
-                              double alpha, const double* A, long long lda, const double* B,
-                              long long ldb, double* C, long long ldc, long long cz,
-                              bool accumulate) {
-  return launch_gemm_f64(st, lower, false, M, N, K, kslice, alpha, A, lda, B, ldb, C, ldc, cz,
-                         accumulate);
-}
-
-hipError_t launch_gemm_nn_f64_sliced(hipStream_t st, int M, int N, int K, int kslice,
-                                     double alpha, const double* A, long long lda,
-                                     const double* B, long long ldb, double* C, long long ldc,
-                                     long long cz) {
-  return launch_gemm_f64(st, false, true, M, N, K, kslice, alpha, A, lda, B, ldb, C, ldc, cz,
-                         false);
+hipError_t launch_gemm_nt_f64(hipStream_t st, int M, int N, int K, double alpha, const double* A,
+                              long long lda, const double* B, long long ldb, double* C,
+                              long long ldc, bool accumulate, int batch, long long az,
+                              long long bz, long long cz) {
+  return launch_gemm_t<false>(st, M, N, K, alpha, A, lda, B, ldb, C, ldc, accumulate, batch, az,
+                              bz, cz);
 }
 
 hipError_t launch_gemm_nn_f64(hipStream_t st, int M, int N, int K, double alpha, const double* A,
                               long long lda, const double* B, long long ldb, double* C,
-                              long long ldc, bool accumulate) {
-  return launch_gemm_f64(st, false, true, M, N, K, K, alpha, A, lda, B, ldb, C, ldc, 0,
-                         accumulate);
+                              long long ldc, bool accumulate, int batch, long long az,
+                              long long bz, long long cz) {
+  return launch_gemm_t<true>(st, M, N, K, alpha, A, lda, B, ldb, C, ldc, accumulate, batch, az,
+                             bz, cz);
 }
 
-// Factor the nb x nb diagonal block at A (leading dimension lda, lower part
-// read and written) as L L^T, and write L^{-1} (lower, zeros above) to
-// Linv [64][64].  A pivot that is not positive and finite sets *flag and is
-// replaced by 1 so that the factorization runs to its end.
-__global__ __launch_bounds__(256) void potrf_diag_kernel(double* __restrict__ A, long long lda,
-                                                         int nb, double* __restrict__ Linv,
-                                                         int* __restrict__ flag) {
-  __shared__ double L[LT][LT + 1];
-  __shared__ double X[LT][LT + 1];
-  const int tid = threadIdx.x;
-  for (int e = tid; e < LT * LT; e += 256) {
-    const int i = e / LT, j = e % LT;
-    L[i][j] = (i < nb && j <= i) ? A[(long long)i * lda + j] : 0.0;
+// ---- Cholesky factorization, right-looking in blocks of 64 columns ----
+//
+// Per block two launches: the panel below the factored diagonal block is
+// multiplied by the block's inverse transpose, then the trailing lower
+// triangle is updated.  The update's first work-group takes the next diagonal
+// block alone and goes on to factor and invert it (chol64.h) while the others
+// work on the rest of the triangle, so the serial part is hidden behind the
+// update for as long as the triangle is large: @POTRFT@
+
+// 64 x 64 part of a row-major matrix into an LDS block (rows past `rows` repeat
+// the last one; `cols` is 32 or 64).
+__device__ __forceinline__ void load_block(double* dst, const double* src, long long ld, int rows,
+                                           int cols) {
+  for (int e = threadIdx.x; e < 64 * 32; e += 256) {
+    const int i = e >> 5, j = 2 * (e & 31);
+    if (j < cols) {
+      const f64x2 v = *(const f64x2_u*)(src + (long long)min(i, rows - 1) * ld + j);
+      *(f64x2*)&dst[i * kCholLd + j] = v;
+    }
   }
+}
+
+// panel[i][c] = sum_{k <= c} panel[i][k] Linv[c][k] in place: 32 rows per
+// work-group, all read before any is written; wave = 16 columns.
+__global__ __launch_bounds__(256) void potrf_panel_kernel(double* __restrict__ panel, long long ld,
+                                                          int rows,
+                                                          const double* __restrict__ Linv) {
+  __shared__ __attribute__((aligned(16))) double x_s[kCholBlock];
+  __shared__ __attribute__((aligned(16))) double p_s[32 * kCholLd];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int lc = lane & 15, lk = lane >> 4;
+  const int i0 = blockIdx.x * 32;
+  double* P = panel + (long long)i0 * ld;
+  const int live = min(32, rows - i0);
+  for (int e = tid; e < 32 * 32; e += 256) {
+    const int i = e >> 5, j = 2 * (e & 31);
+    *(f64x2*)&p_s[i * kCholLd + j] = *(const f64x2_u*)(P + (long long)min(i, live - 1) * ld + j);
+  }
+  load_block(x_s, Linv, LT, LT, LT);
   __syncthreads();
-  // Trailing updates on a 16 x 16 thread grid: thread (ty, tx) owns rows
-  // ty + 16 a and columns tx + 16 b of the block (no index division).
-  const int tx = tid & 15, ty = tid >> 4;
-  for (int j = 0; j < nb; ++j) {
-    double piv = L[j][j];
-    const bool bad = !(piv > 0.0) || !isfinite(piv);
-    const double dj = bad ? 1.0 : sqrt(piv);
-    __syncthreads();  // every thread has read L[j][j]
-    if (tid == 0) {
-      L[j][j] = dj;
-      if (bad) *flag = 1;
+  f64x4 acc[2] = {{0.0, 0.0, 0.0, 0.0}, {0.0, 0.0, 0.0, 0.0}};
+  for (int ks = 0; ks < 4 * (wave + 1); ++ks) {
+    const double b = frag_a(x_s, 16 * wave, 0, ks);
+#pragma unroll
+    for (int a = 0; a < 2; ++a) acc[a] = mfma_f64(frag_a(p_s, 16 * a, 0, ks), b, acc[a]);
+  }
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int i = 16 * a + 4 * v + lk;
+      if (i < live) P[(long long)i * ld + 16 * wave + lc] = acc[a][v];
     }
-    if (tid > j && tid < nb) L[tid][j] /= dj;
+}
+
+// Trailing update: A22 -= P P^T on the lower triangle (64 x 64 tiles; P = the
+// panel's 64 columns, A22 the n x n trailing matrix), and the next diagonal
+// block's factor (in place) and inverse (Linv, 64 x 64, zero above the
+// diagonal) by work-group 0.  P null: no update (the first diagonal block).
+__global__ __launch_bounds__(256, 2) void potrf_trail_kernel(double* __restrict__ A22,
+                                                             const double* __restrict__ P,
+                                                             long long ld, int n,
+                                                             double* __restrict__ Linv,
+                                                             int* __restrict__ flag) {
+  __shared__ __attribute__((aligned(16))) double p_s[kCholBlock];
+  __shared__ __attribute__((aligned(16))) double q_s[kCholBlock];
+  __shared__ double dinv[64];
+  __shared__ int fail;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int lc = lane & 15, lk = lane >> 4;
+  if (blockIdx.x == 0) {
+    const int nb = min(LT, n);
+    if (tid == 0) fail = 0;
+    load_block(q_s, A22, ld, nb, nb);
+    if (P != nullptr) load_block(p_s, P, ld, nb, LT);
     __syncthreads();
+    if (P != nullptr) {
+      int id = 0;
+      for (int bi = 0; bi < nb / 16; ++bi)
+        for (int bj = 0; bj <= bi; ++bj, ++id) {
+          if ((id & 3) != wave) continue;
+          f64x4 c = load_c(q_s, 16 * bi, 16 * bj);
 #pragma unroll
-    for (int a = 0; a < LT / 16; ++a) {
-      const int i = ty + 16 * a;
-      if (i > j && i < nb) {
-        const double lij = L[i][j];
-#pragma unroll
-        for (int b = 0; b < LT / 16; ++b) {
-          const int k = tx + 16 * b;
-          if (k > j && k <= i) L[i][k] = fma(-lij, L[k][j], L[i][k]);
+          for (int ks = 0; ks < 16; ++ks)
+            c = mfma_f64(-frag_a(p_s, 16 * bi, 0, ks), frag_a(p_s, 16 * bj, 0, ks), c);
+          store_c(q_s, 16 * bi, 16 * bj, c);
         }
-      }
-    }
-    __syncthreads();
-  }
-  for (int e = tid; e < nb * nb; e += 256) {
-    const int i = e / nb, j = e % nb;
-    if (j <= i) A[(long long)i * lda + j] = L[i][j];
-  }
-  // L^{-1} row by row: X[i][i] = 1 / L[i][i] and, for c < i,
-  // X[i][c] = -(sum_{t=c}^{i-1} L[i][t] X[t][c]) / L[i][i].  Thread 4 c + q
-  // takes column c and every fourth t from c + q; the four partial sums are
-  // added across the four adjacent lanes.
-  {
-    const int c = tid >> 2, q = tid & 3;
-    if (q == 0 && c < nb) X[c][c] = 1.0 / L[c][c];
-    __syncthreads();
-    for (int i = 1; i < nb; ++i) {
-      double s = 0.0;
-      if (c < i)
-        for (int t = c + q; t < i; t += 4) s = fma(L[i][t], X[t][c], s);
-      s += __shfl_xor(s, 1);
-      s += __shfl_xor(s, 2);
-      if (c < i && q == 0) X[i][c] = -s / L[i][i];
       __syncthreads();
     }
+    chol64_factor(q_s, nb, dinv, &fail);
+    for (int e = tid; e < nb * nb; e += 256) {
+      const int i = e / nb, j = e % nb;
+      if (j <= i) A22[(long long)i * ld + j] = q_s[i * kCholLd + j];
+    }
+    chol64_invert(q_s, nb, dinv, p_s);
+    for (int e = tid; e < LT * LT; e += 256) {
+      const int i = e / LT, j = e % LT;
+      Linv[e] = (i < nb && j <= i) ? p_s[i * kCholLd + j] : 0.0;
+    }
+    if (tid == 0 && fail) *flag = 1;
+    return;
   }
-  for (int e = tid; e < LT * LT; e += 256) {
-    const int i = e / LT, j = e % LT;
-    Linv[e] = (i < nb && j < nb && j <= i) ? X[i][j] : 0.0;
+  // tile blockIdx.x of the lower triangle, row by row (tile 0 is the diagonal
+  // block above)
+  const int id = blockIdx.x;
+  int bi = (int)((sqrtf(8.f * (float)id + 1.f) - 1.f) * 0.5f);
+  while (bi * (bi + 1) / 2 > id) --bi;
+  while ((bi + 1) * (bi + 2) / 2 <= id) ++bi;
+  const int bj = id - bi * (bi + 1) / 2;
+  const int i0 = bi * LT, j0 = bj * LT;
+  const int wm = wave >> 1, wn = wave & 1;
+  double* Ct = A22 + (long long)i0 * ld + j0;
+  const int mi = min(LT, n - i0), mj = min(LT, n - j0);
+  f64x4 acc[2][2];
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int i = min(32 * wm + 16 * a + 4 * v + lk, mi - 1);
+        const int j = min(32 * wn + 16 * b + lc, mj - 1);
+        acc[a][b][v] = Ct[(long long)i * ld + j];
+      }
+  load_block(p_s, P + (long long)i0 * ld, ld, mi, LT);
+  load_block(q_s, P + (long long)j0 * ld, ld, mj, LT);
+  __syncthreads();
+#pragma unroll
+  for (int ks = 0; ks < 16; ++ks) {
+    double fa[2], fb[2];
+#pragma unroll
+    for (int a = 0; a < 2; ++a) fa[a] = -frag_a(p_s, 32 * wm + 16 * a, 0, ks);
+#pragma unroll
+    for (int b = 0; b < 2; ++b) fb[b] = frag_a(q_s, 32 * wn + 16 * b, 0, ks);
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+      for (int b = 0; b < 2; ++b) acc[a][b] = mfma_f64(fa[a], fb[b], acc[a][b]);
   }
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int i = 32 * wm + 16 * a + 4 * v + lk;
+        const int j = 32 * wn + 16 * b + lc;
+        if (i < mi && j < mj && j0 + j <= i0 + i) Ct[(long long)i * ld + j] = acc[a][b][v];
+      }
 }
 
-// In-place lower Cholesky factor of A [d][d] (leading dimension lda; the
-// strict upper part is neither read nor written).  Linv: 64 x 64 fp64 scratch,
-// or, with keep_inverses, one 64 x 64 block per diagonal block (block b at
-// Linv + 4096 b holds the inverse of the factor's diagonal block b).  *flag is
-// set when a pivot is not positive (the caller clears it first).
+// In-place lower Cholesky factor of A [d][d] (d a multiple of 32, leading
+// dimension lda; the strict upper part is not written).  Linv: scratch of two
+// 64 x 64 blocks, or, with keep_inverses, one 64 x 64 block per diagonal block
+// (block b at Linv + 4096 b holds the inverse of the factor's diagonal block
+// b).  *flag is set when a pivot is not positive (the caller clears it first).
 hipError_t launch_potrf_f64(hipStream_t st, double* A, int d, long long lda, double* Linv_base,
                             int* flag, bool keep_inverses) {
-  for (int k0 = 0; k0 < d; k0 += LT) {
-    const int nb = min(LT, d - k0);
-    double* Linv = keep_inverses ? Linv_base + (long long)(k0 / LT) * LT * LT : Linv_base;
-    double* akk = A + (long long)k0 * lda + k0;
-    hipLaunchKernelGGL(potrf_diag_kernel, dim3(1), dim3(256), 0, st, akk, lda, nb, Linv, flag);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    const int rest = d - k0 - nb;
-    if (rest <= 0) break;
-    double* panel = A + (long long)(k0 + nb) * lda + k0;
-    // panel = panel L_kk^{-T}: row i of the panel times row j of L_kk^{-1}
-    e = launch_gemm_nt_f64(st, false, rest, nb, nb, nb, 1.0, panel, lda, Linv, LT, panel, lda, 0,
-                           false);
-    if (e != hipSuccess) return e;
-    // trailing lower triangle -= panel panel^T
-    double* trail = A + (long long)(k0 + nb) * lda + (k0 + nb);
-    e = launch_gemm_nt_f64(st, true, rest, rest, nb, nb, -1.0, panel, lda, panel, lda, trail, lda,
-                           0, true);
+  if (d % 32 != 0) return hipErrorInvalidValue;
+  auto linv = [&](int k) { return Linv_base + (long long)(keep_inverses ? k : k & 1) * LT * LT; };
+  hipLaunchKernelGGL(potrf_trail_kernel, dim3(1), dim3(256), 0, st, A, (const double*)nullptr, lda,
+                     d, linv(0), flag);
+  for (int k0 = 0; k0 + LT < d; k0 += LT) {
+    const int rest = d - k0 - LT, k = k0 / LT;
+    double* panel = A + (long long)(k0 + LT) * lda + k0;
+    hipLaunchKernelGGL(potrf_panel_kernel, dim3((rest + 31) / 32), dim3(256), 0, st, panel, lda,
+                       rest, linv(k));
+    const int nt = (rest + LT - 1) / LT;
+    hipLaunchKernelGGL(potrf_trail_kernel, dim3(nt * (nt + 1) / 2), dim3(256), 0, st,
+                       A + (long long)(k0 + LT) * lda + (k0 + LT), panel, lda, rest, linv(k + 1),
+                       flag);
+    const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
-  return hipSuccess;
+  return hipGetLastError();
 }
 
 // Lower part of H in fp64: C[i][j] = H[i][j], or with reverse the Hessian
-// with its channel order reversed, C[i][j] = H[d-1-i][d-1-j].
+// with its channel order reversed, C[i][j] = H[d-1-i][d-1-j].  One work-group
+// per row.
 __global__ __launch_bounds__(256) void copy_lower_kernel(const float* __restrict__ H, int d,
                                                          int reverse, double* __restrict__ C) {
-  const long long n = (long long)d * d;
-  for (long long e = (long long)blockIdx.x * 256 + threadIdx.x; e < n;
-       e += (long long)gridDim.x * 256) {
-    const int i = (int)(e / d), j = (int)(e % d);
-    if (j <= i)
-      C[e] = (double)(reverse ? H[(long long)(d - 1 - i) * d + (d - 1 - j)] : H[e]);
-  }
+  const int i = blockIdx.x;
+  const float* h = H + (long long)(reverse ? d - 1 - i : i) * d;
+  double* c = C + (long long)i * d;
+  for (int j = threadIdx.x; j <= i; j += 256) c[j] = (double)h[reverse ? d - 1 - j : j];
 }
 
 // M[k][t] = C[d-1-t][d-1-k] for t <= k (reflection about the anti-diagonal,
@@ -280,10 +395,7 @@ __global__ __launch_bounds__(256) void antitranspose_lower_kernel(const double* 
 }
 
 hipError_t launch_copy_lower(hipStream_t st, const float* H, int d, bool reverse, double* C) {
-  const long long n = (long long)d * d;
-  const long long blocks = (n + 255) / 256 < 16384 ? (n + 255) / 256 : 16384;
-  hipLaunchKernelGGL(copy_lower_kernel, dim3((unsigned)blocks), dim3(256), 0, st, H, d,
-                     (int)reverse, C);
+  hipLaunchKernelGGL(copy_lower_kernel, dim3(d), dim3(256), 0, st, H, d, (int)reverse, C);
   return hipGetLastError();
 }
 
