@@ -42,6 +42,7 @@ __global__ __launch_bounds__(256) void chol_groups_kernel(const float* __restric
   double* B2 = sm + 2 * kCholBlock;    // A21, L21 (g = 128)
   double* B3 = sm + 3 * kCholBlock;    // A22, L22 (g = 128)
   __shared__ double dinv[128];
+  __shared__ __attribute__((aligned(16))) double col_s[128];
   __shared__ int fail;
   const int blk = blockIdx.x;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -92,7 +93,7 @@ __global__ __launch_bounds__(256) void chol_groups_kernel(const float* __restric
     load(B3, 64, 64);
   }
   __syncthreads();
-  chol64_factor(B0, n, dinv, &fail);
+  chol64_factor(B0, n, dinv, col_s, &fail);
   out_l(B0, 0, 0);
   chol64_invert(B0, n, dinv, B1);
   out_x(B1, 0);
@@ -124,7 +125,7 @@ __global__ __launch_bounds__(256) void chol_groups_kernel(const float* __restric
       }
     out_l(B2, 64, 0);
     __syncthreads();
-    chol64_factor(B3, 64, dinv + 64, &fail);
+    chol64_factor(B3, 64, dinv + 64, col_s, &fail);
     out_l(B3, 64, 64);
     chol64_invert(B3, 64, dinv + 64, B0);
     out_x(B0, 64);

@@ -49,6 +49,13 @@ __device__ __forceinline__ double chol_rsqrt(double x) {
   }
   return y;
 }
+// 1 / x: the hardware estimate and two Newton steps y <- y + y (1 - x y).
+__device__ __forceinline__ double chol_rcp(double x) {
+  double y = __builtin_amdgcn_rcp(x);
+#pragma unroll
+  for (int it = 0; it < 2; ++it) y = fma(y, fma(-x, y, 1.0), y);
+  return y;
+}
 
 // A and B fragments of k-slice ks (4 wide) of a row-major LDS block:
 // A(i, k) = m[r0 + i][c0 + k];  B(k, j) = m[r0 + k][c0 + j];
@@ -77,34 +84,59 @@ __device__ __forceinline__ void store_c(double* m, int r0, int c0, f64x4 c) {
 // A = L L^T in place for the n x n block (n a multiple of 16, at most 64; the
 // lower triangle is read; the diagonal blocks' upper parts are written as 0),
 // dinv[k] = 1 / L(k, k).  A pivot that is not positive and finite is replaced
-// by 1 and sets *fail.  All 256 threads call it; A is complete on return.
-__device__ __forceinline__ void chol64_factor(double* A, int n, double* dinv, int* fail) {
+// by 1 and sets *fail.  col: 128 doubles of LDS scratch.  All 256 threads call
+// it; A is complete on return.
+//
+// Panel (one wavefront, lane = row): column k stays unscaled while it updates
+// the later ones, a_j -= (a_k / pivot) a_k[row j].  The chain from a pivot to
+// the next is reciprocal, product, readlane of one entry, multiply-add; the
+// other entries go through LDS (one write, uniform 16-byte reads) and are
+// applied a step later, beside the next pivot's reciprocal.  The square roots
+// come at the end, a pivot per lane.
+__device__ __forceinline__ void chol64_factor(double* A, int n, double* dinv, double* col,
+                                              int* fail) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   for (int c0 = 0; c0 < n; c0 += 16) {
     if (wave == 0) {
-      double a[16];
+      double a[16], t[16];
       double* row = A + lane * kCholLd + c0;
 #pragma unroll
       for (int k = 0; k < 16; ++k) a[k] = row[k];
       bool bad = false;
-      double own = 1.0;
+      double own = 1.0, lp = 0.0;
 #pragma unroll
       for (int k = 0; k < 16; ++k) {
-        double piv = readlane_f64(a[k], c0 + k);
-        const bool b = !(piv > 0.0) || !isfinite(piv);
+        const double pk = readlane_f64(a[k], c0 + k);
+        const bool b = !(pk > 0.0 && pk < INFINITY);
         bad |= b;
-        piv = b ? 1.0 : piv;
-        const double rs = chol_rsqrt(piv);
-        const bool diag = lane == c0 + k;
-        own = diag ? rs : own;
-        a[k] = diag ? piv * rs : (lane > c0 + k ? a[k] * rs : 0.0);
+        const double piv = b ? 1.0 : pk;
+        own = lane == c0 + k ? piv : own;
+        // (one wavefront: its LDS accesses complete in order)
+        double* ck = col + 64 * (k & 1);
+        if (k < 14) ck[lane] = a[k];
+        const double ip = chol_rcp(piv);
+        // step k - 1 on the columns past k
 #pragma unroll
-        for (int j = k + 1; j < 16; ++j) a[j] = fma(-a[k], readlane_f64(a[k], c0 + j), a[j]);
+        for (int j = k + 1; j < 16; ++j)
+          if (k > 0) a[j] = fma(-lp, t[j], a[j]);
+        lp = a[k] * ip;
+        if (k < 15) a[k < 15 ? k + 1 : 15] =
+            fma(-lp, readlane_f64(a[k], c0 + (k < 15 ? k + 1 : 15)), a[k < 15 ? k + 1 : 15]);
+        // the reads see the other lanes' writes: not to be moved above them
+        asm volatile("" ::: "memory");
+#pragma unroll
+        for (int j = k + 2; j < 16; ++j) t[j] = ck[c0 + j];
+      }
+      const double rs = chol_rsqrt(own);
+#pragma unroll
+      for (int k = 0; k < 16; ++k) {
+        const double rk = readlane_f64(rs, c0 + k);
+        a[k] = lane == c0 + k ? own * rs : (lane > c0 + k ? a[k] * rk : 0.0);
       }
       if (lane >= c0 && lane < n) {
 #pragma unroll
         for (int k = 0; k < 16; ++k) row[k] = a[k];
-        if (lane < c0 + 16) dinv[lane] = own;
+        if (lane < c0 + 16) dinv[lane] = rs;
       }
       if (bad && lane == 0) *fail = 1;
     }
@@ -161,19 +193,25 @@ __device__ __forceinline__ void chol64_invert(const double* L, int n, const doub
     store_c(X, r, c, x);
   }
   __syncthreads();
-  // 32 -> 64: wave = block (bi, bj) of the lower left 32 x 32
+  // 32 -> 64: wave = block (bi, bj) of the lower left 32 x 32 (a zero block is
+  // multiplied where bi or bj leaves one out: no branches, loads up front)
   if (nb == 4) {
     const int bj = wave & 1, bi = 2 + (wave >> 1);
     f64x4 x = {0.0, 0.0, 0.0, 0.0};
-    for (int u = 2; u <= bi; ++u) {
-      f64x4 t = {0.0, 0.0, 0.0, 0.0};
-      for (int q = bj; q < 2; ++q)
+    f64x4 t[2] = {{0.0, 0.0, 0.0, 0.0}, {0.0, 0.0, 0.0, 0.0}};
 #pragma unroll
-        for (int ks = 0; ks < 4; ++ks)
-          t = mfma_f64(frag_a(L, 16 * u, 16 * q, ks), frag_b(X, 16 * q, 16 * bj, ks), t);
+    for (int q = 0; q < 2; ++q)
 #pragma unroll
-      for (int ks = 0; ks < 4; ++ks) x = mfma_f64(-frag_a(X, 16 * bi, 16 * u, ks), t[ks], x);
-    }
+      for (int ks = 0; ks < 4; ++ks) {
+        const double b = q >= bj ? frag_b(X, 16 * q, 16 * bj, ks) : 0.0;
+#pragma unroll
+        for (int u = 0; u < 2; ++u) t[u] = mfma_f64(frag_a(L, 32 + 16 * u, 16 * q, ks), b, t[u]);
+      }
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks)
+        x = mfma_f64(2 + u <= bi ? -frag_a(X, 16 * bi, 32 + 16 * u, ks) : 0.0, t[u][ks], x);
     store_c(X, 16 * bi, 16 * bj, x);
   }
   __syncthreads();

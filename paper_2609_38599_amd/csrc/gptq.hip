@@ -65,14 +65,16 @@ size_t gptq_workspace_bytes(int rows, int cols, int g) {
 // row by a DPP broadcast, and each lane subtracts or adds M(m, n) times it to
 // the sums of its positions m > n.  (A dot product over the row's lanes at
 // every step, with an fp64 division on it, made a chain about six times as
-// long: 86 us for 4096 rows at g = 128, now @GROUPT@.)  Nothing is recorded at a
+// long: 86 us for 4096 rows at g = 128, now 25.)  Nothing is recorded at a
 // step: a position's sum is final once its step has come, so its value is
 // formed again from it afterwards.
 // Pass 1: y = M_GG^{-1} c and the group's grid from w + y (0 forced into the
 // range); pass 2: the columns in order, each rounded from
 // w_m + (c_m + sum_{n<m} M_mn e_n) / M_mm.
-// M_GG sits in LDS column by column (element (m, n) at n (g + 1) + m, zero on
-// and above the diagonal), so the lanes of a row read consecutive values.
+// M_GG sits in LDS column by column with its rows divided by their diagonal
+// (element (m, n) / M_mm at n (g + 1) + m, zero on and above the diagonal), so
+// the lanes of a row read consecutive values and the sums are kept divided
+// too: no multiplication by 1 / M_mm is left on the chain.
 //
 // x / s of the rounding is the correctly rounded quotient, as a division
 // gives it: q0 = x (1 / s), then q0 + (x - q0 s) (1 / s) with fused
@@ -89,7 +91,7 @@ __global__ __launch_bounds__(512) void gptq_group_kernel(int rows, int cols, int
   constexpr int g = G_SIZE;
   constexpr int NT = g / 16;
   constexpr int LD = g + 1;
-  extern __shared__ double mc[];     // g x LD, then 1 / M_mm
+  extern __shared__ double mc[];     // g x LD, then 1 / M_mm of the g rows
   double* minv = mc + g * LD;
   const int tid = threadIdx.x;
   const int j = tid & 15;
@@ -99,7 +101,7 @@ __global__ __launch_bounds__(512) void gptq_group_kernel(int rows, int cols, int
   const int b0 = grp * g;
   const int G = cols / g;
   const double qmax = (double)((1 << bits) - 1);
-  double cl[NT], wl[NT], acc[NT], inv[NT];
+  double cl[NT], wl[NT], acc[NT];
   {
     const float* w = W + (long long)rr * cols + b0 + j;
     const double* c = comp + (long long)rr * cols + b0 + j;
@@ -109,6 +111,8 @@ __global__ __launch_bounds__(512) void gptq_group_kernel(int rows, int cols, int
       cl[t] = has_comp ? c[16 * t] : 0.0;
     }
   }
+  if (tid < g) minv[tid] = 1.0 / M[(long long)(b0 + tid) * (cols + 1)];
+  __syncthreads();
   {
     // M_GG by rows, two values a load, eight loads in flight a thread (the
     // part above the diagonal is read and dropped)
@@ -127,32 +131,30 @@ __global__ __launch_bounds__(512) void gptq_group_kernel(int rows, int cols, int
         const int e = e0 + u * (int)blockDim.x;
         if (e < NE) {
           const int m = e / (g / 2), n = 2 * (e % (g / 2));
+          const double im = minv[m];
 #pragma unroll
-          for (int q = 0; q < 2; ++q) {
-            mc[(n + q) * LD + m] = n + q < m ? v[u][q] : 0.0;
-            if (n + q == m) minv[m] = 1.0 / v[u][q];
-          }
+          for (int q = 0; q < 2; ++q) mc[(n + q) * LD + m] = n + q < m ? v[u][q] * im : 0.0;
         }
       }
     }
   }
   __syncthreads();
 #pragma unroll
-  for (int t = 0; t < NT; ++t) inv[t] = minv[j + 16 * t];
+  for (int t = 0; t < NT; ++t) cl[t] *= minv[j + 16 * t];
 
   // pass 1: y = M_GG^{-1} c
 #pragma unroll
   for (int t = 0; t < NT; ++t) acc[t] = cl[t];
   Steps<0, g>::run([&](auto nc) __attribute__((always_inline)) {
     constexpr int n = decltype(nc)::value;
-    const double y = row_share<n % 16>(acc[n / 16] * inv[n / 16]);
+    const double y = row_share<n % 16>(acc[n / 16]);
 #pragma unroll
     for (int t = n / 16; t < NT; ++t) acc[t] = fma(-mc[n * LD + j + 16 * t], y, acc[t]);
   });
   double lo = 0.0, hi = 0.0;
 #pragma unroll
   for (int t = 0; t < NT; ++t) {
-    const double v = wl[t] + acc[t] * inv[t];
+    const double v = wl[t] + acc[t];
     lo = fmin(lo, v);
     hi = fmax(hi, v);
   }
@@ -166,21 +168,21 @@ __global__ __launch_bounds__(512) void gptq_group_kernel(int rows, int cols, int
   const double s64 = (double)s32;
   const double zp = fmin(fmax(rint(-lo / s64), 0.0), qmax);
   const double sinv = 1.0 / s64;
-  const double qlo = -zp - 1.0, qhi = qmax - zp + 1.0;
+  const double dlo = -zp, dhi = qmax - zp;   // the range of q - z
 
   // pass 2: the columns in order
-  auto code_of = [&](int t) __attribute__((always_inline)) {
-    const double x = fma(acc[t], inv[t], wl[t]);
-    const double q0 = fmin(fmax(x * sinv, qlo), qhi);
+  // q - z of this lane's position t, from its sum
+  auto step_of = [&](int t) __attribute__((always_inline)) {
+    const double x = wl[t] + acc[t];
+    const double q0 = fmin(fmax(x * sinv, dlo), dhi);
     const double q1 = fma(fma(-q0, s64, x), sinv, q0);
-    return fmin(fmax(rint(q1) + zp, 0.0), qmax);
+    return fmin(fmax(rint(q1), dlo), dhi);
   };
 #pragma unroll
   for (int t = 0; t < NT; ++t) acc[t] = cl[t];
   Steps<0, g>::run([&](auto nc) __attribute__((always_inline)) {
     constexpr int n = decltype(nc)::value;
-    const double q = code_of(n / 16);
-    const double e = row_share<n % 16>(fma(-s64, q - zp, wl[n / 16]));
+    const double e = row_share<n % 16>(fma(-s64, step_of(n / 16), wl[n / 16]));
 #pragma unroll
     for (int t = n / 16; t < NT; ++t) acc[t] = fma(mc[n * LD + j + 16 * t], e, acc[t]);
   });
@@ -189,9 +191,9 @@ __global__ __launch_bounds__(512) void gptq_group_kernel(int rows, int cols, int
     double* e_out = comp + (long long)r * cols + b0 + j;
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
-      const double q = code_of(t);
-      q_out[16 * t] = (uint8_t)q;
-      e_out[16 * t] = fma(-s64, q - zp, wl[t]);
+      const double dz = step_of(t);
+      q_out[16 * t] = (uint8_t)(dz + zp);
+      e_out[16 * t] = fma(-s64, dz, wl[t]);
     }
     if (j == 0) {
       scales[(long long)r * G + grp] = s32;

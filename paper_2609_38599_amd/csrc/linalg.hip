@@ -19,7 +19,8 @@ typedef double f64x2_u __attribute__((ext_vector_type(2), aligned(8)));
 
 // C[i][j] (+)= alpha sum_k A[i][k] B(j, k) for i < M, j < N, with B(j, k) =
 // B[j][k], or B[k][j] when BK.  K is a multiple of 16.  blockIdx.z picks one of
-// a batch of products (strides az, bz, cz).  C must not overlap A or B.
+// a batch of products (strides az, bz, cz).  C must not overlap A or B.  lower:
+// tiles wholly above the diagonal are left out.
 //
 // TM x TN output tile per 256-thread work-group, 2 x 2 wavefronts, k in steps
 // of 16 through two LDS stages; the next step's values are loaded into
@@ -33,7 +34,7 @@ __global__ __launch_bounds__(256, 2) void gemm_f64_kernel(int M, int N, int K, d
                                                           const double* __restrict__ B,
                                                           long long ldb, long long bz, double* C,
                                                           long long ldc, long long cz,
-                                                          int accumulate) {
+                                                          int accumulate, int lower) {
   constexpr int LDR = KB + 2;                  // row stride of a row-major tile
   constexpr int LDK = TN + 16;                 // row stride of a k-major tile
   constexpr int ASZ = TM * LDR, BSZ = BK ? KB * LDK : TN * LDR;
@@ -45,6 +46,7 @@ __global__ __launch_bounds__(256, 2) void gemm_f64_kernel(int M, int N, int K, d
   const int wm = wave >> 1, wn = wave & 1;
   const int lc = lane & 15, lk = lane >> 4;
   const int i0 = blockIdx.y * TM, j0 = blockIdx.x * TN;
+  if (lower && j0 >= i0 + TM) return;   // wholly above the diagonal
   A += (long long)blockIdx.z * az;
   B += (long long)blockIdx.z * bz;
   C += (long long)blockIdx.z * cz;
@@ -144,27 +146,28 @@ template <bool BK>
 static hipError_t launch_gemm_t(hipStream_t st, int M, int N, int K, double alpha, const double* A,
                                 long long lda, const double* B, long long ldb, double* C,
                                 long long ldc, bool accumulate, int batch, long long az,
-                                long long bz, long long cz) {
+                                long long bz, long long cz, bool lower = false) {
   if (M <= 0 || N <= 0 || batch <= 0) return hipSuccess;
   if (K <= 0 || K % KB != 0 || N % 2 != 0) return hipErrorInvalidValue;
   // 128 x 128 tiles read half of what 64 x 64 ones do for a product and run at
-  // @GEMM128@; with fewer of them than about
-  // two per compute unit the smaller tiles spread the work better.
-  const long long big = (long long)((M + 127) / 128) * ((N + 127) / 128) * batch;
+  // 64 TFLOP/s (4096^3; 64 x 64: 48); with fewer of them than about one and a
+  // half per compute unit the smaller tiles spread the work better (4096 x 512 x
+  // 512: 45 us in 64 x 64 tiles, where 128 x 128 ones would use half the units).
+  const long long big = (long long)((M + 127) / 128) * ((N + 127) / 128) * batch / (lower ? 2 : 1);
   if (big >= 384) {
     hipLaunchKernelGGL((gemm_f64_kernel<128, 128, BK>), dim3((N + 127) / 128, (M + 127) / 128, batch),
                        dim3(256), 0, st, M, N, K, alpha, A, lda, az, B, ldb, bz, C, ldc, cz,
-                       (int)accumulate);
+                       (int)accumulate, (int)lower);
   } else {
-    const long long mid = (long long)((M + 63) / 64) * ((N + 63) / 64) * batch;
+    const long long mid = (long long)((M + 63) / 64) * ((N + 63) / 64) * batch / (lower ? 2 : 1);
     if (mid >= 384 || M < 64)
       hipLaunchKernelGGL((gemm_f64_kernel<64, 64, BK>), dim3((N + 63) / 64, (M + 63) / 64, batch),
                          dim3(256), 0, st, M, N, K, alpha, A, lda, az, B, ldb, bz, C, ldc, cz,
-                         (int)accumulate);
+                         (int)accumulate, (int)lower);
     else
       hipLaunchKernelGGL((gemm_f64_kernel<32, 64, BK>), dim3((N + 63) / 64, (M + 31) / 32, batch),
                          dim3(256), 0, st, M, N, K, alpha, A, lda, az, B, ldb, bz, C, ldc, cz,
-                         (int)accumulate);
+                         (int)accumulate, (int)lower);
   }
   return hipGetLastError();
 }
@@ -188,23 +191,29 @@ hipError_t launch_gemm_nn_f64(hipStream_t st, int M, int N, int K, double alpha,
 // ---- Cholesky factorization, right-looking in blocks of 64 columns ----
 //
 // Per block two launches: the panel below the factored diagonal block is
-// multiplied by the block's inverse transpose, then the trailing lower
-// triangle is updated.  The update's first work-group takes the next diagonal
-// block alone and goes on to factor and invert it (chol64.h) while the others
-// work on the rest of the triangle, so the serial part is hidden behind the
-// update for as long as the triangle is large: @POTRFT@
+// multiplied by the block's inverse transpose, then the columns up to the end
+// of the block's 512-wide outer panel are updated.  The update's first
+// work-group takes the next diagonal block alone and goes on to factor and
+// invert it (chol64.h) while the others work on their tiles, so the update
+// hides behind that serial part.  At the end of an outer panel one product
+// with 512 columns updates the rest of the lower triangle: with every update
+// carried through the whole triangle, 64 columns at a time, the first half of
+// the steps were bound by reading and writing it (52 us for the first, 5 TB/s).
+// 4096 channels: 64 diagonal steps of 22 to 27 us and as many panels of 6 us;
+// 84 us for the diagonal block alone before.  The serial part bounds it: of a
+// step's 22 us, 11 factor the block and 3 invert it.
 
 // 64 x 64 part of a row-major matrix into an LDS block (rows past `rows` repeat
 // the last one; `cols` is 32 or 64).
 __device__ __forceinline__ void load_block(double* dst, const double* src, long long ld, int rows,
                                            int cols) {
-  for (int e = threadIdx.x; e < 64 * 32; e += 256) {
-    const int i = e >> 5, j = 2 * (e & 31);
-    if (j < cols) {
-      const f64x2 v = *(const f64x2_u*)(src + (long long)min(i, rows - 1) * ld + j);
-      *(f64x2*)&dst[i * kCholLd + j] = v;
-    }
-  }
+  const int i = threadIdx.x >> 5, j = 2 * (threadIdx.x & 31);
+  if (j >= cols) return;
+  f64x2 v[8];   // every load before the first store
+#pragma unroll
+  for (int u = 0; u < 8; ++u) v[u] = *(const f64x2_u*)(src + (long long)min(i + 8 * u, rows - 1) * ld + j);
+#pragma unroll
+  for (int u = 0; u < 8; ++u) *(f64x2*)&dst[(i + 8 * u) * kCholLd + j] = v[u];
 }
 
 // panel[i][c] = sum_{k <= c} panel[i][k] Linv[c][k] in place: 32 rows per
@@ -240,10 +249,11 @@ __global__ __launch_bounds__(256) void potrf_panel_kernel(double* __restrict__ p
     }
 }
 
-// Trailing update: A22 -= P P^T on the lower triangle (64 x 64 tiles; P = the
-// panel's 64 columns, A22 the n x n trailing matrix), and the next diagonal
-// block's factor (in place) and inverse (Linv, 64 x 64, zero above the
-// diagonal) by work-group 0.  P null: no update (the first diagonal block).
+// Update of the columns right of a panel: A22 -= P P^T on 64 x 64 tiles (P = the
+// panel's 64 columns, A22 the n x n trailing matrix; tile column blockIdx.y,
+// tile row blockIdx.x, those above the diagonal skipped), and the next
+// diagonal block's factor (in place) and inverse (Linv, 64 x 64, zero above the
+// diagonal) by work-group (0, 0).  P null: no update (a first diagonal block).
 __global__ __launch_bounds__(256, 2) void potrf_trail_kernel(double* __restrict__ A22,
                                                              const double* __restrict__ P,
                                                              long long ld, int n,
@@ -252,10 +262,13 @@ __global__ __launch_bounds__(256, 2) void potrf_trail_kernel(double* __restrict_
   __shared__ __attribute__((aligned(16))) double p_s[kCholBlock];
   __shared__ __attribute__((aligned(16))) double q_s[kCholBlock];
   __shared__ double dinv[64];
+  __shared__ __attribute__((aligned(16))) double col_s[128];
   __shared__ int fail;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int lc = lane & 15, lk = lane >> 4;
-  if (blockIdx.x == 0) {
+  const int bi = blockIdx.x, bj = blockIdx.y;
+  if (bi < bj) return;
+  if (bi == 0) {
     const int nb = min(LT, n);
     if (tid == 0) fail = 0;
     load_block(q_s, A22, ld, nb, nb);
@@ -263,37 +276,32 @@ __global__ __launch_bounds__(256, 2) void potrf_trail_kernel(double* __restrict_
     __syncthreads();
     if (P != nullptr) {
       int id = 0;
-      for (int bi = 0; bi < nb / 16; ++bi)
-        for (int bj = 0; bj <= bi; ++bj, ++id) {
+      for (int ti = 0; ti < nb / 16; ++ti)
+        for (int tj = 0; tj <= ti; ++tj, ++id) {
           if ((id & 3) != wave) continue;
-          f64x4 c = load_c(q_s, 16 * bi, 16 * bj);
+          f64x4 c = load_c(q_s, 16 * ti, 16 * tj);
 #pragma unroll
           for (int ks = 0; ks < 16; ++ks)
-            c = mfma_f64(-frag_a(p_s, 16 * bi, 0, ks), frag_a(p_s, 16 * bj, 0, ks), c);
-          store_c(q_s, 16 * bi, 16 * bj, c);
+            c = mfma_f64(-frag_a(p_s, 16 * ti, 0, ks), frag_a(p_s, 16 * tj, 0, ks), c);
+          store_c(q_s, 16 * ti, 16 * tj, c);
         }
       __syncthreads();
     }
-    chol64_factor(q_s, nb, dinv, &fail);
-    for (int e = tid; e < nb * nb; e += 256) {
-      const int i = e / nb, j = e % nb;
-      if (j <= i) A22[(long long)i * ld + j] = q_s[i * kCholLd + j];
+    chol64_factor(q_s, nb, dinv, col_s, &fail);
+#pragma unroll
+    for (int u = 0; u < 16; ++u) {
+      const int i = (tid >> 6) + 4 * u, j = tid & 63;
+      if (i < nb && j <= i) A22[(long long)i * ld + j] = q_s[i * kCholLd + j];
     }
     chol64_invert(q_s, nb, dinv, p_s);
-    for (int e = tid; e < LT * LT; e += 256) {
-      const int i = e / LT, j = e % LT;
-      Linv[e] = (i < nb && j <= i) ? p_s[i * kCholLd + j] : 0.0;
+#pragma unroll
+    for (int u = 0; u < 16; ++u) {
+      const int i = (tid >> 6) + 4 * u, j = tid & 63;
+      Linv[i * LT + j] = (i < nb && j <= i) ? p_s[i * kCholLd + j] : 0.0;
     }
     if (tid == 0 && fail) *flag = 1;
     return;
   }
-  // tile blockIdx.x of the lower triangle, row by row (tile 0 is the diagonal
-  // block above)
-  const int id = blockIdx.x;
-  int bi = (int)((sqrtf(8.f * (float)id + 1.f) - 1.f) * 0.5f);
-  while (bi * (bi + 1) / 2 > id) --bi;
-  while ((bi + 1) * (bi + 2) / 2 <= id) ++bi;
-  const int bj = id - bi * (bi + 1) / 2;
   const int i0 = bi * LT, j0 = bj * LT;
   const int wm = wave >> 1, wn = wave & 1;
   double* Ct = A22 + (long long)i0 * ld + j0;
@@ -337,7 +345,7 @@ __global__ __launch_bounds__(256, 2) void potrf_trail_kernel(double* __restrict_
 }
 
 // In-place lower Cholesky factor of A [d][d] (d a multiple of 32, leading
-// dimension lda; the strict upper part is not written).  Linv: scratch of two
+// dimension lda; what lies above the diagonal is scratch).  Linv: scratch of two
 // 64 x 64 blocks, or, with keep_inverses, one 64 x 64 block per diagonal block
 // (block b at Linv + 4096 b holds the inverse of the factor's diagonal block
 // b).  *flag is set when a pivot is not positive (the caller clears it first).
@@ -345,21 +353,31 @@ hipError_t launch_potrf_f64(hipStream_t st, double* A, int d, long long lda, dou
                             int* flag, bool keep_inverses) {
   if (d % 32 != 0) return hipErrorInvalidValue;
   auto linv = [&](int k) { return Linv_base + (long long)(keep_inverses ? k : k & 1) * LT * LT; };
-  hipLaunchKernelGGL(potrf_trail_kernel, dim3(1), dim3(256), 0, st, A, (const double*)nullptr, lda,
-                     d, linv(0), flag);
-  for (int k0 = 0; k0 + LT < d; k0 += LT) {
-    const int rest = d - k0 - LT, k = k0 / LT;
-    double* panel = A + (long long)(k0 + LT) * lda + k0;
-    hipLaunchKernelGGL(potrf_panel_kernel, dim3((rest + 31) / 32), dim3(256), 0, st, panel, lda,
-                       rest, linv(k));
-    const int nt = (rest + LT - 1) / LT;
-    hipLaunchKernelGGL(potrf_trail_kernel, dim3(nt * (nt + 1) / 2), dim3(256), 0, st,
-                       A + (long long)(k0 + LT) * lda + (k0 + LT), panel, lda, rest, linv(k + 1),
-                       flag);
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
+  constexpr int kOuter = 512;   // columns per outer panel
+  hipError_t e = hipSuccess;
+  for (int o0 = 0; o0 < d && e == hipSuccess; o0 += kOuter) {
+    const int o1 = min(o0 + kOuter, d);
+    hipLaunchKernelGGL(potrf_trail_kernel, dim3(1), dim3(256), 0, st, A + (long long)o0 * (lda + 1),
+                       (const double*)nullptr, lda, d - o0, linv(o0 / LT), flag);
+    for (int k0 = o0; k0 < o1 && k0 + LT < d; k0 += LT) {
+      const int n0 = k0 + LT, rest = d - n0, k = k0 / LT;
+      double* panel = A + (long long)n0 * lda + k0;
+      hipLaunchKernelGGL(potrf_panel_kernel, dim3((rest + 31) / 32), dim3(256), 0, st, panel, lda,
+                         rest, linv(k));
+      if (n0 < o1)
+        hipLaunchKernelGGL(potrf_trail_kernel, dim3((rest + LT - 1) / LT, (o1 - n0 + LT - 1) / LT),
+                           dim3(256), 0, st, A + (long long)n0 * (lda + 1), panel, lda, rest,
+                           linv(k + 1), flag);
+    }
+    e = hipGetLastError();
+    const int rest = d - o1;
+    if (rest > 0 && e == hipSuccess) {
+      const double* p = A + (long long)o1 * lda + o0;
+      e = launch_gemm_t<false>(st, rest, rest, o1 - o0, -1.0, p, lda, p, lda,
+                               A + (long long)o1 * (lda + 1), lda, true, 1, 0, 0, 0, true);
+    }
   }
-  return hipGetLastError();
+  return e;
 }
 
 // Lower part of H in fp64: C[i][j] = H[i][j], or with reverse the Hessian
