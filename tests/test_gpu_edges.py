@@ -1,0 +1,254 @@
+"""The set-up and post-processing kernels at the edges of their tiles and
+dispatch rules (needs an MI355X and the built libjarq.so): sizes just below, at
+and above a tile, remainders, unaligned pointers, and inputs that fp32
+arithmetic turns into infinities or NaN.  References are the float64 oracle or
+plain torch in float64."""
+
+import numpy as np
+import pytest
+import torch
+
+import paper_2609_38599_amd as jq
+from oracle import hosts, jarq, post
+from oracle.qep import corrected_weights
+from paper_2609_38599_amd import binding as jb
+from tests._gpu_common import (GpuLayer, check_scales, random_layer, to_dev)
+
+pytestmark = [pytest.mark.gpu,
+              pytest.mark.skipif(not torch.cuda.is_available(), reason="needs a GPU")]
+
+
+def _spd(d, seed):
+    rng = np.random.default_rng(seed)
+    X = rng.standard_normal((2 * d, d)) * (1.0 + 4.0 * (rng.random(d) < 0.05))
+    H = X.T @ X / (2 * d)
+    H += 0.01 * np.mean(np.diag(H)) * np.eye(d)
+    return np.ascontiguousarray(H.astype(np.float32))
+
+
+# G = cols / g systems: one panel of 16, its edges, one and two rows a lane
+@pytest.mark.parametrize("G", [1, 15, 16, 17, 32, 33, 48, 63, 64, 65, 80, 81, 96, 97, 112, 113, 128])
+def test_scale_solve_sizes(G):
+    g = 32
+    W, H, q, s, z = random_layer(21, G * g, g, 3, seed=G)
+    gk = GpuLayer(W, H, q, s, z, g, 3)
+    # a byte pattern that reads as NaN: what no kernel wrote must not matter
+    gk.ws.fill_(0xff)
+    jq.prepare(gk.p, gk.W, gk.H, gk.ws)
+    gk.scale_step()
+    _, sg = gk.state()
+    ref, ridge = jarq.scale_step(W, H, q, z, g)
+    assert not ridge.any()
+    check_scales(sg, ref, f" G={G}")
+    g2 = GpuLayer(W, H, q, s, z, g, 3, sweeps=1)
+    g2.ws.fill_(0xff)
+    jq.prepare(g2.p, g2.W, g2.H, g2.ws)
+    st = jq.sweeps(g2.p, g2.W, g2.H, g2.codes, g2.scales, g2.zeros, g2.ws)
+    assert st["ridge_rows"][0] == 0
+
+
+# panels of 512 columns, their remainders, one and two row blocks a work-group
+@pytest.mark.parametrize("rows,cols,g", [(17, 512, 32), (33, 544, 32), (70, 640, 128), (5, 1088, 64),
+                                         (4100, 640, 64)])
+def test_gptq_panels(rows, cols, g):
+    rng = np.random.default_rng(cols + rows)
+    W = (0.02 * rng.standard_normal((rows, cols))).astype(np.float32)
+    H = _spd(cols, cols)
+    p = jq.make_params(rows, cols, g, 3)
+    q, s, z = jb.gptq(p, to_dev(W), to_dev(H))
+    some = np.unique(np.linspace(0, rows - 1, 24).astype(int))
+    qo, so, zo = hosts.gptq_host(W[some], H, g, 3)
+    assert np.array_equal(q.cpu().numpy()[some], qo)
+    assert np.array_equal(s.cpu().numpy()[some], so)
+    assert np.array_equal(z.cpu().numpy()[some], zo)
+
+
+# diagonal inverses doubled up to 512 columns: every kind of remainder
+@pytest.mark.parametrize("cols", [32, 64, 96, 160, 224, 352, 512, 544, 608, 736, 992, 1120])
+def test_corrected_target_remainders(cols):
+    rows = 19
+    rng = np.random.default_rng(cols)
+    W = (0.02 * rng.standard_normal((rows, cols))).astype(np.float32)
+    H = _spd(cols, cols)
+    D = 0.05 * rng.standard_normal((cols, cols))
+    p = jq.make_params(rows, cols, 32, 3)
+    got = jb.qep_correct(p, to_dev(W), to_dev(H), to_dev(D), 0.25).cpu().numpy().astype(np.float64)
+    ref = corrected_weights(W, H, D, 0.25)   # the oracle's W + 0.75 (W D^T) H^-1
+    # the bound of the full-size test: half an fp32 ulp and 1e-9 of the correction
+    bound = 0.5 * np.spacing(np.abs(ref).astype(np.float32)).astype(np.float64) * 1.0001 + \
+        1e-9 * np.abs(ref - W).max()
+    assert np.all(np.abs(got - ref) <= bound)
+
+
+def _hess64(X):
+    X = X.double()
+    return X.t() @ X
+
+
+# tiles of 128 and 64 channels, chunks of 32 to 256 tokens, and their remainders
+@pytest.mark.parametrize("m,d", [(1, 8), (31, 64), (33, 72), (255, 128), (257, 136), (300, 200),
+                                 (129, 320), (513, 1024), (40, 4104)])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_hessian_tiles(m, d, dtype):
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(m * 10007 + d)
+    X = torch.randn(m, d, generator=gen, device="cuda").to(dtype)
+    H0 = torch.randn(d, d, generator=gen, device="cuda", dtype=torch.float64)
+    H0 = H0 + H0.t()
+    H = H0.clone()
+    jb.hessian_accumulate(X, H, 0.5)
+    assert torch.equal(H, H.t())
+    # fp32 sums of at most 256 products: (256 + 1) u |X|^T |X| covers them
+    bound = 0.5 * 257 * 2.0 ** -24 * _hess64(X.abs()) + 1e-12 * H0.abs()
+    assert bool(((H - H0 - 0.5 * _hess64(X)).abs() <= bound).all())
+
+
+@pytest.mark.parametrize("m,d", [(33, 72), (300, 200), (64, 1152)])
+def test_cross_tiles(m, d):
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(m + d)
+    X = torch.randn(m, d, generator=gen, device="cuda")
+    Xq = X + 0.1 * torch.randn(m, d, generator=gen, device="cuda")
+    D = torch.zeros(d, d, device="cuda", dtype=torch.float64)
+    jb.cross_accumulate(Xq, X, D, 2.0)
+    diff = (X - Xq).double()
+    bound = 2.0 * 257 * 2.0 ** -24 * (Xq.double().abs().t() @ diff.abs()) + 1e-300
+    assert bool(((D - 2.0 * (Xq.double().t() @ diff)).abs() <= bound).all())
+
+
+@pytest.mark.parametrize("value", [float("inf"), float("-inf"), float("nan"), 3.4e38, 1e30, 1e-40])
+def test_hessian_of_extreme_inputs_is_fp32_arithmetic(value):
+    """Infinities, NaN, values that round to infinity in bf16, overflow and
+    denormals: what fp32 products and sums of them give."""
+    m, d = 70, 136
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(7)
+    X = torch.randint(-3, 4, (m, d), generator=gen, device="cuda").float()
+    X[5, 3] = value
+    X[9, 130] = value
+    X[20:30, 7] = 0.0
+    H = torch.zeros(d, d, device="cuda", dtype=torch.float64)
+    jb.hessian_accumulate(X, H, 1.0)
+    Xc = X.cpu()
+    ref = torch.zeros(d, d)
+    for t in range(m):
+        ref = ref + Xc[t][:, None] * Xc[t][None, :]
+    got = H.cpu()
+    fin = torch.isfinite(ref)
+    assert torch.equal(torch.isfinite(got) & (got.abs() <= 3.5e38), fin)
+    # (two products of finite values that overflow with opposite signs: NaN where
+    # each is rounded, an infinity where they are fused into the sum)
+    if not np.isfinite(value):
+        assert torch.equal(torch.isnan(got), torch.isnan(ref))
+    tol = 257 * 2.0 ** -24 * (Xc.double().nan_to_num(0, 0, 0).abs().t()
+                              @ Xc.double().nan_to_num(0, 0, 0).abs()) + 1e-44
+    assert bool(((got - ref.double()).abs() <= tol)[fin].all())
+
+
+@pytest.mark.parametrize("rows,cols,g", [(3, 32, 32), (64, 64, 64), (65, 192, 64), (130, 2176, 128),
+                                         (2050, 2176, 128)])
+def test_objective_tiles(rows, cols, g):
+    W, H, q, s, z = random_layer(rows, cols, g, 4, seed=rows)
+    gk = GpuLayer(W, H, q, s, z, g, 4, prepare=False)
+    F = jarq.objective_rows(W, H, q, s, z, g)
+    assert np.all(np.abs(gk.objective() - F) <= 1e-5 * F)
+
+
+def test_objective_of_an_infinite_weight():
+    W, H, q, s, z = random_layer(70, 128, 64, 4, seed=3)
+    W[5, 9] = np.inf
+    W[69, 100] = np.nan
+    F = GpuLayer(W, H, q, s, z, 64, 4, prepare=False).objective()
+    ref = jarq.objective_rows(np.delete(W, [5, 69], 0), H, np.delete(q, [5, 69], 0),
+                              np.delete(s, [5, 69], 0), np.delete(z, [5, 69], 0), 64)
+    assert not np.isfinite(F[5]) and not np.isfinite(F[69])
+    assert np.all(np.abs(np.delete(F, [5, 69]) - ref) <= 1e-5 * ref)
+
+
+@pytest.mark.parametrize("g", [32, 64, 128])
+def test_rtn_ties_and_non_finite_weights(g):
+    """Weights on the grid's halves (exact ties), and groups with an infinity
+    or NaN, round as a correctly rounded division does."""
+    rows, cols, bits = 9, 4 * g, 3
+    rng = np.random.default_rng(g)
+    W = rng.integers(-14, 15, (rows, cols)).astype(np.float32) * np.float32(0.5)
+    W[:, 0], W[:, 1] = -3.5, 3.5
+    W[2, g + 3] = np.inf
+    W[3, g + 3] = -np.inf
+    W[4, g + 3] = np.nan
+    W[5, :g] = 0.0
+    W[6] *= np.float32(1e-42)
+    p = jq.make_params(rows, cols, g, bits)
+    q, s, z = (t.cpu().numpy() for t in jb.rtn(p, to_dev(W)))
+    with np.errstate(all="ignore"):
+        qo, so, zo = hosts.rtn_host(W, g, bits)
+    ok = np.isfinite(W).reshape(rows, -1, g).all(2)
+    assert np.array_equal(s[ok], so[ok]) and np.array_equal(z[ok], zo[ok])
+    wide = np.repeat(ok, g, axis=1)
+    assert np.array_equal(q[wide], qo[wide])
+    assert q.max() <= 7
+
+
+def _refined(rows, cols, g, bits, seed):
+    rng = np.random.default_rng(seed)
+    q = rng.integers(0, 1 << bits, (rows, cols)).astype(np.uint8)
+    s = (0.01 * rng.standard_normal((rows, cols // g))).astype(np.float32)
+    z = rng.integers(0, 1 << bits, (rows, cols // g)).astype(np.int32)
+    return q, s, z
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float16, torch.bfloat16])
+@pytest.mark.parametrize("shift", [0, 1])
+@pytest.mark.parametrize("perm", [False, True])
+def test_dequantize_any_alignment(dtype, shift, perm):
+    """Codes and outputs that are not 16-byte aligned, and a permutation with
+    entries outside the columns (skipped, the columns they miss left alone)."""
+    rows, cols, g = 13, 416, 32
+    q, s, z = _refined(rows, cols, g, 4, 1)
+    p = jq.make_params(rows, cols, g, 4)
+    buf = torch.empty(rows * cols + 16, dtype=torch.uint8, device="cuda")
+    codes = buf[shift:shift + rows * cols].view(rows, cols)
+    codes.copy_(to_dev(q))
+    out = torch.full((rows * cols + 16,), 7.0, dtype=dtype, device="cuda")
+    o = out[shift:shift + rows * cols].view(rows, cols)
+    pm = None
+    order = np.arange(cols)
+    if perm:
+        order = np.random.default_rng(2).permutation(cols)
+        order[5], order[40] = -1, cols
+        pm = to_dev(order.astype(np.int32))
+    jb.dequantize(p, codes, to_dev(s), to_dev(z), dtype=dtype, perm=pm, out=o)
+    w = s.repeat(g, axis=1) * (q.astype(np.float32) - z.repeat(g, axis=1).astype(np.float32))
+    ref = torch.full((rows, cols), 7.0, dtype=dtype)
+    live = (order >= 0) & (order < cols)
+    ref[:, order[live]] = torch.from_numpy(w[:, live]).to(dtype)
+    assert torch.equal(o.cpu(), ref)
+    assert bool((out[rows * cols + shift:] == 7.0).all()) and bool((out[:shift] == 7.0).all())
+
+
+@pytest.mark.parametrize("bits", [1, 2, 3, 4, 5, 6, 7, 8])
+@pytest.mark.parametrize("shift", [0, 3])
+def test_pack_any_alignment(bits, shift):
+    rows, cols, g = 11, 352, 32
+    q, _, _ = _refined(rows, cols, g, bits, bits)
+    p = jq.make_params(rows, cols, g, bits)
+    buf = torch.empty(rows * cols + 16, dtype=torch.uint8, device="cuda")
+    codes = buf[shift:shift + rows * cols].view(rows, cols)
+    codes.copy_(to_dev(q))
+    packed = jb.pack_codes(p, codes)
+    assert np.array_equal(packed.cpu().numpy().view(np.uint32), post.pack(q, bits))
+    back = torch.zeros(rows * cols + 16, dtype=torch.uint8, device="cuda")
+    b = back[shift:shift + rows * cols].view(rows, cols)
+    jb.unpack_codes(p, packed, out=b)
+    assert np.array_equal(b.cpu().numpy(), q)
+    assert int(back[rows * cols + shift:].sum()) == 0
+
+
+@pytest.mark.parametrize("d", [1, 15, 16, 17, 4095, 4096, 4097])
+def test_act_order_sizes(d):
+    rng = np.random.default_rng(d)
+    diag = rng.integers(0, max(2, d // 3), d).astype(np.float32)   # many ties
+    H = torch.zeros(d, d, device="cuda")
+    H.diagonal().copy_(to_dev(diag))
+    perm = jb.act_order(H).cpu().numpy()
+    assert np.array_equal(perm, np.argsort(-diag, kind="stable"))
