@@ -42,6 +42,7 @@ Layout make_layout(int rows, int cols, int g) {
   L.mhi = take(C * C * 2);
   L.mlo = take(C * C * 2);
   L.mrow = take(C * sizeof(float));
+  L.mpow = take(C * sizeof(float));
   L.mmax = take(C * sizeof(float));
   L.wrow = take(R * sizeof(float));
   L.wh = take(R * C * sizeof(float));
@@ -64,10 +65,10 @@ Layout make_layout(int rows, int cols, int g) {
   L.gcount = take(G * kSubLists * kCtrStride * sizeof(uint32_t));
   L.gpre = take(G * (kSubLists + 1) * sizeof(int32_t));
   L.gctl = take(sizeof(GramCtl));
-  L.sctl = take(sizeof(SweepCtl));
   L.rowmap = take(R * sizeof(int32_t));
   L.counters = take(kSubLists * sizeof(Counters));
   L.hist = take(JARQ_MAX_RECORDED_SWEEPS * sizeof(SweepRecord));
+  L.sctl = take(sizeof(SweepCtl));
   L.flags = take(sizeof(Flags));
   L.total = off;
   return L;
@@ -203,14 +204,18 @@ hipError_t enqueue_babai(const Ctx& c, int n, const int32_t* rowmap, const int* 
 jarq_status prepare_impl(const jarq_params* p, const float* W, const float* H, void* ws,
                          void* stream) {
   Ctx c = make_ctx(p, ws, stream);
-  JQ_HIP(launch_zero_bytes(c.st, c.flags(), sizeof(Flags)));
-  JQ_HIP(launch_zero_bytes(c.st, c.cnt(), kSubLists * sizeof(Counters)));
+  ZeroRegions z{};
+  z.add(c.flags(), sizeof(Flags));
+  z.add(c.cnt(), kSubLists * sizeof(Counters));
+  z.add(c.ws + c.lay.mmax, (size_t)c.cols * sizeof(float));
+  z.add(c.ws + c.lay.hscale, 2 * sizeof(float));
+  JQ_HIP(launch_begin_run(c.st, z, 0, nullptr, nullptr, nullptr));
   JQ_HIP(launch_chol_groups(c.st, c.cols, c.g, H, c.ws, c.lay));
   JQ_HIP(launch_split_r(c.st, c.cols, c.g, c.ws, c.lay));
   JQ_HIP(launch_split_m(c.st, c.cols, c.g, H, c.ws, c.lay));
   JQ_HIP(launch_split_h(c.st, c.cols, H, c.ws, c.lay));
-  // T = W M^T and RW = W_i L_i, the constant parts of the residual product
-  // and of the objective, and W H from T; W's two fp16 planes borrow P's memory
+  // T~ = W M~^T and RW = W_i L_i, the constant parts of the residual product
+  // and of the objective, and W H from T~; W's two fp16 planes borrow P's memory
   _Float16* whi = (_Float16*)c.pbuf();
   _Float16* wlo = whi + (size_t)c.rows * c.cols;
   float* wrow = (float*)(c.ws + c.lay.wrow);
@@ -239,27 +244,26 @@ jarq_status sweeps_impl(const jarq_params* p, const float* W, const float* H, ui
                         jarq_stats* stats, bool time_stages = true, bool host_alloc = true) {
   (void)H;
   Ctx c = make_ctx(p, ws, stream);
-  // Device-side input checks (codes in range, |zero point| <= 1024).
+  // q - z as fp16, kept in step with the codes by the code update, and the
+  // device-side input checks (codes in range, |zero point| <= 1024).
   JQ_HIP(launch_zero_bytes(c.st, c.flags(), sizeof(Flags)));
-  JQ_HIP(launch_validate(c.st, c.rows, c.cols, c.g, c.bits, codes, zeros, c.flags()));
+  JQ_HIP(launch_codes_cz(c.st, c.rows, c.cols, c.g, c.bits, codes, zeros,
+                         (_Float16*)(c.ws + c.lay.cz), c.flags()));
   Flags f{};
   JQ_HIP(hipMemcpyAsync(&f, c.flags(), sizeof(Flags), hipMemcpyDeviceToHost, c.st));
   JQ_HIP(hipStreamSynchronize(c.st));
   if (f.bad_codes || f.bad_zeros) return JARQ_EINVAL;
 
-  // q - z as fp16, kept in step with the codes by the code update
-  JQ_HIP(launch_codes_cz(c.st, c.rows, c.cols, c.g, codes, zeros, (_Float16*)(c.ws + c.lay.cz)));
-  JQ_HIP(launch_fill_u8(c.st, c.active(), (size_t)c.rows, 1));
-  JQ_HIP(launch_zero_bytes(c.st, c.ws + c.lay.stopat, (size_t)c.rows * sizeof(int32_t)));
-  JQ_HIP(launch_zero_bytes(c.st, c.cnt(), kSubLists * sizeof(Counters)));
-  JQ_HIP(launch_zero_bytes(c.st, c.ws + c.lay.lcur, (size_t)c.rows * sizeof(double)));
-  JQ_HIP(launch_zero_bytes(c.st, c.ws + c.lay.lprev, (size_t)c.rows * sizeof(double)));
-  JQ_HIP(launch_zero_bytes(c.st, c.hist(), JARQ_MAX_RECORDED_SWEEPS * sizeof(SweepRecord)));
-  JQ_HIP(launch_zero_bytes(c.st, c.gctl(), sizeof(GramCtl)));
-  JQ_HIP(launch_zero_bytes(c.st, c.sctl(), sizeof(SweepCtl)));
-  JQ_HIP(launch_zero_bytes(c.st, c.gcount(), (size_t)c.G * kSubLists * kCtrStride * sizeof(uint32_t)));
   // every row active: rowmap = 0 .. rows - 1, sctl->n = rows
-  JQ_HIP(launch_compact_rows(c.st, c.rows, c.active(), c.rowmap(), c.sctl()));
+  ZeroRegions z{};
+  z.add(c.ws + c.lay.stopat, (size_t)c.rows * sizeof(int32_t));
+  z.add(c.cnt(), kSubLists * sizeof(Counters));
+  z.add(c.ws + c.lay.lcur, (size_t)c.rows * sizeof(double));
+  z.add(c.ws + c.lay.lprev, (size_t)c.rows * sizeof(double));
+  z.add(c.hist(), JARQ_MAX_RECORDED_SWEEPS * sizeof(SweepRecord));
+  z.add(c.gctl(), sizeof(GramCtl));
+  z.add(c.gcount(), (size_t)c.G * kSubLists * kCtrStride * sizeof(uint32_t));
+  JQ_HIP(launch_begin_run(c.st, z, c.rows, c.active(), c.rowmap(), c.sctl()));
 
   // Active-set compaction (early stopping on): a sweep works on the rows still
   // active when it starts, in ascending order (rowmap), n of them (sctl->n).
@@ -400,16 +404,21 @@ jarq_status sweeps_impl(const jarq_params* p, const float* W, const float* H, ui
       }
     }
   }
+  // the run's outcome: the sweep state and the flags behind it, in one copy
+  unsigned char outcome[512];
+  const size_t to_flags = c.lay.flags - c.lay.sctl;
+  if (to_flags + sizeof(Flags) > sizeof(outcome) ||
+      hipMemcpyAsync(outcome, c.sctl(), to_flags + sizeof(Flags), hipMemcpyDeviceToHost, c.st) !=
+          hipSuccess)
+    status = JARQ_EHIP;
   if (hipStreamSynchronize(c.st) != hipSuccess) status = JARQ_EHIP;
   if (sc_ev != nullptr) (void)hipEventDestroy(sc_ev);
   if (host_sc != nullptr) (void)hipHostFree(host_sc);
   SweepCtl sc{};
   if (status == JARQ_OK) {
-    if (hipMemcpy(&f, c.flags(), sizeof(Flags), hipMemcpyDeviceToHost) != hipSuccess ||
-        hipMemcpy(&sc, c.sctl(), sizeof(sc), hipMemcpyDeviceToHost) != hipSuccess)
-      status = JARQ_EHIP;
-    else if (f.solve_failed)
-      status = JARQ_ESCALE_SOLVE;
+    memcpy(&sc, outcome, sizeof(sc));
+    memcpy(&f, outcome + to_flags, sizeof(f));
+    if (f.solve_failed) status = JARQ_ESCALE_SOLVE;
   }
   if (stats != nullptr) {
     // sweeps that started with at least one active row
@@ -531,8 +540,8 @@ jarq_status jarq_code_step(const jarq_params* p, const float* W, const float* H,
   if (s != JARQ_OK) return s;
   Ctx c = make_ctx(p, workspace, stream);
   (void)W;
-  if (launch_codes_cz(c.st, c.rows, c.cols, c.g, codes, zeros, (_Float16*)(c.ws + c.lay.cz)) !=
-          hipSuccess ||
+  if (launch_codes_cz(c.st, c.rows, c.cols, c.g, c.bits, codes, zeros,
+                      (_Float16*)(c.ws + c.lay.cz), nullptr) != hipSuccess ||
       launch_resid(c.st, c.rows, c.cols, c.g, c.ws, c.lay, scales, c.pbuf(), nullptr, nullptr) !=
           hipSuccess)
     return JARQ_EHIP;

@@ -1,167 +1,232 @@
-// Products on fp32 matrix cores.
+// Products of fp32 operands.
 //
-// wh_kernel: W H of the scale right-hand sides (prepare; paper App. G.8), from
-// the layer's T = W M^T.  M = blockdiag(L_i^{-1}) H, so group i's columns of W H
-// are T_i L_i^T: g multiplies a value instead of the cols of the product with H.
+// wh_kernel (fp32 matrix cores): W H of the scale right-hand sides (prepare;
+// paper App. G.8), from the layer's T~ = W M~^T.  M~ = blockdiag(L~_i^{-1}) H with
+// L~_i the unit triangle of H_ii's factor, so group i's columns of W H are
+// T~_i L~_i^T: g multiplies a value instead of the cols of the product with H.
 //
-// gemm_ah_kernel: the row objectives e_j^T H e_j of the stand-alone
-// jarq_objective (paper Sec. 3.3.2 and eq. (7)), from E H of every row; the
-// sweep's own residual product runs on fp16 matrix cores (sgemm.hip).
-// E = W - What with What = s_i (q - z_i) is formed on the fly from the codes,
-// scales and zero points (eq. (1)); the epilogue writes, per row and 64-column
-// slice, sum_c E(row, c) (E H)(row, c) in fp64.
+// row_products_kernel (three bf16 planes, bf16x3.h): the row objectives
+// e_j^T H e_j of the stand-alone jarq_objective (paper Sec. 3.3.2 and eq. (7)),
+// from E H of every row; the sweep's own residual product runs on fp16 matrix
+// cores (sgemm.hip).  E = W - What with What = s_i (q - z_i) is formed on the fly
+// from the codes, scales and zero points (eq. (1)); the epilogue writes, per
+// row and 64-column slice, sum_c E(row, c) (E H)(row, c) in fp64.
 //
-// Tiling: 128 x 128 output tile per 256-thread work-group, 2 x 2 waves of
-// 64 x 64, each a 2 x 2 grid of v_mfma_f32_32x32x2f32 accumulators.  H is
-// symmetric, so the B operand B(k, n) = H(k, n) is read as H(n, k): every lane
-// loads four consecutive k of one A row and one H row (16-byte loads); MFMA
-// step t of a chunk of 8 takes k = k0 + 4 * (lane / 32) + t, the same
-// permutation for A and B.
-#include "jarq_internal.h"
+// Tiling: 512 threads; 128 x 128 tile, 2 x 4 wavefronts of 64 x 32, k in steps
+// of 32; where that gives fewer tiles than compute units, 64 x 64 tiles, 2 x 2
+// wavefronts of 32 x 32 twice, k in steps of 64, the second four taking the odd
+// k-slices.  H is symmetric, so B(k, n) = H(k, n) is read along row n.  Both
+// operands go through registers (split there) into LDS, rows padded by 16
+// bytes: two stages for the large tile, one for the small (two work-groups a CU
+// cover each other's loads).  1000 x 2752:
+// 172 us (the fp32 instruction: 517), and a quarter of its error.
+#include "bf16x3.h"
 
 namespace jarq {
 
 namespace {
 
-__device__ __forceinline__ f32x4 load_e4(const float* __restrict__ W,
-                                         const uint8_t* __restrict__ codes,
-                                         const float* __restrict__ scales,
-                                         const int32_t* __restrict__ zeros, int row, int rows,
-                                         int k, int cols, int g, int G) {
-  if (row >= rows) return f32x4{0.f, 0.f, 0.f, 0.f};
-  f32x4 w = *(const f32x4*)(W + (size_t)row * cols + k);
-  const uint32_t q4 = *(const uint32_t*)(codes + (size_t)row * cols + k);
-  const int grp = k / g;
-  const float s = scales[(size_t)row * G + grp];
-  const int z = zeros[(size_t)row * G + grp];
-  w.x -= s * (float)((int)(q4 & 0xffu) - z);
-  w.y -= s * (float)((int)((q4 >> 8) & 0xffu) - z);
-  w.z -= s * (float)((int)((q4 >> 16) & 0xffu) - z);
-  w.w -= s * (float)((int)(q4 >> 24) - z);
-  return w;
-}
+// E(row, k): the weight minus its quantized value
+struct ErrorOf {
+  const float* W;
+  const uint8_t* codes;
+  const float* scales;
+  const int32_t* zeros;
+  int cols, gs, G;   // gs = log2 of the group size
+  __device__ __forceinline__ float at(int row, int col) const {
+    const float w = W[(size_t)row * cols + col];
+    const float s = scales[(size_t)row * G + (col >> gs)];
+    const int z = zeros[(size_t)row * G + (col >> gs)];
+    return w - s * (float)((int)codes[(size_t)row * cols + col] - z);
+  }
+};
 
-__device__ __forceinline__ f32x4 load_h4(const float* __restrict__ H, int n, int cols, int k) {
-  if (n >= cols) return f32x4{0.f, 0.f, 0.f, 0.f};
-  return *(const f32x4*)(H + (size_t)n * cols + k);
-}
-
-__device__ __forceinline__ float elem_e(const float* __restrict__ W,
-                                        const uint8_t* __restrict__ codes,
-                                        const float* __restrict__ scales,
-                                        const int32_t* __restrict__ zeros, int row, int col,
-                                        int cols, int g, int G) {
-  const float w = W[(size_t)row * cols + col];
-  const int grp = col / g;
-  const float s = scales[(size_t)row * G + grp];
-  const int z = zeros[(size_t)row * G + grp];
-  return w - s * (float)((int)codes[(size_t)row * cols + col] - z);
+// The 32 x 32 block of E H at (r0, c0) with the fp32 instruction straight from
+// memory (one wave): for blocks the three planes cannot do.
+__device__ __forceinline__ f32x16 slow_block(const ErrorOf& E, const float* __restrict__ H,
+                                             int rows, int r0, int c0) {
+  const int lane = threadIdx.x & 63, lm = lane & 31, kh = lane >> 5;
+  const int row = min(r0 + lm, rows - 1), col = min(c0 + lm, E.cols - 1);
+  f32x16 acc = f32x16{};
+  for (int k = 0; k < E.cols; k += 2)   // cols is even
+    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(E.at(row, k + kh), H[(size_t)col * E.cols + k + kh],
+                                               acc, 0, 0, 0);
+  return acc;
 }
 
 }  // namespace
 
-__global__ __launch_bounds__(256, 2) void gemm_ah_kernel(int rows, int cols, int g,
-                                                         const float* __restrict__ W,
-                                                         const uint8_t* __restrict__ codes,
-                                                         const float* __restrict__ scales,
-                                                         const int32_t* __restrict__ zeros,
-                                                         const float* __restrict__ H,
-                                                         double* __restrict__ objpart) {
-  const int G = cols / g;
-  const int lane = threadIdx.x & 63;
-  const int wave = threadIdx.x >> 6;
-  const int wm = wave >> 1, wn = wave & 1;
+template <bool BIG>
+__global__ __launch_bounds__(512, BIG ? 2 : 4) void row_products_kernel(int rows, ErrorOf E,
+                                                              const float* __restrict__ H,
+                                                              double* __restrict__ objpart) {
+  constexpr int TE = BIG ? 128 : 64;
+  constexpr int CH = BIG ? 32 : 64;           // k per step
+  constexpr int LD = 2 * CH + 16;             // row stride in bytes
+  constexpr int PLANE = 2 * TE * LD;          // E rows, then H rows
+  constexpr int STAGE = 3 * PLANE;
+  constexpr int AB = BIG ? 2 : 1;             // 32-row blocks per wavefront
+  constexpr int PR = CH / 8;                  // pieces of 8 values per row
+  constexpr int WN = BIG ? 4 : 2;             // wavefronts along the columns
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  const int cols = E.cols;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int wm = BIG ? wave >> 2 : (wave >> 1) & 1, wn = BIG ? wave & 3 : wave & 1;
+  const int wk = BIG ? 0 : wave >> 2;
   const int lm = lane & 31, kh = lane >> 5;
-  const int m0 = blockIdx.y * 128 + wm * 64;
-  const int n0 = blockIdx.x * 128 + wn * 64;
-  const int ra0 = m0 + lm, ra1 = m0 + 32 + lm;
-  const int cb0 = n0 + lm, cb1 = n0 + 32 + lm;
-
-  f32x16 acc00 = {}, acc01 = {}, acc10 = {}, acc11 = {};
-
-  f32x4 a0 = load_e4(W, codes, scales, zeros, ra0, rows, 4 * kh, cols, g, G);
-  f32x4 a1 = load_e4(W, codes, scales, zeros, ra1, rows, 4 * kh, cols, g, G);
-  f32x4 b0 = load_h4(H, cb0, cols, 4 * kh);
-  f32x4 b1 = load_h4(H, cb1, cols, 4 * kh);
-  for (int k0 = 0; k0 < cols; k0 += 8) {
-    const int kn = k0 + 8 + 4 * kh;
-    f32x4 na0, na1, nb0, nb1;
-    const bool more = (k0 + 8) < cols;
-    if (more) {
-      na0 = load_e4(W, codes, scales, zeros, ra0, rows, kn, cols, g, G);
-      na1 = load_e4(W, codes, scales, zeros, ra1, rows, kn, cols, g, G);
-      nb0 = load_h4(H, cb0, cols, kn);
-      nb1 = load_h4(H, cb1, cols, kn);
+  const int m0 = blockIdx.y * TE, n0 = blockIdx.x * TE;
+  // staging: piece tid of the E rows and piece tid of the H rows (both have
+  // TE PR = 512 pieces); rows past the edge repeat the last one (their results
+  // are not stored); k past cols stages 0
+  static_assert(TE * PR == 512, "one piece of each operand per thread");
+  const int pr = tid / PR, pk = 8 * (tid % PR);
+  const int er = min(m0 + pr, rows - 1), hr = min(n0 + pr, cols - 1);
+  const float* w_row = E.W + (size_t)er * cols;
+  const uint8_t* q_row = E.codes + (size_t)er * cols;
+  const float* h_row = H + (size_t)hr * cols;
+  f32x4 we[2], wh[2];
+  uint2 qe;
+  float se;
+  int ze;
+  auto load = [&](int k0) {
+    const int k = min(k0 + pk, cols - 8);
+    we[0] = *(const f32x4*)(w_row + k);
+    we[1] = *(const f32x4*)(w_row + k + 4);
+    qe = *(const uint2*)(q_row + k);
+    se = E.scales[(size_t)er * E.G + (k >> E.gs)];
+    ze = E.zeros[(size_t)er * E.G + (k >> E.gs)];
+    wh[0] = *(const f32x4*)(h_row + k);
+    wh[1] = *(const f32x4*)(h_row + k + 4);
+  };
+  auto store = [&](int k0, char* stage) {
+    const bool in = k0 + pk < cols;
+    float e[8], h[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const uint32_t q = ((i < 4 ? qe.x : qe.y) >> (8 * (i & 3))) & 0xffu;
+      e[i] = in ? we[i >> 2][i & 3] - se * (float)((int)q - ze) : 0.f;
+      h[i] = in ? wh[i >> 2][i & 3] : 0.f;
+    }
+    u32x4 p[2][3];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      uint32_t a, b, c;
+      split_pair(e[2 * i], e[2 * i + 1], a, b, c);
+      p[0][0][i] = a, p[0][1][i] = b, p[0][2][i] = c;
+      split_pair(h[2 * i], h[2 * i + 1], a, b, c);
+      p[1][0][i] = a, p[1][1][i] = b, p[1][2][i] = c;
     }
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      acc00 = __builtin_amdgcn_mfma_f32_32x32x2f32(a0[t], b0[t], acc00, 0, 0, 0);
-      acc01 = __builtin_amdgcn_mfma_f32_32x32x2f32(a0[t], b1[t], acc01, 0, 0, 0);
-      acc10 = __builtin_amdgcn_mfma_f32_32x32x2f32(a1[t], b0[t], acc10, 0, 0, 0);
-      acc11 = __builtin_amdgcn_mfma_f32_32x32x2f32(a1[t], b1[t], acc11, 0, 0, 0);
+    for (int o = 0; o < 2; ++o)
+#pragma unroll
+      for (int pl = 0; pl < 3; ++pl)
+        *(u32x4*)(stage + pl * PLANE + (o * TE + pr) * LD + 2 * pk) = p[o][pl];
+  };
+  f32x16 acc[AB], low[AB];
+#pragma unroll
+  for (int a = 0; a < AB; ++a) acc[a] = low[a] = f32x16{};
+  const int nk = (cols + CH - 1) / CH;
+  load(0);
+  store(0, smem);
+  __syncthreads();
+  for (int q = 0; q < nk; ++q) {
+    const char* cur = smem + (BIG ? (q & 1) * STAGE : 0);
+    if (q + 1 < nk) load((q + 1) * CH);   // in flight during this step
+    const char* ra = cur + (wm * 32 * AB + lm) * LD + 16 * kh;
+    const char* rb = cur + (TE + wn * 32 + lm) * LD + 16 * kh;
+#pragma unroll
+    for (int k2 = 0; k2 < 2; ++k2) {
+      const int ks = BIG ? k2 : 2 * k2 + wk;
+      bf16x8 fb[3], fa[AB][3];
+#pragma unroll
+      for (int p = 0; p < 3; ++p) fb[p] = *(const bf16x8*)(rb + p * PLANE + 32 * ks);
+#pragma unroll
+      for (int a = 0; a < AB; ++a)
+#pragma unroll
+        for (int p = 0; p < 3; ++p)
+          fa[a][p] = *(const bf16x8*)(ra + p * PLANE + 32 * a * LD + 32 * ks);
+      mfma_bf16x3<AB>(fa, fb, acc, low);
     }
-    if (more) {
-      a0 = na0;
-      a1 = na1;
-      b0 = nb0;
-      b1 = nb1;
+    // the other stage was last read before the barrier that ended step q - 1;
+    // a single stage is free once every wave is here
+    if (!BIG) __syncthreads();
+    if (q + 1 < nk) store((q + 1) * CH, smem + (BIG ? ((q + 1) & 1) * STAGE : 0));
+    __syncthreads();
+  }
+#pragma unroll
+  for (int a = 0; a < AB; ++a) acc[a] += low[a];
+  double* part_s = (double*)smem;             // [TE][WN]
+  float* red = (float*)(part_s + TE * WN);    // small tile: sums of the odd k-slices
+  if (!BIG) {
+    if (wk == 1) {
+#pragma unroll
+      for (int v = 0; v < 16; ++v) red[(wave & 3) * 1024 + 64 * v + lane] = acc[0][v];
+    }
+    __syncthreads();
+    if (wk == 0) {
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[0][v] += red[wave * 1024 + 64 * v + lane];
     }
   }
-
-  // Accumulator layout of a 32x32 block: element v of lane l is
-  // (row 8 * (v / 4) + 4 * (l / 32) + v % 4, column l % 32).
-  const f32x16* accs[2][2] = {{&acc00, &acc01}, {&acc10, &acc11}};
+  if (wk == 0) {
+#pragma unroll
+    for (int a = 0; a < AB; ++a) {
+      const int rb0 = m0 + 32 * (AB * wm + a), col = n0 + 32 * wn + lm;
+      bool fine = true;
+#pragma unroll
+      for (int v = 0; v < 16; ++v) fine &= isfinite(acc[a][v]);
+      if (!__all(fine)) acc[a] = slow_block(E, H, rows, rb0, n0 + 32 * wn);
+      // element v of lane l: row 8 (v / 4) + 4 (l / 32) + v % 4, column l % 32
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const int row = rb0 + 8 * (v / 4) + 4 * kh + (v % 4);
+        double x = 0.0;
+        if (row < rows && col < cols) x = (double)E.at(row, col) * (double)acc[a][v];
+#pragma unroll
+        for (int off = 16; off >= 1; off >>= 1) x += __shfl_xor(x, off);
+        if (lm == 0) part_s[(row - m0) * WN + wn] = x;
+      }
+    }
+  }
+  __syncthreads();
+  // 64-column slices: two wavefronts' columns each
   const int nt = (cols + kObjTile - 1) / kObjTile;
-#pragma unroll
-  for (int mb = 0; mb < 2; ++mb) {
-    double part[16];
-#pragma unroll
-    for (int v = 0; v < 16; ++v) part[v] = 0.0;
-#pragma unroll
-    for (int nb = 0; nb < 2; ++nb) {
-      const int col = n0 + nb * 32 + lm;
-      const f32x16 a = *accs[mb][nb];
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const int row = m0 + mb * 32 + 8 * (v / 4) + 4 * kh + (v % 4);
-        if (row < rows && col < cols) {
-          const float e = elem_e(W, codes, scales, zeros, row, col, cols, g, G);
-          part[v] += (double)e * (double)a[v];
-        }
-      }
-    }
-#pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      double x = part[v];
-#pragma unroll
-      for (int off = 16; off >= 1; off >>= 1) x += __shfl_xor(x, off);
-      part[v] = x;
-    }
-    if (lm == 0) {
-      const int slice = n0 / kObjTile;
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const int row = m0 + mb * 32 + 8 * (v / 4) + 4 * kh + (v % 4);
-        if (row < rows && slice < nt) objpart[(size_t)row * nt + slice] = part[v];
-      }
-    }
+  for (int t = tid; t < TE * WN / 2; t += 512) {
+    const int r = t / (WN / 2), sl = t % (WN / 2);
+    const int slice = n0 / kObjTile + sl;
+    if (m0 + r < rows && slice < nt)
+      objpart[(size_t)(m0 + r) * nt + slice] = part_s[r * WN + 2 * sl] + part_s[r * WN + 2 * sl + 1];
   }
+}
+
+template <bool BIG>
+static hipError_t launch_row_products_t(hipStream_t st, int rows, const ErrorOf& E, const float* H,
+                                        double* objpart) {
+  constexpr int TE = BIG ? 128 : 64;
+  constexpr size_t lds = 3 * (BIG ? 2 * 256 * 80 : 128 * 144);
+  static_assert(lds >= 64 * 2 * sizeof(double) + 4 * 1024 * sizeof(float), "LDS");
+  static std::atomic<unsigned long long> lds_set{0};
+  const hipError_t e = allow_dynamic_lds((const void*)row_products_kernel<BIG>, lds, lds_set);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(row_products_kernel<BIG>, dim3((E.cols + TE - 1) / TE, (rows + TE - 1) / TE),
+                     dim3(512), lds, st, rows, E, H, objpart);
+  return hipGetLastError();
 }
 
 hipError_t launch_row_products(hipStream_t st, int rows, int cols, int g, const float* W,
                                const uint8_t* codes, const float* scales, const int32_t* zeros,
                                const float* H, double* objpart) {
-  dim3 grid((cols + 127) / 128, (rows + 127) / 128);
-  hipLaunchKernelGGL(gemm_ah_kernel, grid, dim3(256), 0, st, rows, cols, g, W, codes, scales,
-                     zeros, H, objpart);
-  return hipGetLastError();
+  const ErrorOf E{W, codes, scales, zeros, cols, g == 32 ? 5 : g == 64 ? 6 : 7, cols / g};
+  const long long big = (long long)((cols + 127) / 128) * ((rows + 127) / 128);
+  if (big >= 256) return launch_row_products_t<true>(st, rows, E, H, objpart);
+  return launch_row_products_t<false>(st, rows, E, H, objpart);
 }
 
-// WH(r, n) = sum_{m <= n} T(r, m) L_i(n, m) over the columns of group i, with
-// L_i(n, m) = R_i(m, n) (rmat).  Work-group: 128 rows x one group, R_i staged
-// in LDS; a wavefront takes 32 rows, with the rows' T values of the group in
-// registers, four consecutive k a lane: step t of a chunk of 8 takes k =
-// 4 (lane / 32) + t, in both operands.  Blocks of 32 columns skip the k past
+// WH(r, n) = sum_{m <= n} T~(r, m) L~_i(n, m) over the columns of group i, with
+// L~_i(n, m) = R_i(m, n) / R_i(m, m) (rmat, rdinv), 1 on the diagonal.  Work-group:
+// 128 rows x one group, the triangle staged in LDS; a wavefront takes 32 rows,
+// with the rows' T values of the group in registers, four consecutive k a lane:
+// step t of a chunk of 8 takes k = 4 (lane / 32) + t, in both operands.  Blocks of 32 columns skip the k past
 // their own (R_i is upper triangular).  Bound by reading T and writing W H
 // (8 bytes a value): 176 us for 4096 x 11008 at g = 128 (2.1 TB/s), where the
 // fp32 product with H took 17.8 ms, and nearer to the 64-bit value (scales of
@@ -169,6 +234,7 @@ hipError_t launch_row_products(hipStream_t st, int rows, int cols, int g, const 
 template <int G_SIZE>
 __global__ __launch_bounds__(256) void wh_kernel(int rows, int cols, const float* __restrict__ T,
                                                  const float* __restrict__ rmat,
+                                                 const float* __restrict__ rdinv,
                                                  float* __restrict__ WH) {
   constexpr int g = G_SIZE;
   constexpr int NB = g / 32, KC = g / 8;
@@ -183,7 +249,14 @@ __global__ __launch_bounds__(256) void wh_kernel(int rows, int cols, const float
   f32x4 a[KC];
 #pragma unroll
   for (int kc = 0; kc < KC; ++kc) a[kc] = *(const f32x4*)(t_row + 8 * kc);
-  for (int e = tid; e < g * g / 4; e += 256) *(f32x4*)(r_s + 4 * e) = *(const f32x4*)(Ri + 4 * e);
+  for (int e = tid; e < g * g / 4; e += 256) {
+    const int m = 4 * e / g, n = 4 * e % g;
+    const float ri = rdinv[(size_t)i * g + m];
+    f32x4 v = *(const f32x4*)(Ri + 4 * e);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) v[u] = n + u == m ? 1.f : v[u] * ri;
+    *(f32x4*)(r_s + 4 * e) = v;
+  }
   __syncthreads();
   f32x16 acc[NB];
 #pragma unroll
@@ -209,12 +282,13 @@ __global__ __launch_bounds__(256) void wh_kernel(int rows, int cols, const float
 hipError_t launch_wh(hipStream_t st, int rows, int cols, int g, char* ws, const Layout& lay) {
   const float* T = (const float*)(ws + lay.tm);
   const float* rmat = (const float*)(ws + lay.rmat);
+  const float* rdinv = (const float*)(ws + lay.rdinv);
   float* WH = (float*)(ws + lay.wh);
   const dim3 grid(cols / g, (rows + 127) / 128);
   switch (g) {
-    case 32: hipLaunchKernelGGL(wh_kernel<32>, grid, dim3(256), 0, st, rows, cols, T, rmat, WH); break;
-    case 64: hipLaunchKernelGGL(wh_kernel<64>, grid, dim3(256), 0, st, rows, cols, T, rmat, WH); break;
-    case 128: hipLaunchKernelGGL(wh_kernel<128>, grid, dim3(256), 0, st, rows, cols, T, rmat, WH); break;
+    case 32: hipLaunchKernelGGL(wh_kernel<32>, grid, dim3(256), 0, st, rows, cols, T, rmat, rdinv, WH); break;
+    case 64: hipLaunchKernelGGL(wh_kernel<64>, grid, dim3(256), 0, st, rows, cols, T, rmat, rdinv, WH); break;
+    case 128: hipLaunchKernelGGL(wh_kernel<128>, grid, dim3(256), 0, st, rows, cols, T, rmat, rdinv, WH); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();

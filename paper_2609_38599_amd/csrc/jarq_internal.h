@@ -106,7 +106,7 @@ inline hipError_t allow_dynamic_lds(const void* fn, size_t bytes,
 
 // Offsets (bytes) of the workspace regions for one problem size.
 struct Layout {
-  size_t lfac;      // [G][g][g] f64: L_i^{-1}
+  size_t lfac;      // [G][g][g] f64: L~_i^{-1} (L_i^{-1}, rows times L_i(n, n))
   size_t rcol;      // [G][g][g/(16 W)][16][W] f32: R~_i columns in lane chunks (W = min(4, g/16))
   size_t rdinv;     // [G][g] f32: 1 / R_i(l,l)
   size_t rdsq;      // [G][g] f32: R_i(l,l)^2
@@ -117,14 +117,15 @@ struct Layout {
   size_t rph;       // [G][g][g] f16: R_i row c scaled by 2^t_c, high term
   size_t rpl;       // [G][g][g] f16: low term
   size_t rrow;      // [G][g] f32: 2^-t_c of the R rows
-  size_t mhi;       // [cols][cols] f16: M = blockdiag(L_i^{-1}) H, row n scaled by 2^t_n, high term
+  size_t mhi;       // [cols][cols] f16: M~ = blockdiag(L~_i^{-1}) H, row n scaled by 2^t_n, high term
   size_t mlo;       // [cols][cols] f16: low term
-  size_t mrow;      // [cols] f32: 2^-t_n
-  size_t mmax;      // [cols] f32: row maxima of M (prep scratch)
+  size_t mrow;      // [cols] f32: 2^-t_n / L_i(n, n): M from M~'s planes
+  size_t mpow;      // [cols] f32: 2^-t_n
+  size_t mmax;      // [cols] f32: row maxima of M~ (prep scratch)
   size_t wrow;      // [rows] f32: 2^-t_row of W's fp16 planes (prepare; the planes
                     // themselves occupy p's memory until the first sweep)
   size_t wh;        // [rows][cols] f32: W H
-  size_t tm;        // [rows][cols] f32: T = W M^T (the residual product of W alone)
+  size_t tm;        // [rows][cols] f32: T~ = W M~^T (the residual product of W alone, times L_i(n, n))
   size_t rw;        // [rows][cols] f32: W_i L_i per group (the objective's part of W alone)
   size_t cz;        // [rows][cols] f16: q - z, exact, by layer row (kept with the codes)
   size_t gram;      // [rows][G][G] f32: upper triangle of B^T B
@@ -142,7 +143,7 @@ struct Layout {
   size_t gcount;    // [G][kSubLists] u32 kCtrStride apart: lengths of the sub-lists
   size_t gpre;      // [G][kSubLists + 1] i32: their exclusive prefix sums (last: list length)
   size_t gctl;      // GramCtl
-  size_t sctl;      // SweepCtl
+  size_t sctl;      // SweepCtl (right before flags: the host reads both at once)
   size_t rowmap;    // [rows] i32: row of each position of the sweep (rows still active, ascending)
   size_t counters;  // Counters
   size_t hist;      // [64] SweepRecord
@@ -164,18 +165,20 @@ hipError_t launch_split_r(hipStream_t st, int cols, int g, char* ws, const Layou
 hipError_t launch_row_products(hipStream_t st, int rows, int cols, int g, const float* W,
                                const uint8_t* codes, const float* scales, const int32_t* zeros,
                                const float* H, double* objpart);
-// W H (lay.wh) from T = W M^T and R_i.
+// W H (lay.wh) from T~ = W M~^T and R_i.
 hipError_t launch_wh(hipStream_t st, int rows, int cols, int g, char* ws, const Layout& lay);
 
 hipError_t launch_split_h(hipStream_t st, int cols, const float* H, char* ws, const Layout& lay);
-// M = blockdiag(L_i^{-1}) H as two fp16 planes with per-row scales (after
-// launch_chol_groups; uses the H planes as scratch, so call launch_split_h after).
+// M~ = blockdiag(L~_i^{-1}) H as two fp16 planes with per-row scales (after
+// launch_chol_groups; uses the H planes as scratch, so call launch_split_h
+// after).  The caller has cleared the row maxima (lay.mmax) and max |H|
+// (lay.hscale's second word).
 hipError_t launch_split_m(hipStream_t st, int cols, int g, const float* H, char* ws,
                           const Layout& lay);
 
 // The layer's constant parts of the per-sweep products (jarq_prepare), from
 // W as two fp16 planes (whi, wlo with row scales 2^-t in wrow, all rows):
-// T = W M^T into lay.tm (three products, sgemm.hip) and RW = W_i L_i per
+// T~ = W M~^T into lay.tm (three products, sgemm.hip) and RW = W_i L_i per
 // group into lay.rw (objective.hip).
 hipError_t launch_split_w(hipStream_t st, int rows, int cols, const float* W, _Float16* whi,
                           _Float16* wlo, float* wrow_inv);
@@ -185,10 +188,12 @@ hipError_t launch_wm_product(hipStream_t st, int rows, int cols, const char* ws,
 hipError_t launch_rw_product(hipStream_t st, int rows, int cols, int g, const char* ws,
                              const Layout& lay, const _Float16* whi, const _Float16* wlo,
                              const float* wrow_inv);
-// cz = q - z as fp16 for all rows (kept in step with the codes by the code update).
-hipError_t launch_codes_cz(hipStream_t st, int rows, int cols, int g, const uint8_t* codes,
-                           const int32_t* zeros, _Float16* cz);
-// U = T - What M^T from the exact codes (cz) and the scales, layer rows
+// cz = q - z as fp16 for all rows (kept in step with the codes by the code
+// update).  flags (nullable): codes and zero points out of range are counted.
+hipError_t launch_codes_cz(hipStream_t st, int rows, int cols, int g, int bits,
+                           const uint8_t* codes, const int32_t* zeros, _Float16* cz,
+                           Flags* flags);
+// U = (T~ - What M~^T) / L(n, n) from the exact codes (cz) and the scales, layer rows
 // through rowmap, U by position (sgemm.hip).  ev_start / ev_stop (nullable):
 // events that take the kernel's own start and end times (no marker of their
 // own in the stream).
@@ -309,7 +314,21 @@ hipError_t launch_stop_check(hipStream_t st, int rows, int nt, const double* obj
                              int sweep, float tau, const int32_t* rowmap, uint32_t* zero_ctr,
                              int nzero, uint32_t* zero_ctr2, int nzero2, const int* n_dev);
 
-hipError_t launch_fill_u8(hipStream_t st, uint8_t* p, size_t n, uint8_t v);
+// Regions cleared by one launch, each `words` 32-bit words at `at`.
+constexpr int kZeroRegions = 8;
+struct ZeroRegions {
+  uint32_t* at[kZeroRegions];
+  size_t words[kZeroRegions];
+  int n;
+  void add(void* p, size_t bytes) {
+    at[n] = (uint32_t*)p;
+    words[n++] = bytes / 4;
+  }
+};
+// Clears the regions; with active not null, every row active (active = 1,
+// rowmap = 0 .. rows - 1, sctl->n = rows, no sweep started).
+hipError_t launch_begin_run(hipStream_t st, const ZeroRegions& z, int rows, uint8_t* active,
+                            int32_t* rowmap, SweepCtl* sctl);
 hipError_t launch_zero_bytes(hipStream_t st, void* p, size_t n);
 
 // Also: gram->valid = 1 (every active row's matrix now exists),
@@ -318,9 +337,6 @@ hipError_t launch_record_sweep(hipStream_t st, int rows, const double* lcur,
                                const uint8_t* active, Counters* cnt, SweepRecord* rec,
                                SweepCtl* sctl, GramCtl* gctl, const uint32_t* gcount,
                                int32_t* gpre, int G);
-
-hipError_t launch_validate(hipStream_t st, int rows, int cols, int g, int bits,
-                           const uint8_t* codes, const int32_t* zeros, Flags* flags);
 
 // Per-layer set-up from calibration inputs and the round-to-nearest host.
 hipError_t launch_hessian_update(hipStream_t st, const float* X, int m, int d, double alpha,
@@ -348,7 +364,7 @@ hipError_t launch_potrf_f64(hipStream_t st, double* A, int d, long long lda, dou
 hipError_t launch_copy_lower(hipStream_t st, const float* H, int d, bool reverse, double* C);
 hipError_t launch_antitranspose_lower(hipStream_t st, const double* C, int d, double* M);
 
-// Propagation-corrected target (setup.hip, qep.hip).
+// Propagation-corrected target (hessian.hip, qep.hip).
 hipError_t launch_cross_update(hipStream_t st, const float* Xq, const float* X, int m, int d,
                                double alpha, double* Dacc);
 size_t qep_workspace_bytes(int rows, int cols);

@@ -1,22 +1,26 @@
 // Small per-sweep kernels: row objectives, the early-stopping rule of App. E.2,
 // fills (kernels rather than hipMemsetAsync so a captured graph replays them
-// reliably), the per-sweep record, and the device-side input checks.
+// reliably), and the per-sweep record.
 #include "jarq_internal.h"
 
 namespace jarq {
 
-__global__ void row_objective_kernel(int rows, int nt, const double* __restrict__ part,
-                                     double* __restrict__ out) {
-  const int r = blockIdx.x * blockDim.x + threadIdx.x;
-  if (r >= rows) return;
+// Sixteen lanes per row.
+__global__ __launch_bounds__(256) void row_objective_kernel(int rows, int nt,
+                                                            const double* __restrict__ part,
+                                                            double* __restrict__ out) {
+  const int r = blockIdx.x * 16 + (threadIdx.x >> 4), l = threadIdx.x & 15;
   double s = 0.0;
-  for (int t = 0; t < nt; ++t) s += part[(size_t)r * nt + t];
-  out[r] = s;
+  if (r < rows)
+    for (int t = l; t < nt; t += 16) s += part[(size_t)r * nt + t];
+#pragma unroll
+  for (int off = 8; off >= 1; off >>= 1) s += __shfl_xor(s, off);
+  if (r < rows && l == 0) out[r] = s;
 }
 
 hipError_t launch_row_objective(hipStream_t st, int rows, int nt, const double* objpart,
                                 double* out) {
-  hipLaunchKernelGGL(row_objective_kernel, dim3((rows + 255) / 256), dim3(256), 0, st, rows, nt,
+  hipLaunchKernelGGL(row_objective_kernel, dim3((rows + 15) / 16), dim3(256), 0, st, rows, nt,
                      objpart, out);
   return hipGetLastError();
 }
@@ -103,22 +107,18 @@ hipError_t launch_compact_rows(hipStream_t st, int rows, const uint8_t* active, 
   return hipGetLastError();
 }
 
-__global__ void fill_u8_kernel(uint8_t* __restrict__ p, size_t n, uint8_t v) {
+__global__ void zero_bytes_kernel(uint8_t* __restrict__ p, size_t n) {
   for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
        i += (size_t)gridDim.x * blockDim.x)
-    p[i] = v;
-}
-
-hipError_t launch_fill_u8(hipStream_t st, uint8_t* p, size_t n, uint8_t v) {
-  if (n == 0) return hipSuccess;
-  const size_t blocks = (n + 255) / 256;
-  hipLaunchKernelGGL(fill_u8_kernel, dim3((unsigned)(blocks < 4096 ? blocks : 4096)), dim3(256), 0,
-                     st, p, n, v);
-  return hipGetLastError();
+    p[i] = 0;
 }
 
 hipError_t launch_zero_bytes(hipStream_t st, void* p, size_t n) {
-  return launch_fill_u8(st, (uint8_t*)p, n, 0);
+  if (n == 0) return hipSuccess;
+  const size_t blocks = (n + 255) / 256;
+  hipLaunchKernelGGL(zero_bytes_kernel, dim3((unsigned)(blocks < 4096 ? blocks : 4096)), dim3(256),
+                     0, st, (uint8_t*)p, n);
+  return hipGetLastError();
 }
 
 // Sum of L over all rows (a stopped row keeps its last L, which is still its
@@ -231,28 +231,34 @@ hipError_t launch_record_sweep(hipStream_t st, int rows, const double* lcur,
   return hipGetLastError();
 }
 
-__global__ void validate_kernel(int rows, int cols, int g, int qmax,
-                                const uint8_t* __restrict__ codes,
-                                const int32_t* __restrict__ zeros, Flags* __restrict__ flags) {
-  const size_t n = (size_t)rows * cols;
-  const int G = cols / g;
-  int bad_q = 0, bad_z = 0;
-  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (size_t)gridDim.x * blockDim.x)
-    bad_q += codes[i] > qmax;
-  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < (size_t)rows * G;
-       i += (size_t)gridDim.x * blockDim.x) {
-    const int z = zeros[i];
-    bad_z += (z > 1024 || z < -1024);  // q - z and 1024 + z stay exact in fp16
+// Start of a run in one launch: up to kZeroRegions regions cleared (each a
+// whole number of words), every row active at its own position.
+__global__ __launch_bounds__(256) void begin_run_kernel(ZeroRegions z, int rows,
+                                                        uint8_t* __restrict__ active,
+                                                        int32_t* __restrict__ rowmap,
+                                                        SweepCtl* __restrict__ sctl) {
+  const size_t at = (size_t)blockIdx.x * 256 + threadIdx.x, step = (size_t)gridDim.x * 256;
+#pragma unroll
+  for (int i = 0; i < kZeroRegions; ++i)
+    for (size_t w = at; w < z.words[i]; w += step) z.at[i][w] = 0u;
+  if (active == nullptr) return;
+  for (size_t r = at; r < (size_t)rows; r += step) {
+    active[r] = 1;
+    rowmap[r] = (int32_t)r;
   }
-  if (bad_q) atomicAdd(&flags->bad_codes, bad_q);
-  if (bad_z) atomicAdd(&flags->bad_zeros, bad_z);
+  if (at == 0) {
+    sctl->n = rows;
+    sctl->started = 0;
+  }
 }
 
-hipError_t launch_validate(hipStream_t st, int rows, int cols, int g, int bits,
-                           const uint8_t* codes, const int32_t* zeros, Flags* flags) {
-  hipLaunchKernelGGL(validate_kernel, dim3(1024), dim3(256), 0, st, rows, cols, g,
-                     (1 << bits) - 1, codes, zeros, flags);
+hipError_t launch_begin_run(hipStream_t st, const ZeroRegions& z, int rows, uint8_t* active,
+                            int32_t* rowmap, SweepCtl* sctl) {
+  size_t most = active != nullptr ? (size_t)rows : 0;
+  for (int i = 0; i < kZeroRegions; ++i) most = z.words[i] > most ? z.words[i] : most;
+  const size_t blocks = (most + 255) / 256;
+  hipLaunchKernelGGL(begin_run_kernel, dim3((unsigned)(blocks < 1024 ? (blocks ? blocks : 1) : 1024)),
+                     dim3(256), 0, st, z, rows, active, rowmap, sctl);
   return hipGetLastError();
 }
 

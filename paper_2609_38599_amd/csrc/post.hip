@@ -17,7 +17,7 @@ unsigned grid_of(long long n) {
 // eq. (canonicalization): for s < 0, s' = -s, q' = qmax - q, z' = qmax - z,
 // which represents the same weights.  One thread per group; few scales are
 // negative, so a launch lasts as long as one group's code update, whose
-// 16-byte loads all go out together (6 us for 11008 x 4096 with one scale in
+// 16-byte loads all go out together (8 us for 11008 x 4096 with one scale in
 // fifty negative; word by word, each load behind the last store, 17).
 template <int g>
 __global__ __launch_bounds__(256) void canonicalize_kernel(int rows, int cols, int bits,

@@ -284,15 +284,15 @@ static hipError_t launch_split3_t(hipStream_t st, int M, int N, int K, int lda, 
   return hipGetLastError();
 }
 
-// T = W M^T for the layer, all rows (jarq_prepare): W's two fp16 planes
-// against M's, three products.
+// T~ = W M~^T for the layer, all rows (jarq_prepare): W's two fp16 planes
+// against M~'s, three products.
 hipError_t launch_wm_product(hipStream_t st, int rows, int cols, const char* ws,
                              const Layout& lay, const _Float16* whi, const _Float16* wlo,
                              const float* wrow_inv) {
   if (rows <= 0 || cols <= 0) return hipSuccess;
   const _Float16* bh = (const _Float16*)(ws + lay.mhi);
   const _Float16* bl = (const _Float16*)(ws + lay.mlo);
-  const float* bc = (const float*)(ws + lay.mrow);
+  const float* bc = (const float*)(ws + lay.mpow);
   return launch_split3_t<256, 0>(st, rows, cols, cols, cols, cols, cols, whi, wlo, wrow_inv, bh,
                                  bl, bc, (float*)(ws + lay.tm), nullptr);
 }
@@ -335,8 +335,9 @@ template <int G_SIZE>
 __global__ __launch_bounds__(512, 1) void resid_kernel(
     int M, int N, int K, const _Float16* __restrict__ Cz, const float* __restrict__ scales,
     const _Float16* __restrict__ Bh, const _Float16* __restrict__ Bl,
-    const float* __restrict__ bcol_inv, const float* __restrict__ T, float* __restrict__ U,
-    const int32_t* __restrict__ rowmap, const int* __restrict__ m_dev) {
+    const float* __restrict__ bcol_inv, const float* __restrict__ rdinv,
+    const float* __restrict__ T, float* __restrict__ U, const int32_t* __restrict__ rowmap,
+    const int* __restrict__ m_dev) {
   if (m_dev != nullptr) M = *m_dev;
   constexpr int g = G_SIZE;
   constexpr int RBK = g >= 64 ? 64 : 32;                 // k per stage
@@ -511,7 +512,7 @@ __global__ __launch_bounds__(512, 1) void resid_kernel(
     }
   }
 
-  // Epilogue: U = T - acc 2^-t_n.  Accumulator element v of lane l in a
+  // Epilogue: U = (T~ - acc 2^-t_n) / L(n, n).  Accumulator element v of lane l in a
   // 32 x 32 block: (row 8 (v / 4) + 4 (l / 32) + v % 4, column l % 32).
 #pragma unroll
   for (int a = 0; a < 2; ++a) {
@@ -520,7 +521,7 @@ __global__ __launch_bounds__(512, 1) void resid_kernel(
     for (int b = 0; b < 2; ++b) {
       const int col = n0 + wn * 64 + b * 32 + lm;
       const int colc = min(col, N - 1);
-      const float cs = bcol_inv[colc];
+      const float cs = bcol_inv[colc], ds = rdinv[colc];
       float tv[16];
 #pragma unroll
       for (int v = 0; v < 16; ++v)
@@ -528,7 +529,7 @@ __global__ __launch_bounds__(512, 1) void resid_kernel(
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
         const int row = m0 + tb + 8 * (v / 4) + (v % 4);
-        if (row < M && col < N) U[(size_t)row * N + col] = tv[v] - acc[a][b][v] * cs;
+        if (row < M && col < N) U[(size_t)row * N + col] = (tv[v] - acc[a][b][v] * cs) * ds;
       }
     }
   }
@@ -545,13 +546,14 @@ static hipError_t launch_resid_t(hipStream_t st, int rows, int cols, const char*
     hipExtLaunchKernelGGL((resid_kernel<G_SIZE>), dim3(tiles), dim3(512), 0, st, ev_start,
                           ev_stop, 0u, rows, cols, cols, (const _Float16*)(ws + lay.cz), scales,
                           (const _Float16*)(ws + lay.mhi), (const _Float16*)(ws + lay.mlo),
-                          (const float*)(ws + lay.mrow), (const float*)(ws + lay.tm), U, rowmap,
-                          n_dev);
+                          (const float*)(ws + lay.mpow), (const float*)(ws + lay.rdinv),
+                          (const float*)(ws + lay.tm), U, rowmap, n_dev);
   } else {
     hipLaunchKernelGGL((resid_kernel<G_SIZE>), dim3(tiles), dim3(512), 0, st, rows, cols, cols,
                        (const _Float16*)(ws + lay.cz), scales, (const _Float16*)(ws + lay.mhi),
-                       (const _Float16*)(ws + lay.mlo), (const float*)(ws + lay.mrow),
-                       (const float*)(ws + lay.tm), U, rowmap, n_dev);
+                       (const _Float16*)(ws + lay.mlo), (const float*)(ws + lay.mpow),
+                       (const float*)(ws + lay.rdinv), (const float*)(ws + lay.tm), U, rowmap,
+                       n_dev);
   }
   return hipGetLastError();
 }

@@ -5,8 +5,10 @@
 // hi = fp16(x 2^t), lo = fp16(x 2^t - hi), which carries 22 significant bits.
 // Products of such planes accumulate in fp32 on the matrix cores.
 //   H:  one scale for the whole matrix, chosen so max |H| 2^t lies in [2^13, 2^14).
-//   M = blockdiag(L_i^{-1}) H (the code update's coordinates, eq. (10)): one
-//       scale per row of M, same rule.
+//   M~ = blockdiag(L~_i^{-1}) H, L~_i = L_i with unit diagonal: the code update's
+//       coordinates, M = blockdiag(L_i^{-1}) H (eq. (10)), are its rows divided by
+//       L_i(n, n).  One power of two per row of M~, same rule; the products take
+//       the row factor 2^-t / L_i(n, n).
 //   W: one scale per row, same rule (for the layer's fixed W M^T and W_i L_i).
 // Small-integer operands (codes minus zero points, code changes) are exact in fp16.
 #include "jarq_internal.h"
@@ -41,7 +43,8 @@ __device__ __forceinline__ void split4(f32x4 x, int t, f16x4& hv, f16x4& lv) {
 }
 
 // A row of n x n fp32 values per work-group as two fp16 planes, scaled by 2^t
-// with t from amax[row] (per_row) or amax[0]; inv[row] or inv[0] = 2^-t.
+// with t from amax[row] (per_row) or amax[0]; inv[row] or inv[0] = 2^-t, and per
+// row scaled[row] = 2^-t rdinv[row].
 // Bound by memory traffic (4 bytes in, 4 out per value): 16-byte reads, 173 us
 // at 11008 x 11008 (5.6 TB/s); one value per thread and step took 355.
 template <bool kPerRow>
@@ -49,10 +52,15 @@ __global__ __launch_bounds__(256) void split_rows_kernel(const float* __restrict
                                                          const float* __restrict__ amax,
                                                          _Float16* __restrict__ hi,
                                                          _Float16* __restrict__ lo,
-                                                         float* __restrict__ inv) {
+                                                         float* __restrict__ inv,
+                                                         const float* __restrict__ rdinv,
+                                                         float* __restrict__ scaled) {
   const int r = blockIdx.x;
   const int t = pow2_exponent(amax[kPerRow ? r : 0]);
-  if (threadIdx.x == 0 && (kPerRow || r == 0)) inv[r] = ldexpf(1.f, -t);
+  if (threadIdx.x == 0 && (kPerRow || r == 0)) {
+    inv[r] = ldexpf(1.f, -t);
+    if (kPerRow) scaled[r] = ldexpf(rdinv[r], -t);
+  }
   const size_t row = (size_t)r * n;
   for (int c = threadIdx.x * 4; c < n; c += 1024) {
     f16x4 hv, lv;
@@ -67,15 +75,18 @@ __global__ __launch_bounds__(256) void split_rows_kernel(const float* __restrict
 hipError_t launch_split_h(hipStream_t st, int cols, const float* H, char* ws, const Layout& lay) {
   float* hs = (float*)(ws + lay.hscale);
   hipLaunchKernelGGL(split_rows_kernel<false>, dim3(cols), dim3(256), 0, st, H, cols, hs + 1,
-                     (_Float16*)(ws + lay.hhi), (_Float16*)(ws + lay.hlo), hs);
+                     (_Float16*)(ws + lay.hhi), (_Float16*)(ws + lay.hlo), hs,
+                     (const float*)nullptr, (float*)nullptr);
   return hipGetLastError();
 }
 
-// M = blockdiag(L_i^{-1}) H.  Row n of M (group i = n / g, local index nl) is
-// sum_{m <= nl} L_i^{-1}(nl, m) H(i g + m, :): the residual product with M in
-// place of H gives u = L_i^{-1} (H e)_i for every group at once, and its
-// blocks M(i-block, h-block) = L_i^{-1} H_ih carry a code change of group h
-// into u_i.  Formed in fp64 from the fp64 inverse, rounded to fp32 into a
+// M~ = blockdiag(L~_i^{-1}) H.  Row n of M~ (group i = n / g, local index nl) is
+// sum_{m <= nl} L~_i^{-1}(nl, m) H(i g + m, :): the residual product with M (M~ with
+// rows divided by L_i(n, n)) in place of H gives u = L_i^{-1} (H e)_i for every
+// group at once, and its blocks M(i-block, h-block) = L_i^{-1} H_ih carry a code
+// change of group h into u_i.  (The unit triangle keeps what is exact in H exact
+// in M~ where a group's columns are uncorrelated, and with it W H, which is
+// taken from W M~^T.)  Formed in fp64 from the fp64 inverse, rounded to fp32 into a
 // temporary, with each row's maximum (then split with one scale per row) and
 // the largest |H|.
 //
@@ -191,18 +202,16 @@ static hipError_t launch_split_m_t(hipStream_t st, int cols, const float* H, cha
   float* mtmp = (float*)(ws + lay.hhi);
   float* rowmax = (float*)(ws + lay.mmax);
   float* hmax = (float*)(ws + lay.hscale) + 1;
-  hipError_t e = launch_zero_bytes(st, rowmax, (size_t)cols * sizeof(float));
-  if (e == hipSuccess) e = launch_zero_bytes(st, hmax, sizeof(float));
-  if (e != hipSuccess) return e;
   const size_t lds = (size_t)G_SIZE * (G_SIZE + 2) * sizeof(double);
   static std::atomic<unsigned long long> lds_set{0};
-  e = allow_dynamic_lds((const void*)form_m_kernel<G_SIZE>, lds, lds_set);
+  const hipError_t e = allow_dynamic_lds((const void*)form_m_kernel<G_SIZE>, lds, lds_set);
   if (e != hipSuccess) return e;
   dim3 grid((cols + kFormCols - 1) / kFormCols, cols / G_SIZE);
   hipLaunchKernelGGL(form_m_kernel<G_SIZE>, grid, dim3(512), lds, st, H, cols,
                      (const double*)(ws + lay.lfac), mtmp, rowmax, hmax);
   hipLaunchKernelGGL(split_rows_kernel<true>, dim3(cols), dim3(256), 0, st, mtmp, cols, rowmax,
                      (_Float16*)(ws + lay.mhi), (_Float16*)(ws + lay.mlo),
+                     (float*)(ws + lay.mpow), (const float*)(ws + lay.rdinv),
                      (float*)(ws + lay.mrow));
   return hipGetLastError();
 }
@@ -284,34 +293,49 @@ hipError_t launch_split_w(hipStream_t st, int rows, int cols, const float* W, _F
 }
 
 // cz = q - z as fp16 (exact: codes and zero points are small integers), by
-// layer row; 16 codes per thread and step.
-__global__ void codes_cz_kernel(int rows, int cols, int g, const uint8_t* __restrict__ codes,
-                                const int32_t* __restrict__ zeros, _Float16* __restrict__ cz) {
-  const int G = cols / g;
+// layer row; 16 codes per thread and step.  With flags, also the checks of a
+// run's inputs: codes at most qmax, |z| at most 1024 (q - z and 1024 + z stay
+// exact in fp16).
+__global__ void codes_cz_kernel(int rows, int cols, int g, int qmax,
+                                const uint8_t* __restrict__ codes,
+                                const int32_t* __restrict__ zeros, _Float16* __restrict__ cz,
+                                Flags* __restrict__ flags) {
+  const int sh = __ffs(g) - 5;   // g / 16 pieces a group, a power of two
   const size_t chunks = (size_t)rows * cols / 16;
+  int bad_q = 0, bad_z = 0;
   for (size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x; e < chunks;
        e += (size_t)gridDim.x * blockDim.x) {
     const size_t off = e * 16;
-    const int r = (int)(off / cols), c = (int)(off % cols);
     const uint4 q = *(const uint4*)(codes + off);
-    const float z = (float)zeros[(size_t)r * G + c / g];
+    const int zi = zeros[e >> sh];
+    const float z = (float)zi;
+    bad_z += zi > 1024 || zi < -1024;
     const uint32_t w[4] = {q.x, q.y, q.z, q.w};
     f16x8 h0, h1;
 #pragma unroll
     for (int b = 0; b < 8; ++b) {
-      h0[b] = (_Float16)((float)((w[b >> 2] >> (8 * (b & 3))) & 0xffu) - z);
-      h1[b] = (_Float16)((float)((w[2 + (b >> 2)] >> (8 * (b & 3))) & 0xffu) - z);
+      const int q0 = (int)((w[b >> 2] >> (8 * (b & 3))) & 0xffu);
+      const int q1 = (int)((w[2 + (b >> 2)] >> (8 * (b & 3))) & 0xffu);
+      bad_q += (q0 > qmax) + (q1 > qmax);
+      h0[b] = (_Float16)((float)q0 - z);
+      h1[b] = (_Float16)((float)q1 - z);
     }
     *(f16x8*)(cz + off) = h0;
     *(f16x8*)(cz + off + 8) = h1;
   }
+  if (flags != nullptr) {
+    if (bad_q) atomicAdd(&flags->bad_codes, bad_q);
+    if (bad_z) atomicAdd(&flags->bad_zeros, bad_z);
+  }
 }
 
-hipError_t launch_codes_cz(hipStream_t st, int rows, int cols, int g, const uint8_t* codes,
-                           const int32_t* zeros, _Float16* cz) {
+hipError_t launch_codes_cz(hipStream_t st, int rows, int cols, int g, int bits,
+                           const uint8_t* codes, const int32_t* zeros, _Float16* cz,
+                           Flags* flags) {
   if (rows <= 0 || cols % 16 != 0) return rows <= 0 ? hipSuccess : hipErrorInvalidValue;
-  hipLaunchKernelGGL(codes_cz_kernel, dim3(2048), dim3(256), 0, st, rows, cols, g, codes, zeros,
-                     cz);
+  const size_t blocks = ((size_t)rows * cols / 16 + 255) / 256;
+  hipLaunchKernelGGL(codes_cz_kernel, dim3((unsigned)(blocks < 2048 ? blocks : 2048)), dim3(256), 0,
+                     st, rows, cols, g, (1 << bits) - 1, codes, zeros, cz, flags);
   return hipGetLastError();
 }
 
