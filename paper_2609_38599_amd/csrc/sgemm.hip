@@ -284,6 +284,76 @@ static hipError_t launch_split3_t(hipStream_t st, int M, int N, int K, int lda, 
   return hipGetLastError();
 }
 
+// The same product in 64 x 64 tiles, 2 x 2 wavefronts of 32 x 32, for layers
+// with too few 256-wide tiles; every element's products and their order are
+// those of split3_kernel, so the results are the same bits.
+__global__ __launch_bounds__(256, 1) void split3_small_kernel(
+    int M, int N, int K, const _Float16* __restrict__ Ah, const _Float16* __restrict__ Al,
+    const float* __restrict__ arow_inv, const _Float16* __restrict__ Bh,
+    const _Float16* __restrict__ Bl, const float* __restrict__ bcol_inv, float* __restrict__ C) {
+  constexpr int T = 64, PLANE = T * BK, STAGE = 4 * PLANE;   // halves
+  __shared__ __attribute__((aligned(1024))) _Float16 buf0[STAGE];
+  __shared__ __attribute__((aligned(1024))) _Float16 buf1[STAGE];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int wm = wave >> 1, wn = wave & 1;
+  const int lm = lane & 31, kh = lane >> 5;
+  int tm, tn;
+  if (!tile_of(blockIdx.x, (M + T - 1) / T, (N + T - 1) / T, tm, tn)) return;  // uniform
+  const int m0 = tm * T, n0 = tn * T;
+  // wave w fills the 1 KB piece w (16 rows) of each of the four planes
+  const int r = 16 * wave + (lane >> 2);
+  const unsigned chunk = (unsigned)(((lane & 3) ^ swz(r)) * 8);
+  const unsigned aoff = (unsigned)(m0 + r < M ? m0 + r : 0) * (unsigned)K + chunk;
+  const unsigned boff = (unsigned)(n0 + r < N ? n0 + r : 0) * (unsigned)K + chunk;
+  auto issue = [&](int k0, _Float16* stage) {
+    _Float16* dst = stage + wave * 512;
+    dma16(Ah + k0 + aoff, dst);
+    dma16(Al + k0 + aoff, dst + PLANE);
+    dma16(Bh + k0 + boff, dst + 2 * PLANE);
+    dma16(Bl + k0 + boff, dst + 3 * PLANE);
+  };
+  f32x16 acc = f32x16{};
+  auto compute = [&](const _Float16* st) __attribute__((always_inline)) {
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+      auto frag = [&](int plane, int row) __attribute__((always_inline)) {
+        return *(const f16x8*)(st + plane * PLANE + row * BK + (((2 * ks + kh) ^ swz(row)) << 3));
+      };
+      const f16x8 ah = frag(0, wm * 32 + lm), al = frag(1, wm * 32 + lm);
+      const f16x8 bh = frag(2, wn * 32 + lm), bl = frag(3, wn * 32 + lm);
+      acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah, bh, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah, bl, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(al, bh, acc, 0, 0, 0);
+    }
+  };
+  const int nk = K / BK;
+  issue(0, buf0);
+  __syncthreads();
+  for (int kt = 0; kt < nk; kt += 2) {
+    // a stage was last read before the barrier that precedes its loads; the
+    // barrier after a step waits for the next one's loads
+    if (kt + 1 < nk) issue((kt + 1) * BK, buf1);
+    compute(buf0);
+    __syncthreads();
+    if (kt + 1 < nk) {
+      if (kt + 2 < nk) issue((kt + 2) * BK, buf0);
+      compute(buf1);
+      __syncthreads();
+    }
+  }
+  const int col = n0 + wn * 32 + lm;
+  const float cs = bcol_inv[min(col, N - 1)];
+  float rsc[16];
+#pragma unroll
+  for (int v = 0; v < 16; ++v)
+    rsc[v] = arow_inv[min(m0 + wm * 32 + 8 * (v / 4) + 4 * kh + (v % 4), M - 1)];
+#pragma unroll
+  for (int v = 0; v < 16; ++v) {
+    const int row = m0 + wm * 32 + 8 * (v / 4) + 4 * kh + (v % 4);
+    if (row < M && col < N) C[(size_t)row * N + col] = acc[v] * (rsc[v] * cs);
+  }
+}
+
 // T~ = W M~^T for the layer, all rows (jarq_prepare): W's two fp16 planes
 // against M~'s, three products.
 hipError_t launch_wm_product(hipStream_t st, int rows, int cols, const char* ws,
@@ -293,6 +363,17 @@ hipError_t launch_wm_product(hipStream_t st, int rows, int cols, const char* ws,
   const _Float16* bh = (const _Float16*)(ws + lay.mhi);
   const _Float16* bl = (const _Float16*)(ws + lay.mlo);
   const float* bc = (const float*)(ws + lay.mpow);
+  // 64 x 64 tiles where there are few of 256 x 256 (a whole set-up, large tiles
+  // and small: 611 x 1312, 18 large tiles, 175 and 123 us; 300 x 11008, 86 of
+  // them, 1711 and 1565; 1500 x 4096, 96, 511 and 522)
+  const long long big = (long long)((rows + 255) / 256) * ((cols + 255) / 256);
+  if (big < 96) {
+    if (cols % BK != 0) return hipErrorInvalidValue;
+    const int tiles = ((rows + 63) / 64) * ((cols + 63) / 64);
+    hipLaunchKernelGGL(split3_small_kernel, dim3(tiles), dim3(256), 0, st, rows, cols, cols, whi,
+                       wlo, wrow_inv, bh, bl, bc, (float*)(ws + lay.tm));
+    return hipGetLastError();
+  }
   return launch_split3_t<256, 0>(st, rows, cols, cols, cols, cols, cols, whi, wlo, wrow_inv, bh,
                                  bl, bc, (float*)(ws + lay.tm), nullptr);
 }
@@ -310,8 +391,9 @@ hipError_t launch_wm_product(hipStream_t st, int rows, int cols, const char* ws,
 //
 // Tiling: 256 x 128 output tile per 512-thread work-group, 4 x 2 waves of
 // 64 x 64 (two 32 x 32 blocks each way: the accumulators and the group's
-// partial sums both fit next to the fragments at two waves per SIMD), K in
-// steps of 64 (32 when g = 32) straight from global memory into two LDS
+// partial sums both fit next to the fragments at two waves per SIMD), or 64 x 64
+// per 256 threads, 2 x 2 waves of 32 x 32 (the same products in the same order),
+// by the number of tiles (launch_resid); K in steps of 64 (32 when g = 32) straight from global memory into two LDS
 // stages by direct loads.  A stage row holds CPR 16-byte chunks; chunk c of
 // tile row r sits at position c ^ rswz(r).  A 16-byte read serves 16 lanes
 // (256 bytes, all 64 banks) per clock, and the lanes of a fragment read are
@@ -323,7 +405,6 @@ hipError_t launch_wm_product(hipStream_t st, int rows, int cols, const char* ws,
 // of cz, the scales and T are the layer's rows (gathered through the row
 // map); U is stored by position.
 namespace {
-constexpr int RBM = 256, RBN = 128;
 template <int CPR>
 __device__ __forceinline__ int rswz(int r) {
   if constexpr (CPR == 8) return (r >> 1) & 7;
@@ -331,8 +412,8 @@ __device__ __forceinline__ int rswz(int r) {
 }
 }  // namespace
 
-template <int G_SIZE>
-__global__ __launch_bounds__(512, 1) void resid_kernel(
+template <int G_SIZE, bool BIG>
+__global__ __launch_bounds__(BIG ? 512 : 256, 1) void resid_kernel(
     int M, int N, int K, const _Float16* __restrict__ Cz, const float* __restrict__ scales,
     const _Float16* __restrict__ Bh, const _Float16* __restrict__ Bl,
     const float* __restrict__ bcol_inv, const float* __restrict__ rdinv,
@@ -340,13 +421,17 @@ __global__ __launch_bounds__(512, 1) void resid_kernel(
     const int* __restrict__ m_dev) {
   if (m_dev != nullptr) M = *m_dev;
   constexpr int g = G_SIZE;
+  constexpr int RBM = BIG ? 256 : 64, RBN = BIG ? 128 : 64;
+  constexpr int NW = BIG ? 8 : 4;                        // wavefronts, two along the columns
+  constexpr int AB = BIG ? 2 : 1;                        // 32 x 32 blocks per wavefront each way
+  constexpr int WT = 32 * AB;                            // wavefront tile
   constexpr int RBK = g >= 64 ? 64 : 32;                 // k per stage
   constexpr int KQ = RBK / 16;                           // k-slices per stage
   constexpr int CPR = RBK / 8;                           // 16-byte chunks per stage row
   constexpr int RPP = 64 / CPR;                          // rows per 1 KB piece
   constexpr int SPG = g / RBK;                           // stages per group
   constexpr int A_PLANE = RBM * RBK, B_PLANE = RBN * RBK;  // halves
-  constexpr int APW = RBM / RPP / 8, BPW = RBN / RPP / 8;  // pieces per wave per plane
+  constexpr int APW = RBM / RPP / NW, BPW = RBN / RPP / NW;  // pieces per wave per plane
   constexpr int STAGE = A_PLANE + 2 * B_PLANE;
   __shared__ __attribute__((aligned(1024))) _Float16 buf0[STAGE];
   __shared__ __attribute__((aligned(1024))) _Float16 buf1[STAGE];
@@ -368,17 +453,17 @@ __global__ __launch_bounds__(512, 1) void resid_kernel(
   __syncthreads();
 
   // Direct loads, 16 bytes per lane, one 1 KB piece (RPP rows) per
-  // instruction: wave w fills pieces w, w + 8, ... of each plane; lane L holds
+  // instruction: wave w fills pieces w, w + NW, ... of each plane; lane L holds
   // row RPP j + L / CPR at position L % CPR, i.e. chunk (L % CPR) ^ rswz(row).
   unsigned aoff[APW], boff[BPW];
 #pragma unroll
   for (int i = 0; i < APW; ++i) {
-    const int r = RPP * (wave + 8 * i) + lane / CPR;
+    const int r = RPP * (wave + NW * i) + lane / CPR;
     aoff[i] = (unsigned)lr_s[r] * (unsigned)K + (unsigned)(((lane % CPR) ^ rswz<CPR>(r)) * 8);
   }
 #pragma unroll
   for (int i = 0; i < BPW; ++i) {
-    const int r = RPP * (wave + 8 * i) + lane / CPR;
+    const int r = RPP * (wave + NW * i) + lane / CPR;
     const int gn = n0 + r;
     boff[i] = (unsigned)(gn < N ? gn : 0) * (unsigned)K + (unsigned)(((lane % CPR) ^ rswz<CPR>(r)) * 8);
   }
@@ -387,13 +472,13 @@ __global__ __launch_bounds__(512, 1) void resid_kernel(
   constexpr int NDMA = APW + 2 * BPW;
   auto issue_one = [&](int j, int k0, _Float16* stage) {
     if (j < APW) {
-      dma16(Cz + k0 + aoff[j], stage + (wave + 8 * j) * 512);
+      dma16(Cz + k0 + aoff[j], stage + (wave + NW * j) * 512);
     } else {
       const int i = (j - APW) >> 1;
       if (((j - APW) & 1) == 0)
-        dma16(Bh + k0 + boff[i], stage + A_PLANE + (wave + 8 * i) * 512);
+        dma16(Bh + k0 + boff[i], stage + A_PLANE + (wave + NW * i) * 512);
       else
-        dma16(Bl + k0 + boff[i], stage + A_PLANE + B_PLANE + (wave + 8 * i) * 512);
+        dma16(Bl + k0 + boff[i], stage + A_PLANE + B_PLANE + (wave + NW * i) * 512);
     }
   };
   auto issue = [&](int k0, _Float16* stage) {
@@ -405,11 +490,11 @@ __global__ __launch_bounds__(512, 1) void resid_kernel(
     if (tid < RBM) sc_s[i & 1][tid] = scales[(size_t)lr_s[tid] * G + i];
   };
 
-  f32x16 acc[2][2], seg[2][2];
+  f32x16 acc[AB][AB], seg[AB][AB];
 #pragma unroll
-  for (int a = 0; a < 2; ++a)
+  for (int a = 0; a < AB; ++a)
 #pragma unroll
-    for (int b = 0; b < 2; ++b) acc[a][b] = f32x16{};
+    for (int b = 0; b < AB; ++b) acc[a][b] = f32x16{};
 
   auto lds_rd = [&](const _Float16* plane, int r, int q) {
     const int c = 2 * q + kh;  // k-slice q: chunks 2 q (lanes 0-31) and 2 q + 1
@@ -420,19 +505,19 @@ __global__ __launch_bounds__(512, 1) void resid_kernel(
     return v;
   };
   // One stage (KQ k-slices of 16) on `base`; `first`: the stage opens a group
-  // (its products start the partial sums from zero).  The six reads of slice
+  // (its products start the partial sums from zero).  The 3 AB reads of slice
   // q + 1 are issued before the wait for slice q (LDS returns in order), and
   // the next stage's direct loads (into `stn` at k0n; none if k0n < 0) are
   // spread over the slices.
   auto compute = [&](const _Float16* base, bool first, int k0n, _Float16* stn) {
-    f16x8 af[2][2], bh[2][2], bl[2][2];  // [slot][block]
+    f16x8 af[2][AB], bh[2][AB], bl[2][AB];  // [slot][block]
     auto rd = [&](int q, int sl) {
 #pragma unroll
-      for (int a = 0; a < 2; ++a) af[sl][a] = lds_rd(base, wm * 64 + a * 32 + lm, q);
+      for (int a = 0; a < AB; ++a) af[sl][a] = lds_rd(base, wm * WT + a * 32 + lm, q);
 #pragma unroll
-      for (int b = 0; b < 2; ++b) {
-        bh[sl][b] = lds_rd(base + A_PLANE, wn * 64 + b * 32 + lm, q);
-        bl[sl][b] = lds_rd(base + A_PLANE + B_PLANE, wn * 64 + b * 32 + lm, q);
+      for (int b = 0; b < AB; ++b) {
+        bh[sl][b] = lds_rd(base + A_PLANE, wn * WT + b * 32 + lm, q);
+        bl[sl][b] = lds_rd(base + A_PLANE + B_PLANE, wn * WT + b * 32 + lm, q);
       }
     };
     rd(0, 0);
@@ -443,30 +528,30 @@ __global__ __launch_bounds__(512, 1) void resid_kernel(
 #pragma unroll
         for (int j = q * NDMA / KQ; j < (q + 1) * NDMA / KQ; ++j) issue_one(j, k0n, stn);
       }
-      if (q + 1 < KQ) {
-        rd(q + 1, sl ^ 1);
-        if (sl == 0)
-          asm volatile("s_waitcnt lgkmcnt(6)"
-                       : "+v"(af[0][0]), "+v"(af[0][1]), "+v"(bh[0][0]), "+v"(bh[0][1]),
-                         "+v"(bl[0][0]), "+v"(bl[0][1]));
-        else
-          asm volatile("s_waitcnt lgkmcnt(6)"
-                       : "+v"(af[1][0]), "+v"(af[1][1]), "+v"(bh[1][0]), "+v"(bh[1][1]),
-                         "+v"(bl[1][0]), "+v"(bl[1][1]));
+      const bool more = q + 1 < KQ;
+      if (more) rd(q + 1, sl ^ 1);
+      // wait for slice q's reads (all but the ones just issued); the operands
+      // are the fragments that the wait guards
+      if constexpr (AB == 2) {
+#define JARQ_WAIT_OPS(x) \
+  "+v"(af[x][0]), "+v"(af[x][1]), "+v"(bh[x][0]), "+v"(bh[x][1]), "+v"(bl[x][0]), "+v"(bl[x][1])
+        if (more && sl == 0) asm volatile("s_waitcnt lgkmcnt(6)" : JARQ_WAIT_OPS(0));
+        if (more && sl == 1) asm volatile("s_waitcnt lgkmcnt(6)" : JARQ_WAIT_OPS(1));
+        if (!more && sl == 0) asm volatile("s_waitcnt lgkmcnt(0)" : JARQ_WAIT_OPS(0));
+        if (!more && sl == 1) asm volatile("s_waitcnt lgkmcnt(0)" : JARQ_WAIT_OPS(1));
+#undef JARQ_WAIT_OPS
       } else {
-        if (sl == 0)
-          asm volatile("s_waitcnt lgkmcnt(0)"
-                       : "+v"(af[0][0]), "+v"(af[0][1]), "+v"(bh[0][0]), "+v"(bh[0][1]),
-                         "+v"(bl[0][0]), "+v"(bl[0][1]));
-        else
-          asm volatile("s_waitcnt lgkmcnt(0)"
-                       : "+v"(af[1][0]), "+v"(af[1][1]), "+v"(bh[1][0]), "+v"(bh[1][1]),
-                         "+v"(bl[1][0]), "+v"(bl[1][1]));
+#define JARQ_WAIT_OPS(x) "+v"(af[x][0]), "+v"(bh[x][0]), "+v"(bl[x][0])
+        if (more && sl == 0) asm volatile("s_waitcnt lgkmcnt(3)" : JARQ_WAIT_OPS(0));
+        if (more && sl == 1) asm volatile("s_waitcnt lgkmcnt(3)" : JARQ_WAIT_OPS(1));
+        if (!more && sl == 0) asm volatile("s_waitcnt lgkmcnt(0)" : JARQ_WAIT_OPS(0));
+        if (!more && sl == 1) asm volatile("s_waitcnt lgkmcnt(0)" : JARQ_WAIT_OPS(1));
+#undef JARQ_WAIT_OPS
       }
 #pragma unroll
-      for (int a = 0; a < 2; ++a)
+      for (int a = 0; a < AB; ++a)
 #pragma unroll
-        for (int b = 0; b < 2; ++b) {
+        for (int b = 0; b < AB; ++b) {
           const f32x16 c0 = (first && q == 0) ? f32x16{} : seg[a][b];
           seg[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(af[sl][a], bh[sl][b], c0, 0, 0, 0);
           seg[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(af[sl][a], bl[sl][b], seg[a][b], 0, 0, 0);
@@ -477,12 +562,12 @@ __global__ __launch_bounds__(512, 1) void resid_kernel(
   // row 8 (v / 4) + 4 (lane / 32) + v % 4
   auto fold = [&](int i) {
 #pragma unroll
-    for (int a = 0; a < 2; ++a) {
+    for (int a = 0; a < AB; ++a) {
 #pragma unroll
       for (int v4 = 0; v4 < 4; ++v4) {
-        const f32x4 s4 = *(const f32x4*)&sc_s[i & 1][wm * 64 + a * 32 + 8 * v4 + 4 * kh];
+        const f32x4 s4 = *(const f32x4*)&sc_s[i & 1][wm * WT + a * 32 + 8 * v4 + 4 * kh];
 #pragma unroll
-        for (int b = 0; b < 2; ++b)
+        for (int b = 0; b < AB; ++b)
 #pragma unroll
           for (int u = 0; u < 4; ++u)
             acc[a][b][4 * v4 + u] = fmaf(seg[a][b][4 * v4 + u], s4[u], acc[a][b][4 * v4 + u]);
@@ -515,11 +600,11 @@ __global__ __launch_bounds__(512, 1) void resid_kernel(
   // Epilogue: U = (T~ - acc 2^-t_n) / L(n, n).  Accumulator element v of lane l in a
   // 32 x 32 block: (row 8 (v / 4) + 4 (l / 32) + v % 4, column l % 32).
 #pragma unroll
-  for (int a = 0; a < 2; ++a) {
-    const int tb = wm * 64 + a * 32 + 4 * kh;  // tile row of element v: tb + 8 (v / 4) + v % 4
+  for (int a = 0; a < AB; ++a) {
+    const int tb = wm * WT + a * 32 + 4 * kh;  // tile row of element v: tb + 8 (v / 4) + v % 4
 #pragma unroll
-    for (int b = 0; b < 2; ++b) {
-      const int col = n0 + wn * 64 + b * 32 + lm;
+    for (int b = 0; b < AB; ++b) {
+      const int col = n0 + wn * WT + b * 32 + lm;
       const int colc = min(col, N - 1);
       const float cs = bcol_inv[colc], ds = rdinv[colc];
       float tv[16];
@@ -535,21 +620,22 @@ __global__ __launch_bounds__(512, 1) void resid_kernel(
   }
 }
 
-template <int G_SIZE>
+template <int G_SIZE, bool BIG>
 static hipError_t launch_resid_t(hipStream_t st, int rows, int cols, const char* ws,
                                  const Layout& lay, const float* scales, float* U,
                                  const int32_t* rowmap, const int* n_dev, hipEvent_t ev_start,
                                  hipEvent_t ev_stop) {
-  const int tiles = ((rows + RBM - 1) / RBM) * ((cols + RBN - 1) / RBN);
+  constexpr int RBM = BIG ? 256 : 64, RBN = BIG ? 128 : 64;
+  const dim3 grid(((rows + RBM - 1) / RBM) * ((cols + RBN - 1) / RBN)), block(BIG ? 512 : 256);
   if (ev_start != nullptr || ev_stop != nullptr) {
     // timed: the events take the dispatch's own timestamps
-    hipExtLaunchKernelGGL((resid_kernel<G_SIZE>), dim3(tiles), dim3(512), 0, st, ev_start,
-                          ev_stop, 0u, rows, cols, cols, (const _Float16*)(ws + lay.cz), scales,
+    hipExtLaunchKernelGGL((resid_kernel<G_SIZE, BIG>), grid, block, 0, st, ev_start, ev_stop, 0u,
+                          rows, cols, cols, (const _Float16*)(ws + lay.cz), scales,
                           (const _Float16*)(ws + lay.mhi), (const _Float16*)(ws + lay.mlo),
                           (const float*)(ws + lay.mpow), (const float*)(ws + lay.rdinv),
                           (const float*)(ws + lay.tm), U, rowmap, n_dev);
   } else {
-    hipLaunchKernelGGL((resid_kernel<G_SIZE>), dim3(tiles), dim3(512), 0, st, rows, cols, cols,
+    hipLaunchKernelGGL((resid_kernel<G_SIZE, BIG>), grid, block, 0, st, rows, cols, cols,
                        (const _Float16*)(ws + lay.cz), scales, (const _Float16*)(ws + lay.mhi),
                        (const _Float16*)(ws + lay.mlo), (const float*)(ws + lay.mpow),
                        (const float*)(ws + lay.rdinv), (const float*)(ws + lay.tm), U, rowmap,
@@ -568,16 +654,22 @@ hipError_t launch_resid(hipStream_t st, int rows, int cols, int g, const char* w
     return e;
   }
   if (cols % BK != 0) return hipErrorInvalidValue;
+  // 64 x 64 tiles where 256 x 128 ones would leave half of the compute units
+  // without work (a whole code update, large tiles and small: 512 x 4096, 64
+  // large tiles, 432 and 383 us; 1024 x 4096, 128 of them, 437 and 441; 2048 x
+  // 4096 492 and 556)
+  const long long big = (long long)((rows + 255) / 256) * ((cols + 127) / 128);
+#define JARQ_RESID(g)                                                                            \
+  case g:                                                                                        \
+    return (big >= 128 ? launch_resid_t<g, true> : launch_resid_t<g, false>)(                    \
+        st, rows, cols, ws, lay, scales, U, rowmap, n_dev, ev_start, ev_stop)
   switch (g) {
-    case 32:
-      return launch_resid_t<32>(st, rows, cols, ws, lay, scales, U, rowmap, n_dev, ev_start, ev_stop);
-    case 64:
-      return launch_resid_t<64>(st, rows, cols, ws, lay, scales, U, rowmap, n_dev, ev_start, ev_stop);
-    case 128:
-      return launch_resid_t<128>(st, rows, cols, ws, lay, scales, U, rowmap, n_dev, ev_start,
-                                 ev_stop);
+    JARQ_RESID(32);
+    JARQ_RESID(64);
+    JARQ_RESID(128);
     default: return hipErrorInvalidValue;
   }
+#undef JARQ_RESID
 }
 
 }  // namespace jarq

@@ -252,3 +252,21 @@ def test_act_order_sizes(d):
     H.diagonal().copy_(to_dev(diag))
     perm = jb.act_order(H).cpu().numpy()
     assert np.array_equal(perm, np.argsort(-diag, kind="stable"))
+
+
+# both tile sizes of the residual product and of W M~^T, at and beside the lines
+# between them, the same rows in a layer of either kind: the same bits
+@pytest.mark.parametrize("few,many,cols,g", [(63, 4100, 1024, 64), (65, 4097, 1056, 32),
+                                             (300, 8200, 640, 128), (1000, 3841, 1536, 128)])
+def test_small_and_large_tiles_agree(few, many, cols, g):
+    W, H, q, s, z = random_layer(many, cols, g, 3, seed=few)
+    states = []
+    for n in (few, many):
+        gk = GpuLayer(W[:n], H, q[:n], s[:n], z[:n], g, 3)
+        gk.scale_step()
+        gk.code_step(trace=False)
+        states.append(gk.state())
+    (qa, sa), (qb, sb) = states
+    assert np.array_equal(sa, sb[:few]) and np.array_equal(qa, qb[:few])
+    s_ref, _ = jarq.scale_step(W[:few], H, q[:few], z[:few], g)
+    check_scales(sa, s_ref, f" few {few}")
