@@ -9,7 +9,8 @@
 // fp16, then T reduced against c_a for every row (block_entries below).
 //
 // Full build: a work-group takes a tile of 128 rows and a pair of row-groups
-// {p, G-1-p} (so every work-group walks G+1 blocks).
+// {p, G-1-p} (a walk of G+1 blocks); with few tiles and pairs the walk is cut
+// into parts, a work-group each (walk_parts).
 //
 // Incremental build: entry (a, h) depends on the codes of groups a and h
 // only, so after a code update only the entries of groups whose codes changed
@@ -208,7 +209,17 @@ __device__ __forceinline__ float entry_value(const double* red, int t, float hin
   return (float)(s * (double)hinv);
 }
 
-// ---- full build: 128 positions x a pair of a-groups per work-group ----
+// ---- full build: 128 positions x part z of the walk of a pair of a-groups ----
+// A block takes about 4 us from one to the next where a work-group has a CU to
+// itself (its H loads, three barriers), so a short grid lasts as long as its
+// walk.  Parts of at least two blocks (each stages the codes of its a-group
+// again) up to the 512 work-groups that run at once.  480 x 2048, g = 128:
+// 14 us (one part: 72).
+static int walk_parts(int tiles, int G) {
+  const int wgs = tiles * ((G + 1) / 2);
+  const int parts = 512 / (wgs < 512 ? wgs : 512), most = (G + 2) / 2;
+  return parts < most ? parts : most;
+}
 template <int G_SIZE>
 __global__ __launch_bounds__(256, 2) void gram_kernel(int rows, int cols,
                                                       const _Float16* __restrict__ Hh,
@@ -226,7 +237,7 @@ __global__ __launch_bounds__(256, 2) void gram_kernel(int rows, int cols,
   const int n = n_dev != nullptr ? *n_dev : rows;
   // every work-group takes the same branch (same counts, same n)
   const bool lists = gram_use_lists(ctl, gpre, G, n);
-  if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0 && ctl != nullptr)
+  if (blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0 && threadIdx.x == 0 && ctl != nullptr)
     ctl->listed = lists ? 1 : 0;
   if (lists) return;
   const int r0 = blockIdx.x * RT;
@@ -245,6 +256,9 @@ __global__ __launch_bounds__(256, 2) void gram_kernel(int rows, int cols,
   CodeStage<G_SIZE> st;
   f16x8 hf[2][S::KS];
   const int p = blockIdx.y;
+  // this part's blocks of the walk: G - p of a-group p, then p + 1 of G - 1 - p
+  const int per = (G + (int)gridDim.z) / (int)gridDim.z;   // ceil((G + 1) / parts)
+  const int w0 = per * (int)blockIdx.z, w1 = w0 + per;
   // Thread tid < RT owns tile row tid: it keeps its entries (ga, h) for up to
   // 32 consecutive h in registers and stores them as one contiguous run.
   float* grow_out = gram + (size_t)layer_row(tid < RT ? tid : 0) * G * G;
@@ -254,26 +268,29 @@ __global__ __launch_bounds__(256, 2) void gram_kernel(int rows, int cols,
   for (int side = 0; side < 2; ++side) {
     const int ga = side == 0 ? p : G - 1 - p;
     if (side == 1 && ga == p) break;
+    const int off = side == 0 ? ga : ga - (G - p);   // block h of the side is the walk's h - off
+    const int h0 = max(ga, w0 + off), h1 = min(G, w1 + off);
+    if (h0 >= h1) continue;   // uniform
     lds_barrier();
     st.fetch(codes, zeros, lrow, ga, cols, G, tpart);
     st.store(ca_s, trow, tpart);
-    st.fetch(codes, zeros, lrow, ga, cols, G, tpart);  // block h = ga comes first
-    for (int h = ga; h < G; ++h) {
+    st.fetch(codes, zeros, lrow, h0, cols, G, tpart);
+    for (int h = h0; h < h1; ++h) {
       lds_barrier();  // previous block's reads of ch_s are done
       st.store(ch_s, trow, tpart);
       // H fragments of this block (their latency is covered by the other
       // work-group on the CU), codes of the next one
       fetch_h<G_SIZE>(hf, Hh, Hl, ga, h, cols, lane, wave);
-      if (h + 1 < G) st.fetch(codes, zeros, lrow, h + 1, cols, G, tpart);
+      if (h + 1 < h1) st.fetch(codes, zeros, lrow, h + 1, cols, G, tpart);
       lds_barrier();
       block_entries<G_SIZE>(ca_s, ch_s, hf, red, lane, wave);
       lds_barrier();
       if (tid < RT) {
         const float val = entry_value<G_SIZE>(red, tid, hinv);
-        const int j = (h - ga) & 31;
+        const int j = (h - h0) & 31;
 #pragma unroll
         for (int q = 0; q < 32; ++q) outv[q] = q == j ? val : outv[q];
-        if ((j == 31 || h == G - 1) && r0 + tid < n) {
+        if ((j == 31 || h == h1 - 1) && r0 + tid < n) {
           float* dst = grow_out + (size_t)ga * G + (h - j);
 #pragma unroll
           for (int q = 0; q < 32; ++q)
@@ -463,8 +480,9 @@ static hipError_t launch_gram_t(hipStream_t st, int rows, int cols, const char* 
   if (e == hipSuccess && incremental)
     e = allow_dynamic_lds((const void*)gram_listed_kernel<g>, lds, listed_set);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((gram_kernel<g>), dim3((rows + RT - 1) / RT, (G + 1) / 2), dim3(256), lds,
-                     st, rows, cols, (const _Float16*)(ws + lay.hhi),
+  const int tiles = (rows + RT - 1) / RT;
+  hipLaunchKernelGGL((gram_kernel<g>), dim3(tiles, (G + 1) / 2, walk_parts(tiles, G)), dim3(256),
+                     lds, st, rows, cols, (const _Float16*)(ws + lay.hhi),
                      (const _Float16*)(ws + lay.hlo), (const float*)(ws + lay.hscale), codes,
                      zeros, gram, rowmap, n_dev, ctl, gpre);
   if (incremental) {

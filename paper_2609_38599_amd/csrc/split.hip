@@ -91,7 +91,7 @@ hipError_t launch_split_h(hipStream_t st, int cols, const float* H, char* ws, co
 // the largest |H|.
 //
 // On the fp64 matrix cores (v_mfma_f64_16x16x4_f64, 64 cycles each): a
-// work-group stages L_i^{-1} in LDS once and takes kFormCols columns, a
+// work-group stages L_i^{-1} in LDS once and takes `span` columns, a
 // wavefront 16 columns at a time with all g rows of M in registers; the
 // 16 x 16 blocks above the diagonal of L_i^{-1} are skipped.  One LDS read per
 // matrix instruction (row stride g + 2 doubles: the 16 rows and the k-pairs
@@ -99,14 +99,22 @@ hipError_t launch_split_h(hipStream_t st, int cols, const float* H, char* ws, co
 // 59 us at 4096 columns and 498 us at 11008 (g = 128; 35 TFLOP/s of the 70 the
 // fp64 matrix cores sustain, counting the blocks computed), against 875 and
 // 6584 us for one column per thread with fp64 vector FMAs.
-constexpr int kFormCols = 512;
+//
+// span: 512, less (a multiple of 128) where that leaves compute units without
+// a work-group (2048 columns, g = 128: 35 us; always 512: 55).
+static int form_span(int cols, int g) {
+  int span = 512;
+  while (span > 128 && (long long)((cols + span - 1) / span) * (cols / g) < 256) span /= 2;
+  return span;
+}
 
 template <int G_SIZE>
 __global__ __launch_bounds__(512) void form_m_kernel(const float* __restrict__ H, int cols,
                                                      const double* __restrict__ linv,
                                                      float* __restrict__ mtmp,
                                                      float* __restrict__ rowmax,
-                                                     float* __restrict__ hmax) {
+                                                     float* __restrict__ hmax,
+                                                     int span) {
   constexpr int g = G_SIZE;
   constexpr int LD = g + 2;
   constexpr int NB = g / 16;
@@ -122,7 +130,7 @@ __global__ __launch_bounds__(512) void form_m_kernel(const float* __restrict__ H
     *(f64x2*)(li + r * LD + c) = *(const f64x2*)(Li + r * g + c);
   }
   __syncthreads();
-  const int cend = min(cols, (int)(blockIdx.x + 1) * kFormCols);
+  const int cend = min(cols, (int)(blockIdx.x + 1) * span);
   // B(k, j) of k-slice ks: H(i g + 4 ks + lane / 16, c + lane % 16)
   // (wave-uniform bases, 32-bit offsets: g rows of at most 16384 columns)
   const float* Hi = H + (size_t)i * g * cols;
@@ -137,7 +145,7 @@ __global__ __launch_bounds__(512) void form_m_kernel(const float* __restrict__ H
   for (int b = 0; b < NB; ++b)
 #pragma unroll
     for (int v = 0; v < 4; ++v) mx[b][v] = 0.f;
-  int c = blockIdx.x * kFormCols + 16 * wave;   // cols is a multiple of 16
+  int c = blockIdx.x * span + 16 * wave;   // cols is a multiple of 16
   if (c < cend) {
 #pragma unroll
     for (int ks = 0; ks < 4 * NB; ++ks) h[ks] = fetch(c, ks);
@@ -206,9 +214,10 @@ static hipError_t launch_split_m_t(hipStream_t st, int cols, const float* H, cha
   static std::atomic<unsigned long long> lds_set{0};
   const hipError_t e = allow_dynamic_lds((const void*)form_m_kernel<G_SIZE>, lds, lds_set);
   if (e != hipSuccess) return e;
-  dim3 grid((cols + kFormCols - 1) / kFormCols, cols / G_SIZE);
+  const int span = form_span(cols, G_SIZE);
+  const dim3 grid((cols + span - 1) / span, cols / G_SIZE);
   hipLaunchKernelGGL(form_m_kernel<G_SIZE>, grid, dim3(512), lds, st, H, cols,
-                     (const double*)(ws + lay.lfac), mtmp, rowmax, hmax);
+                     (const double*)(ws + lay.lfac), mtmp, rowmax, hmax, span);
   hipLaunchKernelGGL(split_rows_kernel<true>, dim3(cols), dim3(256), 0, st, mtmp, cols, rowmax,
                      (_Float16*)(ws + lay.mhi), (_Float16*)(ws + lay.mlo),
                      (float*)(ws + lay.mpow), (const float*)(ws + lay.rdinv),

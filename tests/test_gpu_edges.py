@@ -270,3 +270,21 @@ def test_small_and_large_tiles_agree(few, many, cols, g):
     assert np.array_equal(sa, sb[:few]) and np.array_equal(qa, qb[:few])
     s_ref, _ = jarq.scale_step(W[:few], H, q[:few], z[:few], g)
     check_scales(sa, s_ref, f" few {few}")
+
+
+# the walk of a pair of groups in one part and in many, odd and even numbers of
+# groups, and the span of M~'s formation: the same bits as in a layer of many rows
+@pytest.mark.parametrize("G", [1, 2, 3, 4, 5, 16, 31, 33, 64, 67])
+def test_gram_walk_parts_agree(G):
+    g = 32
+    many = 128 * (512 // ((G + 1) // 2)) + 1 if G > 8 else 4500
+    W, H, q, s, z = random_layer(many, G * g, g, 3, seed=G)
+    out = []
+    for n in (130, many):
+        gk = GpuLayer(W[:n], H, q[:n], s[:n], z[:n], g, 3)
+        gk.ws.fill_(0xff)
+        jq.prepare(gk.p, gk.W, gk.H, gk.ws)
+        gk.scale_step()
+        out.append(gk.state()[1])
+    assert np.array_equal(out[0], out[1][:130])
+    check_scales(out[0], jarq.scale_step(W[:130], H, q[:130], z[:130], g)[0], f" G={G}")
