@@ -486,6 +486,11 @@ __global__ __launch_bounds__(512, 1) void babai_kernel(
     // loads in flight) and the R~ buffer is known at compile time (i0 is
     // even: group i0 + p + 1 goes to rc1_s for even p).
     static_assert(PG % 2 == 0, "panels hold an even number of groups");
+    // Fragment buffers: a block of 32-wide groups is applied in much less time
+    // than its loads take, so two more fly (a code update of 4096 x 2048, g =
+    // 32: 421 us with loads under a branch, 377 without, 370 with a third
+    // buffer; g = 64: 277, 279, 278, g = 128: 261, 263, 264).
+    constexpr int TD = g == 32 ? 3 : 2;
     stage_rcol(i0, rc0_s);
     if (prep_live) {
       u_from_p(i0, ua1);
@@ -500,29 +505,36 @@ __global__ __launch_bounds__(512, 1) void babai_kernel(
     auto prep_at = [&](auto pc) {
       constexpr int p = decltype(pc)::value;
       const int i = i0 + p;
-      TFrag fa, fb;
+      TFrag f[TD];
       // u of group i + 1 is in ua[p % 2] (loaded one position earlier); the
       // load of group i + 2's goes out now
       f32x4 (&uc)[BPW] = (p % 2 == 0) ? ua0 : ua1;
       f32x4 (&un)[BPW] = (p % 2 == 0) ? ua1 : ua0;
       if (prep_live) {
         if (i + 2 < i1) u_from_p(i + 2, un);
-        // block h = i0 + k sits in fa for even k, fb for odd k; the next
-        // block loads while the current one is applied, and the last one,
-        // M(i + 1, i), stays in flight across the barrier.  A block of an
-        // earlier group that no row of the tile accepted (decided before this
-        // position) is neither loaded nor applied.
-        auto wanted = [&](int k) { return k == p || tacc_s[k] != 0; };
-        if (wanted(0)) load_t(i + 1, i0, fa);
-        Unroll<0, p>::run([&](auto kc) {
+        // block h = i0 + k sits in f[k % TD]; the next TD - 1 blocks load while
+        // one is applied, and the last one, M(i + 1, i), stays in flight
+        // across the barrier.  A block of an earlier group that no row of the
+        // tile accepted (decided before this position) is not applied; short
+        // groups load M(i + 1, i) in its place (a load that may not happen
+        // leaves the compiler to wait for every one), long ones nothing.
+        auto fetch = [&](int k, TFrag& fr) __attribute__((always_inline)) {
+          const bool wanted = k == p || tacc_s[k] != 0;
+          if constexpr (g == 32)
+            load_t(i + 1, wanted ? i0 + k : i, fr);
+          else if (wanted)
+            load_t(i + 1, i0 + k, fr);
+        };
+        Unroll<0, (p + 1 < TD - 1 ? p + 1 : TD - 1)>::run([&](auto kc) {
           constexpr int k = decltype(kc)::value;
-          if constexpr (k % 2 == 0) {
-            if (wanted(k + 1)) load_t(i + 1, i0 + k + 1, fb);
-            apply_t(i0 + k, fa, true, uc);
-          } else {
-            if (wanted(k + 1)) load_t(i + 1, i0 + k + 1, fa);
-            apply_t(i0 + k, fb, true, uc);
+          fetch(k, f[k % TD]);
+        });
+        Unroll<0, p>::run([&](auto kc) {
+          constexpr int k = decltype(kc)::value, nx = k + TD - 1;
+          if constexpr (nx <= p) {
+            fetch(nx, f[nx % TD]);
           }
+          apply_t(i0 + k, f[k % TD], true, uc);
         });
       }
       // R~ (i + 1) last: LDS reads issued after a direct load to LDS wait for
@@ -534,10 +546,7 @@ __global__ __launch_bounds__(512, 1) void babai_kernel(
         stage_rcol(i + 1, rc0_s);
       lds_barrier();  // group i decided: its changes are in dqp_s, tacc_s
       if (prep_live) {
-        if constexpr (p % 2 == 0)
-          apply_t(i, fa, true, uc);
-        else
-          apply_t(i, fb, true, uc);
+        apply_t(i, f[p % TD], true, uc);
         write_u(uc);
       }
       // The direct loads of R~ (i + 1) are complete once this wave's vector
