@@ -114,9 +114,12 @@ size_t jarq_workspace_bytes(const jarq_params* p);
 
 /*
  * Per-layer set-up (eq. (9) and the right-hand-side shortcut of App. G.8):
- * factor every diagonal block H_ii = R_i^T R_i (fp64 Cholesky), store R_i,
- * R_i^{-1} and 1/diag(R_i) in fp32, and compute WH = W H in fp32.  Synchronises
- * `stream` and returns JARQ_ENOT_SPD if a block is not positive definite.
+ * factor every diagonal block H_ii = R_i^T R_i (fp64 Cholesky), store R_i and
+ * 1/diag(R_i) in fp32, form M = blockdiag(R_i^{-T}) H (fp64, rounded to fp32, kept
+ * as two fp16 planes with a power of two per row) and the layer's constant
+ * products, among them WH = W H to fp32 accuracy (all 24 bits of W and H,
+ * sums in fp32).  Synchronises `stream` and returns JARQ_ENOT_SPD if a block is
+ * not positive definite.
  * W [rows][cols] fp32; H [cols][cols] fp32, symmetric, full storage.
  */
 jarq_status jarq_prepare(const jarq_params* p, const float* W, const float* H,

@@ -42,7 +42,6 @@ Layout make_layout(int rows, int cols, int g) {
   L.mhi = take(C * C * 2);
   L.mlo = take(C * C * 2);
   L.mrow = take(C * sizeof(float));
-  L.mpow = take(C * sizeof(float));
   L.mmax = take(C * sizeof(float));
   L.wrow = take(R * sizeof(float));
   L.wh = take(R * C * sizeof(float));
@@ -212,17 +211,17 @@ jarq_status prepare_impl(const jarq_params* p, const float* W, const float* H, v
   JQ_HIP(launch_begin_run(c.st, z, 0, nullptr, nullptr, nullptr));
   JQ_HIP(launch_chol_groups(c.st, c.cols, c.g, H, c.ws, c.lay));
   JQ_HIP(launch_split_r(c.st, c.cols, c.g, c.ws, c.lay));
+  JQ_HIP(launch_wh(c.st, c.rows, c.cols, W, H, c.ws, c.lay));
   JQ_HIP(launch_split_m(c.st, c.cols, c.g, H, c.ws, c.lay));
   JQ_HIP(launch_split_h(c.st, c.cols, H, c.ws, c.lay));
-  // T~ = W M~^T and RW = W_i L_i, the constant parts of the residual product
-  // and of the objective, and W H from T~; W's two fp16 planes borrow P's memory
+  // T = W M^T and RW = W_i L_i, the constant parts of the residual product
+  // and of the objective; W's two fp16 planes borrow P's memory
   _Float16* whi = (_Float16*)c.pbuf();
   _Float16* wlo = whi + (size_t)c.rows * c.cols;
   float* wrow = (float*)(c.ws + c.lay.wrow);
   JQ_HIP(launch_split_w(c.st, c.rows, c.cols, W, whi, wlo, wrow));
   JQ_HIP(launch_wm_product(c.st, c.rows, c.cols, c.ws, c.lay, whi, wlo, wrow));
   JQ_HIP(launch_rw_product(c.st, c.rows, c.cols, c.g, c.ws, c.lay, whi, wlo, wrow));
-  JQ_HIP(launch_wh(c.st, c.rows, c.cols, c.g, c.ws, c.lay));
   Flags f{};
   JQ_HIP(hipMemcpyAsync(&f, c.flags(), sizeof(Flags), hipMemcpyDeviceToHost, c.st));
   JQ_HIP(hipStreamSynchronize(c.st));

@@ -6,9 +6,7 @@
 // (the Babai proposal does not depend on the row signs of R_i).  One work-group
 // factors one g x g block in LDS in fp64, inverts the lower factor L_i = R_i^T,
 // and writes the forms the later kernels read:
-//   lfac  L~_i^{-1} in fp64 (zero above the diagonal), L~_i = L_i with its columns
-//         divided by its diagonal: L_i^{-1} with its rows multiplied by L_i(n, n),
-//         a unit triangle, for M~ = blockdiag(L~^{-1}) H
+//   lfac  L_i^{-1} in fp64 (zero above the diagonal), for M = blockdiag(L^{-1}) H
 //   rcol  column l, chunk c, lane j, w: R_i(m, l) / R_i(m, m) for m < l, 0
 //         for m >= l, with m = j + 16 (W c + w), W = min(4, g / 16) (column l
 //         of R_i above the diagonal with each row scaled by its inverse
@@ -80,12 +78,12 @@ __global__ __launch_bounds__(256) void chol_groups_kernel(const float* __restric
           (float)(r0 + i >= c0 + j ? B[i * kCholLd + j] : 0.0);
     }
   };
-  // the diagonal block of L~^{-1} at (r0, r0)
+  // the diagonal block of L^{-1} at (r0, r0)
   auto out_x = [&](const double* X, int r0) {
     for (int e = tid; e < n * n; e += 256) {
       const int i = e / n, j = e % n;
       lfac_b[(size_t)(r0 + i) * g + r0 + j] =
-          j < i ? X[i * kCholLd + j] / dinv[r0 + i] : (j == i ? 1.0 : 0.0);
+          j <= i ? X[i * kCholLd + j] : 0.0;
     }
   };
 
@@ -155,10 +153,7 @@ __global__ __launch_bounds__(256) void chol_groups_kernel(const float* __restric
             x = mfma_f64(-frag_a(B0, 16 * bi, 16 * u, ks), t[u][ks], x);
 #pragma unroll
         for (int v = 0; v < 4; ++v)
-        {
-          const int i = 64 + 16 * bi + 4 * v + (lane >> 4);
-          lfac_b[(size_t)i * g + 16 * wave + (lane & 15)] = x[v] / dinv[i];
-        }
+          lfac_b[(size_t)(64 + 16 * bi + 4 * v + (lane >> 4)) * g + 16 * wave + (lane & 15)] = x[v];
       }
     }
     // the zero blocks above the diagonal of L^{-1} and below that of R

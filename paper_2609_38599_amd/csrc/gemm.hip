@@ -1,9 +1,4 @@
-// Products of fp32 operands.
-//
-// wh_kernel (fp32 matrix cores): W H of the scale right-hand sides (prepare;
-// paper App. G.8), from the layer's T~ = W M~^T.  M~ = blockdiag(L~_i^{-1}) H with
-// L~_i the unit triangle of H_ii's factor, so group i's columns of W H are
-// T~_i L~_i^T: g multiplies a value instead of the cols of the product with H.
+// The product E H of the stand-alone row objectives.
 //
 // row_products_kernel (three bf16 planes, bf16x3.h): the row objectives
 // e_j^T H e_j of the stand-alone jarq_objective (paper Sec. 3.3.2 and eq. (7)),
@@ -220,78 +215,6 @@ hipError_t launch_row_products(hipStream_t st, int rows, int cols, int g, const 
   const long long big = (long long)((cols + 127) / 128) * ((rows + 127) / 128);
   if (big >= 256) return launch_row_products_t<true>(st, rows, E, H, objpart);
   return launch_row_products_t<false>(st, rows, E, H, objpart);
-}
-
-// WH(r, n) = sum_{m <= n} T~(r, m) L~_i(n, m) over the columns of group i, with
-// L~_i(n, m) = R_i(m, n) / R_i(m, m) (rmat, rdinv), 1 on the diagonal.  Work-group:
-// 128 rows x one group, the triangle staged in LDS; a wavefront takes 32 rows,
-// with the rows' T values of the group in registers, four consecutive k a lane:
-// step t of a chunk of 8 takes k = 4 (lane / 32) + t, in both operands.  Blocks of 32 columns skip the k past
-// their own (R_i is upper triangular).  Bound by reading T and writing W H
-// (8 bytes a value): 176 us for 4096 x 11008 at g = 128 (2.1 TB/s), where the
-// fp32 product with H took 17.8 ms, and nearer to the 64-bit value (scales of
-// that layer 5.3e-7 off instead of 1.1e-6): T's sums have fewer fp32 roundings.
-template <int G_SIZE>
-__global__ __launch_bounds__(256) void wh_kernel(int rows, int cols, const float* __restrict__ T,
-                                                 const float* __restrict__ rmat,
-                                                 const float* __restrict__ rdinv,
-                                                 float* __restrict__ WH) {
-  constexpr int g = G_SIZE;
-  constexpr int NB = g / 32, KC = g / 8;
-  __shared__ float r_s[g * g];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int lm = lane & 31, kh = lane >> 5;
-  const int i = blockIdx.x;
-  const float* Ri = rmat + (size_t)i * g * g;
-  const int r0 = blockIdx.y * 128 + 32 * wave;
-  const int row = r0 + lm < rows ? r0 + lm : rows - 1;   // past the end: never stored
-  const float* t_row = T + (size_t)row * cols + (size_t)i * g + 4 * kh;
-  f32x4 a[KC];
-#pragma unroll
-  for (int kc = 0; kc < KC; ++kc) a[kc] = *(const f32x4*)(t_row + 8 * kc);
-  for (int e = tid; e < g * g / 4; e += 256) {
-    const int m = 4 * e / g, n = 4 * e % g;
-    const float ri = rdinv[(size_t)i * g + m];
-    f32x4 v = *(const f32x4*)(Ri + 4 * e);
-#pragma unroll
-    for (int u = 0; u < 4; ++u) v[u] = n + u == m ? 1.f : v[u] * ri;
-    *(f32x4*)(r_s + 4 * e) = v;
-  }
-  __syncthreads();
-  f32x16 acc[NB];
-#pragma unroll
-  for (int b = 0; b < NB; ++b) acc[b] = f32x16{};
-#pragma unroll
-  for (int kc = 0; kc < KC; ++kc)
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-#pragma unroll
-      for (int b = kc / 4; b < NB; ++b)
-        acc[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(
-            a[kc][t], r_s[(8 * kc + 4 * kh + t) * g + 32 * b + lm], acc[b], 0, 0, 0);
-    }
-#pragma unroll
-  for (int b = 0; b < NB; ++b)
-#pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      const int r = r0 + 8 * (v / 4) + 4 * kh + (v % 4);
-      if (r < rows) WH[(size_t)r * cols + (size_t)i * g + 32 * b + lm] = acc[b][v];
-    }
-}
-
-hipError_t launch_wh(hipStream_t st, int rows, int cols, int g, char* ws, const Layout& lay) {
-  const float* T = (const float*)(ws + lay.tm);
-  const float* rmat = (const float*)(ws + lay.rmat);
-  const float* rdinv = (const float*)(ws + lay.rdinv);
-  float* WH = (float*)(ws + lay.wh);
-  const dim3 grid(cols / g, (rows + 127) / 128);
-  switch (g) {
-    case 32: hipLaunchKernelGGL(wh_kernel<32>, grid, dim3(256), 0, st, rows, cols, T, rmat, rdinv, WH); break;
-    case 64: hipLaunchKernelGGL(wh_kernel<64>, grid, dim3(256), 0, st, rows, cols, T, rmat, rdinv, WH); break;
-    case 128: hipLaunchKernelGGL(wh_kernel<128>, grid, dim3(256), 0, st, rows, cols, T, rmat, rdinv, WH); break;
-    default: return hipErrorInvalidValue;
-  }
-  return hipGetLastError();
 }
 
 }  // namespace jarq

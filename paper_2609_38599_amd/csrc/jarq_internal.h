@@ -106,7 +106,7 @@ inline hipError_t allow_dynamic_lds(const void* fn, size_t bytes,
 
 // Offsets (bytes) of the workspace regions for one problem size.
 struct Layout {
-  size_t lfac;      // [G][g][g] f64: L~_i^{-1} (L_i^{-1}, rows times L_i(n, n))
+  size_t lfac;      // [G][g][g] f64: L_i^{-1}
   size_t rcol;      // [G][g][g/(16 W)][16][W] f32: R~_i columns in lane chunks (W = min(4, g/16))
   size_t rdinv;     // [G][g] f32: 1 / R_i(l,l)
   size_t rdsq;      // [G][g] f32: R_i(l,l)^2
@@ -117,15 +117,14 @@ struct Layout {
   size_t rph;       // [G][g][g] f16: R_i row c scaled by 2^t_c, high term
   size_t rpl;       // [G][g][g] f16: low term
   size_t rrow;      // [G][g] f32: 2^-t_c of the R rows
-  size_t mhi;       // [cols][cols] f16: M~ = blockdiag(L~_i^{-1}) H, row n scaled by 2^t_n, high term
+  size_t mhi;       // [cols][cols] f16: M = blockdiag(L_i^{-1}) H, row n scaled by 2^t_n, high term
   size_t mlo;       // [cols][cols] f16: low term
-  size_t mrow;      // [cols] f32: 2^-t_n / L_i(n, n): M from M~'s planes
-  size_t mpow;      // [cols] f32: 2^-t_n
-  size_t mmax;      // [cols] f32: row maxima of M~ (prep scratch)
+  size_t mrow;      // [cols] f32: 2^-t_n
+  size_t mmax;      // [cols] f32: row maxima of M (prep scratch)
   size_t wrow;      // [rows] f32: 2^-t_row of W's fp16 planes (prepare; the planes
                     // themselves occupy p's memory until the first sweep)
   size_t wh;        // [rows][cols] f32: W H
-  size_t tm;        // [rows][cols] f32: T~ = W M~^T (the residual product of W alone, times L_i(n, n))
+  size_t tm;        // [rows][cols] f32: T = W M^T (the residual product of W alone)
   size_t rw;        // [rows][cols] f32: W_i L_i per group (the objective's part of W alone)
   size_t cz;        // [rows][cols] f16: q - z, exact, by layer row (kept with the codes)
   size_t gram;      // [rows][G][G] f32: upper triangle of B^T B
@@ -165,11 +164,14 @@ hipError_t launch_split_r(hipStream_t st, int cols, int g, char* ws, const Layou
 hipError_t launch_row_products(hipStream_t st, int rows, int cols, int g, const float* W,
                                const uint8_t* codes, const float* scales, const int32_t* zeros,
                                const float* H, double* objpart);
-// W H (lay.wh) from T~ = W M~^T and R_i.
-hipError_t launch_wh(hipStream_t st, int rows, int cols, int g, char* ws, const Layout& lay);
+// W H into lay.wh (sgemm.hip).  W's three bf16 planes take the memory of cz, dq
+// and p, H's that of the fp16 planes hhi, hlo and mhi: call it before those are
+// written.
+hipError_t launch_wh(hipStream_t st, int rows, int cols, const float* W, const float* H, char* ws,
+                     const Layout& lay);
 
 hipError_t launch_split_h(hipStream_t st, int cols, const float* H, char* ws, const Layout& lay);
-// M~ = blockdiag(L~_i^{-1}) H as two fp16 planes with per-row scales (after
+// M = blockdiag(L_i^{-1}) H as two fp16 planes with per-row scales (after
 // launch_chol_groups; uses the H planes as scratch, so call launch_split_h
 // after).  The caller has cleared the row maxima (lay.mmax) and max |H|
 // (lay.hscale's second word).
@@ -178,7 +180,7 @@ hipError_t launch_split_m(hipStream_t st, int cols, int g, const float* H, char*
 
 // The layer's constant parts of the per-sweep products (jarq_prepare), from
 // W as two fp16 planes (whi, wlo with row scales 2^-t in wrow, all rows):
-// T~ = W M~^T into lay.tm (three products, sgemm.hip) and RW = W_i L_i per
+// T = W M^T into lay.tm (three products, sgemm.hip) and RW = W_i L_i per
 // group into lay.rw (objective.hip).
 hipError_t launch_split_w(hipStream_t st, int rows, int cols, const float* W, _Float16* whi,
                           _Float16* wlo, float* wrow_inv);
@@ -193,7 +195,7 @@ hipError_t launch_rw_product(hipStream_t st, int rows, int cols, int g, const ch
 hipError_t launch_codes_cz(hipStream_t st, int rows, int cols, int g, int bits,
                            const uint8_t* codes, const int32_t* zeros, _Float16* cz,
                            Flags* flags);
-// U = (T~ - What M~^T) / L(n, n) from the exact codes (cz) and the scales, layer rows
+// U = T - What M^T from the exact codes (cz) and the scales, layer rows
 // through rowmap, U by position (sgemm.hip).  ev_start / ev_stop (nullable):
 // events that take the kernel's own start and end times (no marker of their
 // own in the stream).

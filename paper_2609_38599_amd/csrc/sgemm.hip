@@ -29,7 +29,7 @@
 // compact block of tiles that share A row-tiles and B column-tiles in its L2.
 #include <hip/hip_ext.h>
 
-#include "jarq_internal.h"
+#include "bf16x3.h"
 
 namespace jarq {
 
@@ -354,15 +354,15 @@ __global__ __launch_bounds__(256, 1) void split3_small_kernel(
   }
 }
 
-// T~ = W M~^T for the layer, all rows (jarq_prepare): W's two fp16 planes
-// against M~'s, three products.
+// T = W M^T for the layer, all rows (jarq_prepare): W's two fp16 planes
+// against M's, three products.
 hipError_t launch_wm_product(hipStream_t st, int rows, int cols, const char* ws,
                              const Layout& lay, const _Float16* whi, const _Float16* wlo,
                              const float* wrow_inv) {
   if (rows <= 0 || cols <= 0) return hipSuccess;
   const _Float16* bh = (const _Float16*)(ws + lay.mhi);
   const _Float16* bl = (const _Float16*)(ws + lay.mlo);
-  const float* bc = (const float*)(ws + lay.mpow);
+  const float* bc = (const float*)(ws + lay.mrow);
   // 64 x 64 tiles where there are few of 256 x 256 (a whole set-up, large tiles
   // and small: 611 x 1312, 18 large tiles, 175 and 123 us; 300 x 11008, 86 of
   // them, 1711 and 1565; 1500 x 4096, 96, 511 and 522)
@@ -416,9 +416,8 @@ template <int G_SIZE, bool BIG>
 __global__ __launch_bounds__(BIG ? 512 : 256, 1) void resid_kernel(
     int M, int N, int K, const _Float16* __restrict__ Cz, const float* __restrict__ scales,
     const _Float16* __restrict__ Bh, const _Float16* __restrict__ Bl,
-    const float* __restrict__ bcol_inv, const float* __restrict__ rdinv,
-    const float* __restrict__ T, float* __restrict__ U, const int32_t* __restrict__ rowmap,
-    const int* __restrict__ m_dev) {
+    const float* __restrict__ bcol_inv, const float* __restrict__ T, float* __restrict__ U,
+    const int32_t* __restrict__ rowmap, const int* __restrict__ m_dev) {
   if (m_dev != nullptr) M = *m_dev;
   constexpr int g = G_SIZE;
   constexpr int RBM = BIG ? 256 : 64, RBN = BIG ? 128 : 64;
@@ -597,7 +596,7 @@ __global__ __launch_bounds__(BIG ? 512 : 256, 1) void resid_kernel(
     }
   }
 
-  // Epilogue: U = (T~ - acc 2^-t_n) / L(n, n).  Accumulator element v of lane l in a
+  // Epilogue: U = T - acc 2^-t_n.  Accumulator element v of lane l in a
   // 32 x 32 block: (row 8 (v / 4) + 4 (l / 32) + v % 4, column l % 32).
 #pragma unroll
   for (int a = 0; a < AB; ++a) {
@@ -606,7 +605,7 @@ __global__ __launch_bounds__(BIG ? 512 : 256, 1) void resid_kernel(
     for (int b = 0; b < AB; ++b) {
       const int col = n0 + wn * WT + b * 32 + lm;
       const int colc = min(col, N - 1);
-      const float cs = bcol_inv[colc], ds = rdinv[colc];
+      const float cs = bcol_inv[colc];
       float tv[16];
 #pragma unroll
       for (int v = 0; v < 16; ++v)
@@ -614,7 +613,7 @@ __global__ __launch_bounds__(BIG ? 512 : 256, 1) void resid_kernel(
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
         const int row = m0 + tb + 8 * (v / 4) + (v % 4);
-        if (row < M && col < N) U[(size_t)row * N + col] = (tv[v] - acc[a][b][v] * cs) * ds;
+        if (row < M && col < N) U[(size_t)row * N + col] = tv[v] - acc[a][b][v] * cs;
       }
     }
   }
@@ -632,14 +631,13 @@ static hipError_t launch_resid_t(hipStream_t st, int rows, int cols, const char*
     hipExtLaunchKernelGGL((resid_kernel<G_SIZE, BIG>), grid, block, 0, st, ev_start, ev_stop, 0u,
                           rows, cols, cols, (const _Float16*)(ws + lay.cz), scales,
                           (const _Float16*)(ws + lay.mhi), (const _Float16*)(ws + lay.mlo),
-                          (const float*)(ws + lay.mpow), (const float*)(ws + lay.rdinv),
-                          (const float*)(ws + lay.tm), U, rowmap, n_dev);
+                          (const float*)(ws + lay.mrow), (const float*)(ws + lay.tm), U, rowmap,
+                          n_dev);
   } else {
     hipLaunchKernelGGL((resid_kernel<G_SIZE, BIG>), grid, block, 0, st, rows, cols, cols,
                        (const _Float16*)(ws + lay.cz), scales, (const _Float16*)(ws + lay.mhi),
-                       (const _Float16*)(ws + lay.mlo), (const float*)(ws + lay.mpow),
-                       (const float*)(ws + lay.rdinv), (const float*)(ws + lay.tm), U, rowmap,
-                       n_dev);
+                       (const _Float16*)(ws + lay.mlo), (const float*)(ws + lay.mrow),
+                       (const float*)(ws + lay.tm), U, rowmap, n_dev);
   }
   return hipGetLastError();
 }
@@ -670,6 +668,198 @@ hipError_t launch_resid(hipStream_t st, int rows, int cols, int g, const char* w
     default: return hipErrorInvalidValue;
   }
 #undef JARQ_RESID
+}
+
+// ---- W H (the right-hand sides of the scale update, App. G.8) ----
+//
+// An fp32-grade product of fp32 operands: both as three bf16 planes, which hold
+// all 24 bits of every value whatever the range of its row, and the six products
+// above 2^-25 relative (bf16x3.h), so that what is exact in fp32 (small
+// integers) stays exact.  (Taking W H from T = W M^T and L_i is cheaper, 0.18
+// instead of 5.3 ms at 4096 x 11008, but M is rounded and the fp16 planes hold 22
+// bits below the largest value of a row: integers lost their last bits, and rows
+// that span more than 2^17 their small weights.)
+//
+// H is symmetric, so B(k, n) = H(k, n) is read along row n.  256 x 128 tiles, 4 x 2
+// wavefronts of 64 x 64, or 64 x 64 tiles of 2 x 2 wavefronts of 32 x 32 (the same
+// products in the same order: the same bits), K in steps of 32 straight from
+// memory into two LDS stages.  Bound by the matrix cores: 4096 x 4096 0.7 ms with
+// the splits (1.2 PFLOP/s), 4096 x 11008 5.6 ms (the fp32 instruction: 1.5 and
+// 17.8 ms).
+namespace {
+// n8 pieces of eight values of x as three planes.
+__global__ __launch_bounds__(256) void split_bf16x3_kernel(const float* __restrict__ x, size_t n8,
+                                                           u32x4* __restrict__ h,
+                                                           u32x4* __restrict__ m,
+                                                           u32x4* __restrict__ l) {
+  for (size_t e = (size_t)blockIdx.x * 256 + threadIdx.x; e < n8; e += (size_t)gridDim.x * 256) {
+    const f32x4 v0 = ((const f32x4*)x)[2 * e], v1 = ((const f32x4*)x)[2 * e + 1];
+    u32x4 p[3];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      uint32_t a, b, c;
+      split_pair(i < 2 ? v0[2 * i] : v1[2 * i - 4], i < 2 ? v0[2 * i + 1] : v1[2 * i - 3], a, b, c);
+      p[0][i] = a, p[1][i] = b, p[2][i] = c;
+    }
+    h[e] = p[0];
+    m[e] = p[1];
+    l[e] = p[2];
+  }
+}
+
+hipError_t launch_split_bf16x3(hipStream_t st, const float* x, size_t n, __bf16* const (&pl)[3]) {
+  const size_t n8 = n / 8, blocks = (n8 + 255) / 256;   // cols is a multiple of 32
+  hipLaunchKernelGGL(split_bf16x3_kernel, dim3((unsigned)(blocks < 8192 ? blocks : 8192)), dim3(256),
+                     0, st, x, n8, (u32x4*)pl[0], (u32x4*)pl[1], (u32x4*)pl[2]);
+  return hipGetLastError();
+}
+
+struct Planes {
+  const __bf16* p[3];
+};
+
+// The 32 x 32 block of W H at (r0, c0) with the fp32 instruction straight from
+// memory (one wavefront): for sums the planes cannot do (bf16x3.h).
+__device__ __forceinline__ f32x16 wh_slow_block(const float* __restrict__ W,
+                                                const float* __restrict__ H, int M, int N, int r0,
+                                                int c0) {
+  const int lane = threadIdx.x & 63, lm = lane & 31, kh = lane >> 5;
+  const float* w = W + (size_t)min(r0 + lm, M - 1) * N + kh;
+  const float* h = H + (size_t)min(c0 + lm, N - 1) * N + kh;
+  f32x16 acc = f32x16{};
+  for (int k = 0; k < N; k += 2)   // N is even
+    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(w[k], h[k], acc, 0, 0, 0);
+  return acc;
+}
+}  // namespace
+
+// C [M][N] = A B, A [M][N] and B [N][N] symmetric.
+template <bool BIG>
+__global__ __launch_bounds__(BIG ? 512 : 256, 1) void wh_kernel(int M, int N, Planes A, Planes B,
+                                                                const float* __restrict__ W,
+                                                                const float* __restrict__ H,
+                                                                float* __restrict__ C) {
+  constexpr int TM = BIG ? 256 : 64, TN = BIG ? 128 : 64;
+  constexpr int NW = BIG ? 8 : 4, AB = BIG ? 2 : 1, WT = 32 * AB;
+  constexpr int A_PLANE = TM * BK, B_PLANE = TN * BK;          // values
+  constexpr int STAGE = 3 * (A_PLANE + B_PLANE);
+  constexpr int APW = TM / 16 / NW, BPW = TN / 16 / NW;        // 1 KB pieces per wave and plane
+  __shared__ __attribute__((aligned(1024))) _Float16 buf0[STAGE];
+  __shared__ __attribute__((aligned(1024))) _Float16 buf1[STAGE];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave >> 1, wn = wave & 1;
+  const int lm = lane & 31, kh = lane >> 5;
+  int tm, tn;
+  if (!tile_of(blockIdx.x, (M + TM - 1) / TM, (N + TN - 1) / TN, tm, tn)) return;  // uniform
+  const int m0 = tm * TM, n0 = tn * TN;
+  // rows past the edge read the tile's first row: their results are not stored
+  unsigned aoff[APW], boff[BPW];
+#pragma unroll
+  for (int i = 0; i < APW; ++i) {
+    const int r = 16 * (wave + NW * i) + (lane >> 2);
+    aoff[i] = (unsigned)(m0 + r < M ? r : 0) * (unsigned)N + (unsigned)(((lane & 3) ^ swz(r)) * 8);
+  }
+#pragma unroll
+  for (int i = 0; i < BPW; ++i) {
+    const int r = 16 * (wave + NW * i) + (lane >> 2);
+    boff[i] = (unsigned)(n0 + r < N ? r : 0) * (unsigned)N + (unsigned)(((lane & 3) ^ swz(r)) * 8);
+  }
+  const size_t a0 = (size_t)m0 * N, b0 = (size_t)n0 * N;
+  auto issue = [&](int k0, _Float16* stage) {
+#pragma unroll
+    for (int p = 0; p < 3; ++p) {
+#pragma unroll
+      for (int i = 0; i < APW; ++i)
+        dma16((const _Float16*)(A.p[p] + a0 + k0) + aoff[i],
+              stage + p * A_PLANE + (wave + NW * i) * 512);
+#pragma unroll
+      for (int i = 0; i < BPW; ++i)
+        dma16((const _Float16*)(B.p[p] + b0 + k0) + boff[i],
+              stage + 3 * A_PLANE + p * B_PLANE + (wave + NW * i) * 512);
+    }
+  };
+  f32x16 big[AB][AB], low[AB][AB];
+#pragma unroll
+  for (int b = 0; b < AB; ++b)
+#pragma unroll
+    for (int a = 0; a < AB; ++a) big[b][a] = low[b][a] = f32x16{};
+  auto compute = [&](const _Float16* st) __attribute__((always_inline)) {
+    auto frag = [&](const _Float16* plane, int r, int ks) __attribute__((always_inline)) {
+      return *(const bf16x8*)(plane + r * BK + (((2 * ks + kh) ^ swz(r)) << 3));
+    };
+#pragma unroll
+    for (int ks = 0; ks < BK / 16; ++ks) {
+      bf16x8 fa[AB][3], fb[AB][3];
+#pragma unroll
+      for (int p = 0; p < 3; ++p)
+#pragma unroll
+        for (int a = 0; a < AB; ++a) {
+          fa[a][p] = frag(st + p * A_PLANE, wm * WT + a * 32 + lm, ks);
+          fb[a][p] = frag(st + 3 * A_PLANE + p * B_PLANE, wn * WT + a * 32 + lm, ks);
+        }
+#pragma unroll
+      for (int b = 0; b < AB; ++b) mfma_bf16x3<AB>(fa, fb[b], big[b], low[b]);
+    }
+  };
+  const int nk = N / BK;
+  issue(0, buf0);
+  __syncthreads();
+  for (int kt = 0; kt < nk; kt += 2) {
+    // a stage was last read before the barrier that precedes its loads; the
+    // barrier after a step waits for the next one's loads
+    if (kt + 1 < nk) issue((kt + 1) * BK, buf1);
+    compute(buf0);
+    __syncthreads();
+    if (kt + 1 < nk) {
+      if (kt + 2 < nk) issue((kt + 2) * BK, buf0);
+      compute(buf1);
+      __syncthreads();
+    }
+  }
+#pragma unroll
+  for (int a = 0; a < AB; ++a)
+#pragma unroll
+    for (int b = 0; b < AB; ++b) {
+      const int rb = m0 + wm * WT + a * 32, cb = n0 + wn * WT + b * 32;
+      f32x16 acc = big[b][a] + low[b][a];
+      bool fine = true;
+#pragma unroll
+      for (int v = 0; v < 16; ++v) fine &= isfinite(acc[v]);
+      if (!__all(fine)) {
+        const f32x16 slow = wh_slow_block(W, H, M, N, rb, cb);
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[v] = isfinite(acc[v]) ? acc[v] : slow[v];
+      }
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const int row = rb + 8 * (v / 4) + 4 * kh + (v % 4);
+        if (row < M && cb + lm < N) C[(size_t)row * N + cb + lm] = acc[v];
+      }
+    }
+}
+
+hipError_t launch_wh(hipStream_t st, int rows, int cols, const float* W, const float* H, char* ws,
+                     const Layout& lay) {
+  if (cols % BK != 0) return hipErrorInvalidValue;
+  __bf16* const wp[3] = {(__bf16*)(ws + lay.cz), (__bf16*)(ws + lay.dq), (__bf16*)(ws + lay.p)};
+  __bf16* const hp[3] = {(__bf16*)(ws + lay.hhi), (__bf16*)(ws + lay.hlo), (__bf16*)(ws + lay.mhi)};
+  hipError_t e = launch_split_bf16x3(st, W, (size_t)rows * cols, wp);
+  if (e == hipSuccess) e = launch_split_bf16x3(st, H, (size_t)cols * cols, hp);
+  if (e != hipSuccess) return e;
+  const Planes A{{wp[0], wp[1], wp[2]}}, B{{hp[0], hp[1], hp[2]}};
+  float* C = (float*)(ws + lay.wh);
+  // large tiles from 160 of them on (a whole set-up, large tiles and small:
+  // 1024 x 4096, 128 large tiles, 748 and 723 us; 1280 x 4096, 160 of them, 807 and
+  // 819; 1536 x 4096 818 and 886)
+  const long long big = (long long)((rows + 255) / 256) * ((cols + 127) / 128);
+  if (big >= 160)
+    hipLaunchKernelGGL(wh_kernel<true>, dim3((unsigned)big), dim3(512), 0, st, rows, cols, A, B, W,
+                       H, C);
+  else
+    hipLaunchKernelGGL(wh_kernel<false>, dim3(((rows + 63) / 64) * ((cols + 63) / 64)), dim3(256),
+                       0, st, rows, cols, A, B, W, H, C);
+  return hipGetLastError();
 }
 
 }  // namespace jarq

@@ -5,10 +5,8 @@
 // hi = fp16(x 2^t), lo = fp16(x 2^t - hi), which carries 22 significant bits.
 // Products of such planes accumulate in fp32 on the matrix cores.
 //   H:  one scale for the whole matrix, chosen so max |H| 2^t lies in [2^13, 2^14).
-//   M~ = blockdiag(L~_i^{-1}) H, L~_i = L_i with unit diagonal: the code update's
-//       coordinates, M = blockdiag(L_i^{-1}) H (eq. (10)), are its rows divided by
-//       L_i(n, n).  One power of two per row of M~, same rule; the products take
-//       the row factor 2^-t / L_i(n, n).
+//   M = blockdiag(L_i^{-1}) H, the code update's coordinates (eq. (10)): one
+//       power of two per row, same rule.
 //   W: one scale per row, same rule (for the layer's fixed W M^T and W_i L_i).
 // Small-integer operands (codes minus zero points, code changes) are exact in fp16.
 #include "jarq_internal.h"
@@ -43,8 +41,7 @@ __device__ __forceinline__ void split4(f32x4 x, int t, f16x4& hv, f16x4& lv) {
 }
 
 // A row of n x n fp32 values per work-group as two fp16 planes, scaled by 2^t
-// with t from amax[row] (per_row) or amax[0]; inv[row] or inv[0] = 2^-t, and per
-// row scaled[row] = 2^-t rdinv[row].
+// with t from amax[row] (per_row) or amax[0]; inv[row] or inv[0] = 2^-t.
 // Bound by memory traffic (4 bytes in, 4 out per value): 16-byte reads, 173 us
 // at 11008 x 11008 (5.6 TB/s); one value per thread and step took 355.
 template <bool kPerRow>
@@ -52,15 +49,10 @@ __global__ __launch_bounds__(256) void split_rows_kernel(const float* __restrict
                                                          const float* __restrict__ amax,
                                                          _Float16* __restrict__ hi,
                                                          _Float16* __restrict__ lo,
-                                                         float* __restrict__ inv,
-                                                         const float* __restrict__ rdinv,
-                                                         float* __restrict__ scaled) {
+                                                         float* __restrict__ inv) {
   const int r = blockIdx.x;
   const int t = pow2_exponent(amax[kPerRow ? r : 0]);
-  if (threadIdx.x == 0 && (kPerRow || r == 0)) {
-    inv[r] = ldexpf(1.f, -t);
-    if (kPerRow) scaled[r] = ldexpf(rdinv[r], -t);
-  }
+  if (threadIdx.x == 0 && (kPerRow || r == 0)) inv[r] = ldexpf(1.f, -t);
   const size_t row = (size_t)r * n;
   for (int c = threadIdx.x * 4; c < n; c += 1024) {
     f16x4 hv, lv;
@@ -75,20 +67,16 @@ __global__ __launch_bounds__(256) void split_rows_kernel(const float* __restrict
 hipError_t launch_split_h(hipStream_t st, int cols, const float* H, char* ws, const Layout& lay) {
   float* hs = (float*)(ws + lay.hscale);
   hipLaunchKernelGGL(split_rows_kernel<false>, dim3(cols), dim3(256), 0, st, H, cols, hs + 1,
-                     (_Float16*)(ws + lay.hhi), (_Float16*)(ws + lay.hlo), hs,
-                     (const float*)nullptr, (float*)nullptr);
+                     (_Float16*)(ws + lay.hhi), (_Float16*)(ws + lay.hlo), hs);
   return hipGetLastError();
 }
 
-// M~ = blockdiag(L~_i^{-1}) H.  Row n of M~ (group i = n / g, local index nl) is
-// sum_{m <= nl} L~_i^{-1}(nl, m) H(i g + m, :): the residual product with M (M~ with
-// rows divided by L_i(n, n)) in place of H gives u = L_i^{-1} (H e)_i for every
-// group at once, and its blocks M(i-block, h-block) = L_i^{-1} H_ih carry a code
-// change of group h into u_i.  (The unit triangle keeps what is exact in H exact
-// in M~ where a group's columns are uncorrelated, and with it W H, which is
-// taken from W M~^T.)  Formed in fp64 from the fp64 inverse, rounded to fp32 into a
-// temporary, with each row's maximum (then split with one scale per row) and
-// the largest |H|.
+// M = blockdiag(L_i^{-1}) H.  Row n of M (group i = n / g, local index nl) is
+// sum_{m <= nl} L_i^{-1}(nl, m) H(i g + m, :): the residual product with M in place
+// of H gives u = L_i^{-1} (H e)_i for every group at once, and its blocks
+// M(i-block, h-block) = L_i^{-1} H_ih carry a code change of group h into u_i.
+// Formed in fp64 from the fp64 inverse, rounded to fp32 into a temporary, with
+// each row's maximum (then split with one scale per row) and the largest |H|.
 //
 // On the fp64 matrix cores (v_mfma_f64_16x16x4_f64, 64 cycles each): a
 // work-group stages L_i^{-1} in LDS once and takes `span` columns, a
@@ -220,7 +208,6 @@ static hipError_t launch_split_m_t(hipStream_t st, int cols, const float* H, cha
                      (const double*)(ws + lay.lfac), mtmp, rowmax, hmax, span);
   hipLaunchKernelGGL(split_rows_kernel<true>, dim3(cols), dim3(256), 0, st, mtmp, cols, rowmax,
                      (_Float16*)(ws + lay.mhi), (_Float16*)(ws + lay.mlo),
-                     (float*)(ws + lay.mpow), (const float*)(ws + lay.rdinv),
                      (float*)(ws + lay.mrow));
   return hipGetLastError();
 }

@@ -288,3 +288,95 @@ def test_gram_walk_parts_agree(G):
         out.append(gk.state()[1])
     assert np.array_equal(out[0], out[1][:130])
     check_scales(out[0], jarq.scale_step(W[:130], H, q[:130], z[:130], g)[0], f" G={G}")
+
+
+def _scales_of(W, H, codes, zeros, g, bits=8):
+    gk = GpuLayer(W, H, codes, np.ones((W.shape[0], W.shape[1] // g), np.float32), zeros, g, bits)
+    gk.scale_step()
+    return gk.state()[1].astype(np.float64)
+
+
+# W H by small and large tiles
+@pytest.mark.parametrize("rows,cols", [(70, 96), (300, 1024), (4100, 1024)])
+def test_scales_of_an_integer_layer_are_exact(rows, cols):
+    """Integer W, H and codes whose Gram entries and W H fit fp32: everything
+    ahead of the fp64 solve is exact, so a scale is its 64-bit value rounded."""
+    g = 32
+    G = cols // g
+    rng = np.random.default_rng(rows + cols)
+    X = rng.integers(-1, 2, (cols + 64, cols))
+    X[:, 1:] += X[:, :-1]                       # correlated channels
+    H = (X.T @ X + 8 * np.eye(cols, dtype=np.int64)).astype(np.float64)
+    W = rng.integers(-9, 10, (rows, cols)).astype(np.float64)
+    codes = rng.integers(0, 3, (rows, cols)).astype(np.uint8)
+    zeros = np.ones((rows, G), np.int32)
+    C = codes.astype(np.float64) - 1.0
+    # no sum of magnitudes, in any order, passes 2^24
+    assert (np.abs(W) @ np.abs(H)).max() < 2 ** 24
+    assert (np.abs(C) @ np.abs(H)).max() * g < 2 ** 24
+    got = _scales_of(W.astype(np.float32), H.astype(np.float32), codes, zeros, g)
+    WH = W @ H
+    A = np.empty((rows, G, G))
+    for a in range(G):
+        T = C[:, a * g:(a + 1) * g] @ H[a * g:(a + 1) * g]
+        A[:, a] = (T * C).reshape(rows, G, g).sum(2)
+    ref = np.linalg.solve(A, (WH * C).reshape(rows, G, g).sum(2)[:, :, None])[:, :, 0]
+    # half an fp32 ulp, and the fp64 solves (condition numbers below 1e4)
+    bound = 0.5 * np.spacing(np.abs(ref).astype(np.float32)).astype(np.float64) + \
+        1e-11 * np.abs(ref).max(axis=1, keepdims=True)
+    assert np.all(np.abs(got - ref) <= bound)
+
+
+def _one_code_layer(rows, g, seed, value=None):
+    """Two groups without correlation between them, one code of 1 in each: a
+    scale is (W H)_n / H_nn of that code's column.  Channel scales are powers of
+    two over 28 octaves, which scale W, H and W H without rounding."""
+    cols = 2 * g
+    rng = np.random.default_rng(seed)
+    D = np.ldexp(1.0, -rng.integers(0, 29, cols))
+    D[0], D[g - 1], D[g], D[2 * g - 1] = 1.0, 2.0 ** -28, 1.0, 2.0 ** -28
+    X = rng.standard_normal((4 * g, cols))
+    H0 = X.T @ X / (4 * g)
+    H0[:g, g:] = H0[g:, :g] = 0.0
+    np.fill_diagonal(H0, 1.0)
+    H0 = H0.astype(np.float32).astype(np.float64)
+    H0 = np.triu(H0) + np.triu(H0, 1).T + np.eye(cols)     # diagonal 2
+    W0 = rng.standard_normal((rows, cols)).astype(np.float32).astype(np.float64)
+    H, W = H0 * D * D[:, None], W0 / D
+    if value is not None:
+        W[5, 0] = value
+    codes = np.zeros((rows, cols), np.uint8)
+    codes[:, 0] = codes[:, g] = 1               # the channels of scale 1
+    return W.astype(np.float32), H.astype(np.float32), codes, np.zeros((rows, 2), np.int32)
+
+
+@pytest.mark.parametrize("rows", [70, 33000])
+def test_scales_where_weights_span_many_octaves(rows):
+    """W H to fp32 rounding whatever the range of a row of W: sums of 64 terms,
+    (64 + 2) u of the sum of magnitudes, and the scale's own rounding."""
+    g = 64
+    W, H, codes, zeros = _one_code_layer(rows, g, 11)
+    got = _scales_of(W, H, codes, zeros, g)
+    W, H = W.astype(np.float64), H.astype(np.float64)
+    n = [0, g]
+    ref, size = (W @ H)[:, n] / 2.0, (np.abs(W) @ np.abs(H))[:, n] / 2.0
+    assert np.all(np.abs(got - ref) <= 66 * 2.0 ** -24 * size + 2.0 ** -24 * np.abs(ref))
+
+
+@pytest.mark.parametrize("rows", [70, 33000])
+@pytest.mark.parametrize("value", [float("inf"), float("nan"), 3.4e38])
+def test_scales_of_extreme_weights(rows, value):
+    """An infinity, a NaN, or a weight that rounds to infinity in bf16 stays in
+    its row and group, and is what fp32 arithmetic makes of it."""
+    g = 64
+    W, H, codes, zeros = _one_code_layer(rows, g, 12)
+    H *= np.float32(0.25)                       # 3.4e38 H_nn is finite
+    base = _scales_of(W, H, codes, zeros, g)
+    W[5, 0] = value
+    got = _scales_of(W, H, codes, zeros, g)
+    others = np.delete(np.arange(rows), 5)
+    assert np.array_equal(got[others], base[others])
+    if np.isfinite(value):
+        assert abs(got[5, 0] - value) <= 66 * 2.0 ** -24 * value
+    else:
+        assert not np.isfinite(got[5, 0])
