@@ -487,7 +487,7 @@ __global__ __launch_bounds__(512, 1) void babai_kernel(
     // even: group i0 + p + 1 goes to rc1_s for even p).
     static_assert(PG % 2 == 0, "panels hold an even number of groups");
     // Fragment buffers: a block of 32-wide groups is applied in much less time
-    // than its loads take, so two more fly (a code update of 4096 x 2048, g =
+    // than its loads take, so one more flies (a code update of 4096 x 2048, g =
     // 32: 421 us with loads under a branch, 377 without, 370 with a third
     // buffer; g = 64: 277, 279, 278, g = 128: 261, 263, 264).
     constexpr int TD = g == 32 ? 3 : 2;
@@ -517,13 +517,18 @@ __global__ __launch_bounds__(512, 1) void babai_kernel(
         // across the barrier.  A block of an earlier group that no row of the
         // tile accepted (decided before this position) is not applied; short
         // groups load M(i + 1, i) in its place (a load that may not happen
-        // leaves the compiler to wait for every one), long ones nothing.
+        // leaves the compiler to wait for every one), long ones nothing.  The
+        // block in its place is found by arithmetic on the flag (0 or 1), read
+        // into a scalar register once for this load alone: a select on it
+        // shares its condition with the branch of apply_t, and what is loaded
+        // must not hang on how the compiler orders the two.
         auto fetch = [&](int k, TFrag& fr) __attribute__((always_inline)) {
-          const bool wanted = k == p || tacc_s[k] != 0;
-          if constexpr (g == 32)
-            load_t(i + 1, wanted ? i0 + k : i, fr);
-          else if (wanted)
+          if constexpr (g == 32) {
+            const int flag = k == p ? 1 : __builtin_amdgcn_readfirstlane(tacc_s[k]);
+            load_t(i + 1, i + (k - p) * flag, fr);
+          } else if (k == p || tacc_s[k] != 0) {
             load_t(i + 1, i0 + k, fr);
+          }
         };
         Unroll<0, (p + 1 < TD - 1 ? p + 1 : TD - 1)>::run([&](auto kc) {
           constexpr int k = decltype(kc)::value;

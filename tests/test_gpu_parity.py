@@ -525,3 +525,23 @@ def test_changed_row_lists_of_a_short_last_tile(rows, cols, g):
         step.code_step(trace=False)
     qs, ss = step.state()
     assert np.array_equal(qg, qs) and np.array_equal(sg, ss)
+
+
+@pytest.mark.parametrize("rows,G", [(203, 50), (40, 33)])
+def test_code_update_of_later_panels_short_groups(rows, G):
+    """g = 32: panels of sixteen groups, three and four of them, every decision
+    against the oracle; in the later sweeps many a group is accepted by no row
+    of a tile of sixteen."""
+    g, bits = 32, 3
+    W, H, q, s, z = random_layer(rows, G * g, g, bits, seed=G)
+    R = jarq.group_factors(H, g)
+    gl = GpuLayer(W, H, q, s, z, g, bits)
+    none = 0
+    for k in range(6):
+        gl.scale_step()
+        q0, sk = gl.state()
+        cand, dec = gl.code_step()
+        check_code_step(W, H, R, q0, sk, z, g, bits, cand, dec, f" G {G} sweep {k}")
+        tiles = dec[:rows - rows % 16].reshape(-1, 16, G) == jq.DEC_ACCEPT
+        none += int((~tiles.any(axis=1))[:, :-1].sum())
+    assert none > 0

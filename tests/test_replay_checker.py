@@ -49,6 +49,49 @@ def test_planted_wrong_decision_is_flagged():
     assert rep2.skip_mismatch >= 1
 
 
+def _wrong_block_step(W, H, R, codes, s, zeros, g, bits, panel):
+    """A code step that keeps u = L^-1 (H e)_i up to date change by change and,
+    for the third group of every panel after the first, takes H(i, i - 1) where
+    the change of group i - 2 needs H(i, i - 2)."""
+    q, qmax, G = codes.astype(np.float64), (1 << bits) - 1, W.shape[1] // g
+    zc = np.repeat(zeros, g, axis=1).astype(np.float64)
+    cand, dec = codes.copy(), np.zeros(s.shape, np.uint8)
+    P = (W - np.repeat(s, g, axis=1) * (q - zc)) @ H
+    last = None                                   # the change of the group before
+    for i in range(G):
+        b = slice(i * g, (i + 1) * g)
+        Pi = P[:, b]
+        if i > panel and i % panel == 2:
+            Pi = Pi + last @ (H[(i - 2) * g:(i - 1) * g, b] - H[(i - 1) * g:i * g, b])
+        z = zeros[:, i].astype(np.float64)
+        v = np.linalg.solve(R[i].T, (Pi + s[:, i:i + 1] * (q[:, b] - z[:, None]) @ H[b, b]).T).T
+        v /= s[:, i:i + 1]
+        c, _ = jarq.babai_group(v, R[i], z, qmax)
+        old = v - (q[:, b] - z[:, None]) @ R[i].T
+        new = v - (c - z[:, None]) @ R[i].T
+        acc = (new * new).sum(1) < (old * old).sum(1)
+        delta = s[:, i:i + 1] * (c - q[:, b]) * acc[:, None]
+        cand[:, b], dec[:, i] = c.astype(np.uint8), np.where(acc, jarq.DEC_ACCEPT, jarq.DEC_REJECT)
+        P -= delta @ H[b]
+        if i % panel == 0:
+            last = delta                          # used two groups later
+    return cand, dec
+
+
+def test_wrong_correction_block_of_a_later_panel_is_flagged():
+    """The layer of the GPU test of later panels: a single wrong block there
+    shows, and without it the same loop replays clean."""
+    from tests._gpu_common import random_layer
+    g, bits = 32, 3
+    W, H, q, s, z = random_layer(40, 50 * g, g, bits, seed=50)
+    H, W = H.astype(np.float64), W.astype(np.float64)
+    R = jarq.group_factors(H, g)
+    s, _ = jarq.scale_step(W, H, q, z, g)
+    for panel, ok in ((10 ** 6, True), (16, False)):
+        cand, dec = _wrong_block_step(W, H, R, q, s, z, g, bits, panel)
+        assert replay_code_step(W, H, R, q, s, z, g, bits, cand, dec).ok == ok
+
+
 # ---------------------------------------------------------------------------
 # forced_refine: the oracle's own K iterations, deferring only inside the bands
 # ---------------------------------------------------------------------------
