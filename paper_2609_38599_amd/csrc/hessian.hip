@@ -26,12 +26,11 @@
 // channels: bf16 0.25 ms (0.55 PFLOP/s; 64 x 64 tiles of 32 x 32 a wavefront
 // staged through registers: 0.41), fp32 1.0 ms (the fp32 instruction: 1.45).
 #include "bf16x3.h"
+#include "token_spans.h"
 
 namespace jarq {
 
 namespace {
-constexpr int kSumTokens = 256;   // tokens per fp32 partial sum
-
 // The tiles of one launch: `big` 128 x 128 tiles (of the strict upper triangle,
 // or of the full grid for the cross term), then 64 x 64 tiles: the three of
 // each diagonal tile (symmetric), and the four of each of the last `cut` big
@@ -321,16 +320,17 @@ hipError_t launch_hessian_update_bf16(hipStream_t st, const void* X, int m, int 
 // The tile's sums with the fp32 instruction straight from memory (one wave,
 // blocks of 32 x 32): for the tiles the three planes cannot do.
 template <bool CROSS>
-__device__ __forceinline__ void syrk_f32_slow(const float* __restrict__ Xq, const float* __restrict__ X, int m,
-                              int d, int a0, int b0, double (&sum)[16]) {
+__device__ __forceinline__ void syrk_f32_slow(const float* __restrict__ Xq,
+                                              const float* __restrict__ X, int m, int d, int a0,
+                                              int b0, double (&sum)[16]) {
   const int lane = threadIdx.x & 63, lm = lane & 31, kh = lane >> 5;
   const bool ia = a0 + lm < d, ib = b0 + lm < d;
   const size_t ca = ia ? a0 + lm : 0, cb = ib ? b0 + lm : 0;
 #pragma unroll
   for (int v = 0; v < 16; ++v) sum[v] = 0.0;
-  for (int t0 = 0; t0 < m; t0 += kSumTokens) {
+  for (int t0 = 0, t1; t0 < m; t0 = t1) {
     f32x16 acc = f32x16{};
-    const int t1 = min(t0 + kSumTokens, m);
+    t1 = span_end(t0, m);
     for (int t = t0; t < t1; t += 2) {
       const bool it = t + kh < m;
       const size_t r = (size_t)(it ? t + kh : m - 1) * d;

@@ -191,3 +191,38 @@ def test_bench_refuses_more_than_one_gpu():
     assert res.returncode != 0
     assert "one GPU" in (res.stdout + res.stderr)
     assert res.stdout.strip() == "" or not res.stdout.strip().startswith("{")
+
+
+def test_token_spans_of_the_longest_chunks(tmp_path):
+    """The spans of the fp32 partial sums cover a chunk of any accepted length
+    without an intermediate value past it (signed overflow in a constant
+    expression does not compile)."""
+    import subprocess
+
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    src = tmp_path / "spans.cpp"
+    src.write_text("""
+#include <climits>
+#include "token_spans.h"
+using namespace jarq;
+// from a span start near the end: the spans that are left, or -1 for a wrong one
+constexpr int walk(int t0, int m) {
+  int n = 0;
+  while (t0 < m) {
+    const int t1 = span_end(t0, m);
+    if (t1 <= t0 || t1 > m || t1 - t0 > kSumTokens || (t1 < m && t1 - t0 != kSumTokens)) return -1;
+    t0 = t1;
+    ++n;
+  }
+  return n;
+}
+constexpr int kMost = INT_MAX - 64;   // the most tokens an entry point takes
+static_assert(walk(0, 1) == 1 && walk(0, 255) == 1 && walk(0, 256) == 1 && walk(0, 257) == 2, "");
+static_assert(walk(kMost / 256 * 256, kMost) == 1, "");
+static_assert(walk(kMost / 256 * 256 - 1024, kMost) == 5, "");
+static_assert(walk(kMost / 256 * 256 - 256, kMost / 256 * 256) == 1, "");
+""")
+    inc = os.path.join(root, "paper_2609_38599_amd", "csrc")
+    res = subprocess.run(["g++", "-std=c++17", "-fsyntax-only", "-I", inc, str(src)],
+                         capture_output=True, text=True)
+    assert res.returncode == 0, res.stderr
