@@ -380,3 +380,22 @@ def test_scales_of_extreme_weights(rows, value):
         assert abs(got[5, 0] - value) <= 66 * 2.0 ** -24 * value
     else:
         assert not np.isfinite(got[5, 0])
+
+
+# the permuted write-back scatters up to 64 rows and gathers from there on
+@pytest.mark.parametrize("rows,cols", [(1, 416), (64, 416), (65, 416), (1030, 288), (64, 16384),
+                                       (70, 16384)])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_dequantize_permuted_rows(rows, cols, dtype):
+    g = 32 if cols < 4096 else 128
+    q, s, z = _refined(rows, cols, g, 4, rows)
+    order = np.random.default_rng(rows).permutation(cols)
+    order[7], order[cols - 1] = cols + 3, -2
+    out = torch.full((rows, cols), 7.0, dtype=dtype, device="cuda")
+    jb.dequantize(jq.make_params(rows, cols, g, 4), to_dev(q), to_dev(s), to_dev(z), dtype=dtype,
+                  perm=to_dev(order.astype(np.int32)), out=out)
+    w = s.repeat(g, axis=1) * (q.astype(np.float32) - z.repeat(g, axis=1).astype(np.float32))
+    ref = torch.full((rows, cols), 7.0, dtype=dtype)
+    live = (order >= 0) & (order < cols)
+    ref[:, order[live]] = torch.from_numpy(w[:, live]).to(dtype)
+    assert torch.equal(out.cpu(), ref)
