@@ -14,17 +14,11 @@
 // whose sums come out infinite or NaN is formed again with the fp32
 // instruction, which treats such inputs as fp32 arithmetic does.
 //
-// Operands come from LDS channel-major (a row per channel, tokens along it),
-// so a fragment (32 channels x 16 tokens) is one 16-byte read a lane.  Threads
-// load 8 tokens of a few adjacent channels and transpose them in registers
-// (one v_perm for two values of one channel).  Rows are padded by 16 bytes,
-// which puts the 16 rows of a read, and the 16 chunks of a write, in
-// distinct banks.
-//
-// Work: 128 x 128 tiles, then 64 x 64 ones (Split below).
-// Bound by the matrix cores and the reads that feed them.  8192 tokens x 4096
-// channels: bf16 0.25 ms (0.55 PFLOP/s; 64 x 64 tiles of 32 x 32 a wavefront
-// staged through registers: 0.41), fp32 1.0 ms (the fp32 instruction: 1.45).
+// Work: 128 x 128 tiles, 128 x 64 and 64 x 64 ones (Split below), each with its fp64
+// sums of 256-token partial sums in registers.  Bound by the matrix cores and the
+// reads that feed them.  8192 tokens x 4096 channels: bf16 0.25 ms (0.55 PFLOP/s;
+// 64 x 64 tiles staged through registers: 0.41), fp32 1.0 ms (the fp32
+// instruction: 1.45).
 #include "bf16x3.h"
 #include "token_spans.h"
 
@@ -32,24 +26,27 @@ namespace jarq {
 
 namespace {
 // The tiles of one launch: `big` 128 x 128 tiles (of the strict upper triangle,
-// or of the full grid for the cross term), then 64 x 64 tiles: the three of
-// each diagonal tile (symmetric), and the four of each of the last `cut` big
-// ones.  `slots` big tiles run at a time; where the last round of them would
-// leave more than half of the chip idle, its tiles are cut into quarters,
-// which start as soon as anything ends.
+// or of the full grid for the cross term), then smaller ones: the three 64 x 64 of
+// each diagonal tile (symmetric), and each of the last `cut` big ones in `parts`
+// parts, two of 128 x 64 or four of 64 x 64.
 struct Split {
   int nt;       // 128-wide tiles per side
-  int big, cut, small;
+  int big, cut, parts, small;
 };
-Split split_of(int d, bool sym, int slots) {
+Split split_of(int d, bool sym) {
   Split s;
   s.nt = (d + 127) / 128;
-  const int all = sym ? s.nt * (s.nt - 1) / 2 : s.nt * s.nt;
-  const int last = all % slots;
-  s.cut = last < slots / 2 ? last : 0;
-  s.big = all - s.cut;
-  s.small = 4 * s.cut + (sym ? 3 * s.nt : 0);
+  s.big = sym ? s.nt * (s.nt - 1) / 2 : s.nt * s.nt;
+  s.cut = 0;
+  s.parts = 4;
+  s.small = sym ? 3 * s.nt : 0;
   return s;
+}
+void cut_last(Split& s, int cut, int parts) {
+  s.big -= cut;
+  s.cut = cut;
+  s.parts = parts;
+  s.small += parts * cut;
 }
 
 // Tile `id` of the strict upper triangle, row by row.
@@ -63,9 +60,10 @@ __device__ __forceinline__ void upper_tile(int id, int nt, int& ta, int& tb) {
   tb = ta + 1 + id - start(ta);
 }
 
-// Origin of the work-group's tile: a 128-wide one (returns true) or a 64-wide one.
+// Origin of the work-group's tile and its edges.
+enum Tile { kWhole, kHalf, kQuarter };   // 128 x 128, 128 x 64, 64 x 64
 template <bool CROSS>
-__device__ __forceinline__ bool tile_of(int id, const Split& s, int& a0, int& b0) {
+__device__ __forceinline__ Tile tile_of(int id, const Split& s, int& a0, int& b0) {
   int ta, tb;
   auto big_tile = [&](int t) {
     if (CROSS) {
@@ -74,26 +72,26 @@ __device__ __forceinline__ bool tile_of(int id, const Split& s, int& a0, int& b0
     } else {
       upper_tile(t, s.nt, ta, tb);
     }
+    a0 = 128 * ta;
+    b0 = 128 * tb;
   };
   if (id < s.big) {
     big_tile(id);
-    a0 = 128 * ta;
-    b0 = 128 * tb;
-    return true;
+    return kWhole;
   }
   id -= s.big;
-  int q;
-  if (id < 4 * s.cut) {
-    big_tile(s.big + id / 4);
-    q = id % 4;
-  } else {
-    id -= 4 * s.cut;
-    ta = tb = id / 3;
-    q = id % 3 == 2 ? 3 : id % 3;   // (0, 0), (0, 1), (1, 1)
+  if (id < s.parts * s.cut) {
+    big_tile(s.big + id / s.parts);
+    const int q = id % s.parts;
+    b0 += 64 * (q & 1);
+    a0 += 64 * (q >> 1);
+    return s.parts == 2 ? kHalf : kQuarter;
   }
-  a0 = 128 * ta + 64 * (q >> 1);
-  b0 = 128 * tb + 64 * (q & 1);
-  return false;
+  id -= s.parts * s.cut;
+  const int q = id % 3;   // (0, 0), (0, 1), (1, 1)
+  a0 = 128 * (id / 3) + 64 * (q >> 1);
+  b0 = 128 * (id / 3) + 64 * (q > 0);
+  return kQuarter;
 }
 
 // Adds alpha sum to the accumulator at the 32 x 32 block (a0, b0): element v
@@ -279,7 +277,7 @@ __device__ __forceinline__ void syrk_bf16_tile(const __bf16* __restrict__ X, int
   }
   flush();
   // a part of its own for each wave (the stages are done with)
-  double* out = (double*)buf0 + wave * 32 * 33;
+  double* out = (double*)(wave < 2 ? buf0 : buf1) + (wave & 1) * 32 * 33;
 #pragma unroll
   for (int a = 0; a < AB; ++a)
 #pragma unroll
@@ -288,34 +286,60 @@ __device__ __forceinline__ void syrk_bf16_tile(const __bf16* __restrict__ X, int
                        out);
 }
 
-__global__ __launch_bounds__(256, 2) void syrk_bf16_kernel(const __bf16* __restrict__ X, int m,
-                                                           int d, double alpha,
-                                                           double* __restrict__ Hacc, Split s) {
+// WHOLE: 128-wide tiles among them (their 128 registers of fp64 sums leave 220
+// bytes a lane in scratch: in the epilogue, once a tile, but for one pair around
+// each 256-token addition); otherwise 64-wide ones alone, whose stages leave room
+// for four work-groups on a CU.
+template <bool WHOLE>
+__global__ __launch_bounds__(256, WHOLE ? 2 : 4) void syrk_bf16_kernel(
+    const __bf16* __restrict__ X, int m, int d, double alpha, double* __restrict__ Hacc, Split s) {
+  constexpr int STAGE = 2 * BCH * (WHOLE ? 256 : 128);     // bytes
+  constexpr int OUT = 2 * 32 * 33 * sizeof(double);        // two wavefronts' blocks
+  constexpr int BUF = STAGE > OUT ? STAGE : (OUT + 1023) / 1024 * 1024;
   // two arrays, so that the compiler can tell which one a load in flight writes
-  __shared__ __attribute__((aligned(1024))) char buf0[2 * BCH * 256 + 1024];
-  __shared__ __attribute__((aligned(1024))) char buf1[2 * BCH * 256];
-  static_assert(sizeof(buf0) >= 4 * 32 * 33 * sizeof(double), "blocks stored through buf0");
+  __shared__ __attribute__((aligned(1024))) char buf0[BUF];
+  __shared__ __attribute__((aligned(1024))) char buf1[BUF];
   int a0, b0;
-  if (tile_of<false>(blockIdx.x, s, a0, b0))
-    syrk_bf16_tile<true>(X, m, d, alpha, Hacc, a0, b0, buf0, buf1);
-  else if (a0 < d && b0 < d)   // uniform
-    syrk_bf16_tile<false>(X, m, d, alpha, Hacc, a0, b0, buf0, buf1);
+  const Tile tile = tile_of<false>(blockIdx.x, s, a0, b0);   // uniform
+  if constexpr (WHOLE) {
+    if (tile == kWhole) {
+      syrk_bf16_tile<true>(X, m, d, alpha, Hacc, a0, b0, buf0, buf1);
+      return;
+    }
+  }
+  if (a0 < d && b0 < d) syrk_bf16_tile<false>(X, m, d, alpha, Hacc, a0, b0, buf0, buf1);
 }
 
+// 64-wide tiles alone below 256 128-wide ones (each would have a CU to itself;
+// 4096 tokens x 2048 channels, 120 of them: 46 us, whole 79, cut but with the
+// stages of the whole ones 75; x 2816, 231 of them: 64, 81 and 81); beyond, the last
+// round of 128-wide ones (512 at a time, two on a CU) is cut where it would leave
+// more than half of the chip idle (x 6144, 104 left over: 320, whole 326; x 3072,
+// 276 of them: 91, all cut 115).
 hipError_t launch_hessian_update_bf16(hipStream_t st, const void* X, int m, int d, double alpha,
                                       double* Hacc) {
-  const Split s = split_of(d, true, 512);   // two work-groups per CU
-  hipLaunchKernelGGL(syrk_bf16_kernel, dim3(s.big + s.small), dim3(256), 0, st, (const __bf16*)X,
-                     m, d, alpha, Hacc, s);
+  Split s = split_of(d, true);
+  const int last = s.big % 512;
+  if (last < 256) cut_last(s, last, 4);
+  if (s.big == 0)
+    hipLaunchKernelGGL(syrk_bf16_kernel<false>, dim3(s.small), dim3(256), 0, st, (const __bf16*)X,
+                       m, d, alpha, Hacc, s);
+  else
+    hipLaunchKernelGGL(syrk_bf16_kernel<true>, dim3(s.big + s.small), dim3(256), 0, st,
+                       (const __bf16*)X, m, d, alpha, Hacc, s);
   return hipGetLastError();
 }
 
 // ---- fp32 inputs ----
-// 512 threads.  Big tile: 2 x 4 wavefronts of 64 x 32, chunks of 32 tokens;
-// small tile: 2 x 2 wavefronts of 32 x 32 twice, chunks of 64 tokens, the
-// second four wavefronts taking the odd k-slices (their sums are added to the
-// first four's at the end).  A thread stages 8 tokens x 2 channels; two LDS
-// stages of three planes; one work-group per CU.
+// 512 threads.  128 x 128: 2 x 4 wavefronts of 64 x 32, chunks of 32 tokens;
+// 128 x 64: 4 x 2 wavefronts of 32 x 32, the same chunks; 64 x 64: 2 x 2 wavefronts
+// of 32 x 32 twice, chunks of 64 tokens, the second four wavefronts taking the odd
+// k-slices (their sums are added to the first four's at the end).  A thread
+// stages 8 tokens x 2 channels and converts them to the planes; two LDS stages
+// of three planes; one work-group per CU.  The planes lie channel-major (a row per
+// channel, tokens along it), so a fragment (32 channels x 16 tokens) is one
+// 16-byte read a lane; rows are padded by 16 bytes, which puts the 16 rows of a
+// read, and the 16 chunks of a write, in distinct banks.
 //
 // The tile's sums with the fp32 instruction straight from memory (one wave,
 // blocks of 32 x 32): for the tiles the three planes cannot do.
@@ -345,34 +369,38 @@ __device__ __forceinline__ void syrk_f32_slow(const float* __restrict__ Xq,
   }
 }
 
-template <bool CROSS, bool BIG>
+template <bool CROSS, int TA, int TB>
 __device__ __forceinline__ void syrk_f32_tile(const float* __restrict__ Xq,
                                               const float* __restrict__ X, int m, int d,
                                               double alpha, double* __restrict__ Hacc, int a0,
                                               int b0, char* smem) {
-  constexpr int TE = BIG ? 128 : 64;
-  constexpr int CH = BIG ? 32 : 64;           // tokens per chunk
+  constexpr bool TWICE = TA == 64;            // eight wavefronts on four blocks
+  constexpr int CH = TWICE ? 64 : 32;         // tokens per chunk
   constexpr int LD = 2 * CH + 16;             // row stride in bytes
-  constexpr int PLANE = 2 * TE * LD;          // A rows, then B rows
+  constexpr int PLANE = (TA + TB) * LD;       // A rows, then B rows
   constexpr int STAGE = 3 * PLANE;
-  constexpr int AB = BIG ? 2 : 1;             // 32-row blocks per wavefront
+  constexpr int WN = TB / 32;                 // wavefronts along the columns
+  constexpr int AB = TA * TB == 128 * 128 ? 2 : 1;   // 32-row blocks per wavefront
   constexpr int FLUSH = kSumTokens / CH;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = BIG ? wave >> 2 : (wave >> 1) & 1, wn = BIG ? wave & 3 : wave & 1;
-  const int wk = BIG ? 0 : wave >> 2;         // first k-slice (small tile: every second one)
+  const int wm = wave / WN % (TA / (32 * AB)), wn = wave % WN;
+  const int wk = TWICE ? wave >> 2 : 0;       // first k-slice (64 x 64: every second one)
   const int lm = lane & 31, kh = lane >> 5;
   // staging: 8 tokens at 8 tg, 2 channels from tile row r2
-  constexpr int TGB = BIG ? 1 : 2;            // token-group bits taken from the wave
+  constexpr int TGB = TWICE ? 2 : 1;          // token-group bits taken from the wave
   const int tg = (lane & 1) + 2 * (wave & ((1 << TGB) - 1));
   const int r2 = 64 * (wave >> TGB) + 2 * (lane >> 1);
-  const bool is_b = r2 >= TE;
-  const int ch = is_b ? b0 + r2 - TE : a0 + r2;
+  // (128 x 64: six wavefronts stage; uniform in a wave, as is_b)
+  const bool stages = TA == TB || r2 < TA + TB;
+  const bool is_b = r2 >= TA;
+  const int ch = is_b ? b0 + r2 - TA : a0 + r2;
   const bool in_ch = ch < d;                  // d is even
   // 32-bit byte offsets from the chunk's first token
   const uint32_t row = 4u * (uint32_t)d, c4 = 4u * (uint32_t)(in_ch ? ch : 0);
   // raw values: they are first touched when they are stored, a chunk later
   float2 st[8], sx[CROSS ? 8 : 1];
   auto load = [&](int t0) {
+    if (!stages) return;
     const int last = m - 1 - t0;   // tokens past m read the last one
     const char* bq = (const char*)(Xq + (size_t)t0 * d);
     const char* bx = (const char*)(X + (size_t)t0 * d);
@@ -387,6 +415,7 @@ __device__ __forceinline__ void syrk_f32_tile(const float* __restrict__ Xq,
     }
   };
   auto store = [&](int t0, char* stage) {
+    if (!stages) return;
     if constexpr (CROSS) {
       if (is_b) {
 #pragma unroll
@@ -440,10 +469,10 @@ __device__ __forceinline__ void syrk_f32_tile(const float* __restrict__ Xq,
     const char* cur = smem + (q & 1) * STAGE;
     if (q + 1 < nch) load((q + 1) * CH);   // in flight during this chunk
     const char* ra = cur + (wm * 32 * AB + lm) * LD + 16 * kh;
-    const char* rb = cur + (TE + wn * 32 + lm) * LD + 16 * kh;
+    const char* rb = cur + (TA + wn * 32 + lm) * LD + 16 * kh;
 #pragma unroll
-    for (int k2 = 0; k2 < (BIG ? CH / 16 : CH / 32); ++k2) {
-      const int ks = BIG ? k2 : 2 * k2 + wk;
+    for (int k2 = 0; k2 < 2; ++k2) {
+      const int ks = TWICE ? 2 * k2 + wk : k2;
       bf16x8 fb[3], fa[AB][3];
 #pragma unroll
       for (int p = 0; p < 3; ++p) fb[p] = *(const bf16x8*)(rb + p * PLANE + 32 * ks);
@@ -460,7 +489,7 @@ __device__ __forceinline__ void syrk_f32_tile(const float* __restrict__ Xq,
     __syncthreads();
   }
   flush();
-  if (!BIG) {
+  if (TWICE) {
     // the second four wavefronts hand their sums to the first four
     double* red = (double*)smem + (wave & 3) * 1024;
     if (wk == 1) {
@@ -473,7 +502,7 @@ __device__ __forceinline__ void syrk_f32_tile(const float* __restrict__ Xq,
     for (int v = 0; v < 16; ++v) sum[0][v] += red[64 * v + lane];
   }
   // a part of its own for each wave, apart from the sums above
-  double* buf = (double*)smem + (BIG ? wave * 32 * 33 : 4096 + (wave & 3) * 32 * 33);
+  double* buf = (double*)smem + (TWICE ? 4096 + (wave & 3) * 32 * 33 : wave * 32 * 33);
 #pragma unroll
   for (int a = 0; a < AB; ++a) {
     const int ba = a0 + 32 * (AB * wm + a), bb = b0 + 32 * wn;
@@ -492,17 +521,35 @@ __global__ __launch_bounds__(512, 1) void syrk_f32_kernel(const float* __restric
                                                           double* __restrict__ Hacc, Split s) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
   int a0, b0;
-  if (tile_of<CROSS>(blockIdx.x, s, a0, b0))
-    syrk_f32_tile<CROSS, true>(Xq, X, m, d, alpha, Hacc, a0, b0, smem);
-  else if (a0 < d && b0 < d)   // uniform
-    syrk_f32_tile<CROSS, false>(Xq, X, m, d, alpha, Hacc, a0, b0, smem);
+  const Tile tile = tile_of<CROSS>(blockIdx.x, s, a0, b0);   // uniform
+  if (tile == kWhole)
+    syrk_f32_tile<CROSS, 128, 128>(Xq, X, m, d, alpha, Hacc, a0, b0, smem);
+  else if (a0 >= d || b0 >= d)
+    return;
+  else if (tile == kHalf)
+    syrk_f32_tile<CROSS, 128, 64>(Xq, X, m, d, alpha, Hacc, a0, b0, smem);
+  else
+    syrk_f32_tile<CROSS, 64, 64>(Xq, X, m, d, alpha, Hacc, a0, b0, smem);
 }
 
 template <bool CROSS>
 static hipError_t launch_syrk_f32(hipStream_t st, const float* Xq, const float* X, int m, int d,
                                   double alpha, double* Hacc) {
-  const Split s = split_of(d, !CROSS, 256);   // one work-group per CU
-  // big tile: 2 stages x 3 planes x 256 rows of 80 bytes; small: 128 rows of 144
+  // The last round of whole tiles (256 at a time, one on a CU) whole, in halves or
+  // in quarters, whichever takes the least time together with the diagonal's
+  // quarters: a round of whole tiles takes 2.2 times, one of halves 1.7 times as
+  // long as one of quarters (4096 tokens: 221, 168 and 98 us; cross term 262, 202 and
+  // 127).  66 whole tiles (1536 channels) 220, 168 and 197 us, 120 of them (2048) 221 in
+  // one round, 293 in three of quarters, 20 left over (3072) 446 whole and 328.
+  Split s = split_of(d, !CROSS);
+  const int last = s.big % 256;
+  auto rounds = [&](int parts) { return (parts * last + s.small + 255) / 256; };
+  const double whole = 2.2, half = 1.7 * rounds(2), quarter = rounds(4);
+  if (quarter <= half && quarter < whole)
+    cut_last(s, last, 4);
+  else if (half < whole)
+    cut_last(s, last, 2);
+  // whole: 2 stages x 3 planes x 256 rows of 80 bytes; quarter: 128 rows of 144
   constexpr size_t lds = 2 * 3 * 256 * 80;
   static_assert(lds >= 2 * 3 * 128 * 144 && lds >= (4096 + 4 * 32 * 33) * sizeof(double), "LDS");
   static std::atomic<unsigned long long> lds_set{0};

@@ -399,3 +399,42 @@ def test_dequantize_permuted_rows(rows, cols, dtype):
     live = (order >= 0) & (order < cols)
     ref[:, order[live]] = torch.from_numpy(w[:, live]).to(dtype)
     assert torch.equal(out.cpu(), ref)
+
+
+# the last round of 128-wide tiles whole, in halves and in quarters; bf16: 64-wide
+# tiles alone, and whole ones with a last round cut and not
+@pytest.mark.parametrize("d,dtype", [(1440, torch.float32), (1928, torch.float32),
+                                     (2824, torch.float32), (2816, torch.bfloat16),
+                                     (3080, torch.bfloat16), (4168, torch.bfloat16)])
+def test_hessian_splits(d, dtype):
+    m = 300
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(d)
+    X = torch.randn(m, d, generator=gen, device="cuda").to(dtype)
+    H = torch.zeros(d, d, device="cuda", dtype=torch.float64)
+    jb.hessian_accumulate(X, H, 1.0)
+    assert torch.equal(H, H.t())
+    bound = 257 * 2.0 ** -24 * _hess64(X.abs()) + 1e-300
+    assert bool(((H - _hess64(X)).abs() <= bound).all())
+
+
+@pytest.mark.parametrize("d", [1000, 1096, 1416, 1480, 2312])
+def test_cross_splits(d):
+    m = 300
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(d)
+    X = torch.randn(m, d, generator=gen, device="cuda")
+    Xq = X + 0.1 * torch.randn(m, d, generator=gen, device="cuda")
+    D = torch.zeros(d, d, device="cuda", dtype=torch.float64)
+    jb.cross_accumulate(Xq, X, D, 1.0)
+    diff = (X - Xq).double()
+    bound = 257 * 2.0 ** -24 * (Xq.double().abs().t().contiguous() @ diff.abs()) + 1e-300
+    assert bool(((D - Xq.double().t().contiguous() @ diff).abs() <= bound).all())
+    # an infinity: that channel's rows alone
+    Xq[3, 5] = float("inf")
+    E = torch.zeros(d, d, device="cuda", dtype=torch.float64)
+    jb.cross_accumulate(Xq, X, E, 1.0)
+    keep = torch.arange(d, device="cuda") != 5
+    assert not bool(torch.isfinite(E[5]).any()) and not bool(torch.isfinite(E[:, 5]).any())
+    some = keep[:, None] & keep[None, :]
+    assert bool(((E - D).abs() <= 2 * bound)[some].all())
