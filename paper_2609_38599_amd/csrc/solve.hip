@@ -8,10 +8,11 @@
 // row of the system per lane (two for G > 64), its columns are eliminated
 // there, and the blocks right of it are updated on the fp64 matrix cores.
 // Bound by the chain of columns and, beside it, the fp64 units; 32 to 128
-// systems of a sweep's rows a CU hide it.  14336 rows of G = 64: 216 us (the
+// systems of a sweep's rows a CU hide it.  14336 rows of G = 64: 226 us (the
 // matrix in 4 x 4 register tiles spread over the lanes, updated on the vector
-// units: 510); 4096 rows of G = 32: 29 us (a row per lane: 34); 4096 of G = 128
-// with their Gram matrices: 1.74 ms (in LDS, two wavefronts a row: 7.85).
+// units: 551); 4096 rows of G = 32: 28 us (a row per lane: 33), of G = 88: 211 (411),
+// of G = 128 0.88 ms (in LDS, two wavefronts a row: 7.0).  For G > 80 the blocks
+// do not all fit: T = 6, 7 and 8 keep 16, 200 and 560 bytes a lane in scratch.
 // The stabilised branch of
 // App. E.2 (add lambda I and factor again) is taken when an entry is not
 // finite, a pivot is not positive, the smallest pivot is at most
@@ -105,11 +106,18 @@ struct Panels {
 // rows and columns from G to 16 T are zero but for a diagonal of kPadPivot, large
 // enough never to be the smallest pivot.
 //
-// LDS: panel p holds rows 16 p .. 16 T - 1 of its 16 columns, kSolveLd doubles a
-// row (17: the 16 rows and the k-pairs of a fragment read cover the 64 banks
-// once), first the Schur complement's columns, then L's, which stay there for
-// the backward substitution; then two buffers for the column exchange.  One
-// wavefront: its LDS accesses complete in order, so there is no barrier; the
+// LDS.  Rows are kSolveLd doubles (17: the 16 rows and the k-pairs of a fragment
+// read cover the 64 banks once), first of the Schur complement's columns, then of
+// L's, which stay there for the backward substitution.  Panel p's rows from its
+// diagonal ones on, then the column exchange; or PACKED, where that puts more
+// systems on a CU (T = 4: eight for seven, T = 6: four for three) or leaves fewer
+// registers in scratch (T = 8): one block of 16 diagonal rows, used by every panel
+// in turn and then by its column exchange; panel p's rows below them; L's strict
+// lower triangles of the diagonal rows, packed row by row, 120 a panel.  4096 rows,
+// not packed and packed: G = 64 82 and 70 us, 88 389 and 211, 128 991 and 879; where
+// it changes neither, packing costs its writes (G = 32 31 and 32, 80 166 and 175, 104
+// 645 and 683).
+// One wavefront: its LDS accesses complete in order, so there is no barrier; the
 // empty asm statements keep the compiler from moving a read above another
 // lane's write.
 constexpr int kSolveLd = 17;
@@ -118,13 +126,25 @@ template <int T>
 struct SolveShape {
   static constexpr int NS = T > 4 ? 2 : 1;        // rows of the system per lane
   static constexpr int NBLK = T * (T + 1) / 2;
-  // first element of panel p
-  static __host__ __device__ constexpr int off(int p) { return 16 * kSolveLd * (p * T - p * (p - 1) / 2); }
-  static constexpr size_t lds_bytes() { return (size_t)(off(T) + 2 * 64) * sizeof(double); }
+  static constexpr bool PACKED = T == 4 || T == 6 || T == 8;
+  static constexpr int kRows = 16 * kSolveLd;     // 16 rows
+  // diagonal rows of panel p, and its rows from 16 (p + 1) on
+  static __host__ __device__ constexpr int diag(int p) {
+    return PACKED ? 0 : kRows * (p * T - p * (p - 1) / 2);
+  }
+  static __host__ __device__ constexpr int below(int p) {
+    return PACKED ? kRows * (1 + p * (T - 1) - p * (p - 1) / 2) : diag(p) + kRows;
+  }
+  static constexpr int kEnd = PACKED ? below(T) : diag(T);   // the triangles, or the exchange
+  // (a backward step reads up to 15 entries past a triangle's row)
+  static constexpr size_t lds_bytes() {
+    return (size_t)(kEnd + (PACKED ? 120 * T + 16 : 128)) * sizeof(double);
+  }
 };
+static_assert(4 * SolveShape<6>::lds_bytes() <= 160 * 1024, "four systems a CU");
 
 template <int T>
-__global__ __launch_bounds__(64, T > 4 ? 1 : 2) void solve_kernel(
+__global__ __launch_bounds__(64, T > 4 ? 1 : T > 2 ? 2 : 4) void solve_kernel(
     int rows, int cols, int g, const float* __restrict__ gram, const RhsSrc rs,
     float* __restrict__ scales, const uint8_t* __restrict__ active, Counters* __restrict__ cnt,
     Flags* __restrict__ flags, float lam, float rcond, int accept,
@@ -139,7 +159,6 @@ __global__ __launch_bounds__(64, T > 4 ? 1 : 2) void solve_kernel(
   if (active != nullptr && !active[grow]) return;
   const int lane = threadIdx.x, lc = lane & 15, lk = lane >> 4;
   extern __shared__ double sm[];
-  double* colb = sm + S::off(T);
 
   // ---- right-hand side r_i = sum over group i of (q - z) (W H) ----
   const bool cached = rs.ctl != nullptr && rs.ctl->valid != 0;   // uniform
@@ -225,7 +244,10 @@ __global__ __launch_bounds__(64, T > 4 ? 1 : 2) void solve_kernel(
     Panels<0, T>::run([&](auto pc) __attribute__((always_inline)) {
       constexpr int p = decltype(pc)::value;
       constexpr int c0 = 16 * p, sp = c0 / 64, l0 = c0 % 64;   // slot and lane of its first row
-      double* L = sm + S::off(p);
+      constexpr int below = 16 * (T - p - 1);
+      double* dg = sm + S::diag(p);
+      double* L = sm + S::below(p);
+      double* colb = S::PACKED ? dg : sm + S::kEnd;   // (the diagonal rows are in registers then)
       // (an opaque copy, so that the comparisons below are made here and not
       // kept for every panel across the passes)
       int ln = lane;
@@ -234,7 +256,8 @@ __global__ __launch_bounds__(64, T > 4 ? 1 : 2) void solve_kernel(
       for (int bi = p; bi < T; ++bi)
 #pragma unroll
         for (int v = 0; v < 4; ++v)
-          L[(16 * (bi - p) + lc) * kSolveLd + 4 * v + lk] = blk[bi * (bi + 1) / 2 + p][v];
+          (bi == p ? dg : L + 16 * (bi - p - 1) * kSolveLd)[lc * kSolveLd + 4 * v + lk] =
+              blk[bi * (bi + 1) / 2 + p][v];
       asm volatile("" ::: "memory");
       double a[NS][16], t[16], lp[NS];
       double* lrow[NS];
@@ -242,8 +265,9 @@ __global__ __launch_bounds__(64, T > 4 ? 1 : 2) void solve_kernel(
       auto slots = [&](auto&& fn) __attribute__((always_inline)) { Panels<sp, NS>::run(fn); };
       slots([&](auto sc) __attribute__((always_inline)) {
         constexpr int s = decltype(sc)::value;
-        const int i = ln + 64 * s;   // rows above the panel repeat its first, rows past it the last
-        lrow[s] = L + min(max(i - c0, 0), 16 * (T - p) - 1) * kSolveLd;
+        const int i = ln + 64 * s - c0;   // rows above the panel repeat its first, rows past it the last
+        lrow[s] = i < 16 || below == 0 ? dg + min(max(i, 0), 15) * kSolveLd
+                                       : L + min(i - 16, below - 1) * kSolveLd;
 #pragma unroll
         for (int k = 0; k < 16; ++k) a[s][k] = lrow[s][k];
       });
@@ -251,6 +275,8 @@ __global__ __launch_bounds__(64, T > 4 ? 1 : 2) void solve_kernel(
       Panels<0, 16>::run([&](auto kc) __attribute__((always_inline)) {
         constexpr int k = decltype(kc)::value;
         constexpr int kn = k < 15 ? k + 1 : 15;
+        // columns from G on change nothing (uniform)
+        if (p == T - 1 && c0 + k >= G) return;
         asm volatile("" : "+v"(ln));
         const double pk = readlane_f64(a[sp][k], l0 + k);
         const bool b = !(pk > 0.0 && pk < INFINITY);
@@ -295,10 +321,16 @@ __global__ __launch_bounds__(64, T > 4 ? 1 : 2) void solve_kernel(
       }
       slots([&](auto sc) __attribute__((always_inline)) {
         constexpr int s = decltype(sc)::value;
-        const int i = ln + 64 * s;
-        if (i >= c0 && i < 16 * T) {
+        const int i = ln + 64 * s - c0;
+        if (i >= (S::PACKED ? 16 : 0) && i < 16 + below) {
 #pragma unroll
           for (int k = 0; k < 16; ++k) lrow[s][k] = a[s][k];
+        }
+        if constexpr (S::PACKED && s == sp) {
+          double* tri = sm + S::kEnd + 120 * p + i * (i - 1) / 2;
+#pragma unroll
+          for (int k = 0; k < 15; ++k)
+            if (i > k && i < 16) tri[k] = a[s][k];
         }
       });
       asm volatile("" ::: "memory");
@@ -309,7 +341,7 @@ __global__ __launch_bounds__(64, T > 4 ? 1 : 2) void solve_kernel(
         for (int b = p + 1; b < T; ++b)
 #pragma unroll
           for (int ks = 0; ks < 4; ++ks)
-            f[b - p - 1][ks] = L[(16 * (b - p) + lc) * kSolveLd + 4 * ks + lk];
+            f[b - p - 1][ks] = L[(16 * (b - p - 1) + lc) * kSolveLd + 4 * ks + lk];
 #pragma unroll
         for (int ks = 0; ks < 4; ++ks)
 #pragma unroll
@@ -365,22 +397,28 @@ __global__ __launch_bounds__(64, T > 4 ? 1 : 2) void solve_kernel(
   }
 
   // ---- backward substitution L^T s = y: s_k = y_k / l_kk, y_i -= l_ki s_k ----
-  {
-    // L(k, i) of lane i: panel i / 16, its row k
+  // Step k of panel pk = k / 16: lane i finds L(k, i) in row k of panel i / 16, or
+  // (packed) in the triangle of panel pk if that is its own.  Lanes of later
+  // panels read something of theirs, unused.
+  for (int pk = T - 1; pk >= 0; --pk) {
     const double* li[NS];
+    bool own[NS];
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
       const int i = min(lane + 64 * s, 16 * T - 1), p = i >> 4;
-      li[s] = sm + 16 * kSolveLd * (p * T - p * (p - 1) / 2) - 16 * p * kSolveLd + (i & 15);
+      own[s] = S::PACKED && p >= pk;
+      li[s] = sm + (i & 15) +
+              (own[s] ? S::kEnd + 120 * p
+                      : S::below(p) + S::kRows * (S::PACKED ? pk - p - 1 : max(pk - p, 0) - 1));
     }
-    for (int k = G - 1; k >= 0; --k) {
+    for (int kr = min(15, G - 1 - 16 * pk); kr >= 0; --kr) {
+      const int k = 16 * pk + kr;
       const double y = NS == 1 || k < 64 ? rr[0] * rs_own[0] : rr[NS - 1] * rs_own[NS - 1];
       const double sk = readlane_f64(y, k & 63);
 #pragma unroll
       for (int s = 0; s < NS; ++s) {
         const int i = lane + 64 * s;
-        // (lanes at or past k read their own panel's first row instead)
-        const double l = li[s][kSolveLd * (i < k ? k : min(i, 16 * T - 1))];
+        const double l = li[s][own[s] ? kr * (kr - 1) / 2 : kr * kSolveLd];
         rr[s] = i < k ? fma(-l, sk, rr[s]) : (i == k ? sk : rr[s]);
       }
     }

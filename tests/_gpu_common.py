@@ -106,14 +106,14 @@ class GpuLayer:
         return out.cpu().numpy()
 
 
-def check_scales(s_gpu, s_ref, label=""):
+def check_scales(s_gpu, s_ref, label="", rtol=SCALE_RTOL):
     s_gpu = np.asarray(s_gpu, np.float64)
     s_ref = np.asarray(s_ref, np.float64)
     rms = np.sqrt(np.mean(s_ref * s_ref, axis=1, keepdims=True))
-    tol = SCALE_RTOL * np.maximum(np.abs(s_ref), SCALE_FLOOR * rms)
+    tol = rtol * np.maximum(np.abs(s_ref), SCALE_FLOOR * rms)
     err = np.abs(s_gpu - s_ref)
-    worst = float(np.max(err / np.maximum(tol, 1e-300) * SCALE_RTOL))
-    say(f"[scales{label}] worst scaled error {worst:.3e} (bar {SCALE_RTOL:g})")
+    worst = float(np.max(err / np.maximum(tol, 1e-300) * rtol))
+    say(f"[scales{label}] worst scaled error {worst:.3e} (bar {rtol:g})")
     assert np.all(err <= tol), f"scales differ: worst {worst:.3e}"
 
 

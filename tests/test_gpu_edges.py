@@ -18,6 +18,11 @@ pytestmark = [pytest.mark.gpu,
               pytest.mark.skipif(not torch.cuda.is_available(), reason="needs a GPU")]
 
 
+# Scales of well-conditioned systems from fp32 Gram entries and W H: four times
+# the largest error over these layers (9.9e-7 of a scale, at G = 128)
+WELL_RTOL = 4e-6
+
+
 def _spd(d, seed):
     rng = np.random.default_rng(seed)
     X = rng.standard_normal((2 * d, d)) * (1.0 + 4.0 * (rng.random(d) < 0.05))
@@ -39,12 +44,13 @@ def test_scale_solve_sizes(G):
     _, sg = gk.state()
     ref, ridge = jarq.scale_step(W, H, q, z, g)
     assert not ridge.any()
-    check_scales(sg, ref, f" G={G}")
+    check_scales(sg, ref, f" G={G}", WELL_RTOL)
     g2 = GpuLayer(W, H, q, s, z, g, 3, sweeps=1)
     g2.ws.fill_(0xff)
     jq.prepare(g2.p, g2.W, g2.H, g2.ws)
     st = jq.sweeps(g2.p, g2.W, g2.H, g2.codes, g2.scales, g2.zeros, g2.ws)
     assert st["ridge_rows"][0] == 0
+    check_scales(g2.state()[1], ref, f" sweep G={G}", WELL_RTOL)
 
 
 # panels of 512 columns, their remainders, one and two row blocks a work-group
@@ -269,7 +275,7 @@ def test_small_and_large_tiles_agree(few, many, cols, g):
     (qa, sa), (qb, sb) = states
     assert np.array_equal(sa, sb[:few]) and np.array_equal(qa, qb[:few])
     s_ref, _ = jarq.scale_step(W[:few], H, q[:few], z[:few], g)
-    check_scales(sa, s_ref, f" few {few}")
+    check_scales(sa, s_ref, f" few {few}", WELL_RTOL)
 
 
 # the walk of a pair of groups in one part and in many, odd and even numbers of
@@ -287,7 +293,8 @@ def test_gram_walk_parts_agree(G):
         gk.scale_step()
         out.append(gk.state()[1])
     assert np.array_equal(out[0], out[1][:130])
-    check_scales(out[0], jarq.scale_step(W[:130], H, q[:130], z[:130], g)[0], f" G={G}")
+    check_scales(out[0], jarq.scale_step(W[:130], H, q[:130], z[:130], g)[0], f" G={G}",
+                 WELL_RTOL)
 
 
 def _scales_of(W, H, codes, zeros, g, bits=8):

@@ -343,12 +343,12 @@ def _near_singular_layer(rows, cols, g, kahan_rows, seed):
     return W, np.ascontiguousarray(H.astype(np.float32)), q, s, z
 
 
-@pytest.mark.parametrize("cols,g", [(512, 32), (1024, 32), (4608, 64), (3200, 32), (3840, 32)])
+# every number of 16-column panels of the solve, whole and short last ones
+@pytest.mark.parametrize("cols,g", [(512, 32), (1024, 32), (1312, 32), (1824, 32), (4608, 64),
+                                    (2880, 32), (3104, 32), (3200, 32), (3840, 32), (4096, 32)])
 def test_ridge_trigger_on_large_pivots_matches_oracle(cols, g):
-    # G = 16 and 32 (register solve, two rows per wavefront: rows 1 and 6
-    # share theirs with a well-conditioned row), 72 and 100 (tile solve), 120
-    # (LDS solve).  The pivot test alone would miss rows 1 and 6; the
-    # eigenvalue bound and the factorisation of A - t I must catch them.
+    # The pivot test alone would miss rows 1 and 6; the eigenvalue bound and
+    # the factorisation of A - t I must catch them.
     W, H, q, s, z = _near_singular_layer(8, cols, g, (1, 6), seed=cols)
     gl = GpuLayer(W, H, q, s, z, g, 3)
     gl.scale_step()
@@ -359,14 +359,17 @@ def test_ridge_trigger_on_large_pivots_matches_oracle(cols, g):
     g2 = GpuLayer(W, H, q, s, z, g, 3, sweeps=1)
     st = jq.sweeps(g2.p, g2.W, g2.H, g2.codes, g2.scales, g2.zeros, g2.ws)
     assert st["ridge_rows"][0] == 2
+    check_scales(g2.state()[1], s_ref, f" near-singular sweep G {cols // g}")
 
 
-@pytest.mark.parametrize("cols,g", [(256, 64), (4608, 64)])
+@pytest.mark.parametrize("cols,g", [(256, 64), (640, 32), (1312, 32), (1824, 32), (4608, 64),
+                                    (2880, 32), (3200, 32), (4096, 32)])
 def test_ridge_acceptance_matches_oracle(cols, g):
     # Rows 3 and 17 have a group at its zero point (rank-deficient B_j).  With H
     # scaled by 1e-8 the ridge term dominates and the ridge solution raises F_j:
     # ridge acceptance keeps those rows' scales; unscaled, it keeps the ridge
-    # solution.  G = 4 and G = 72 cover both solve kernels.
+    # solution.  G from 4 to 128: the Gram matrix is loaded again for the test of
+    # acceptance in every instance of the solve.
     W, H, q, s, z = random_layer(40, cols, g, 3, seed=5)
     q = q.copy()
     q[3, g:2 * g] = z[3, 1]
