@@ -99,7 +99,6 @@ __device__ __forceinline__ Tile tile_of(int id, const Split& s, int& a0, int& b0
 // product alpha * sum is rounded once and the new value stored at both
 // places (no contraction into an fma).  buf: 32 x 33 doubles of LDS of this
 // wave, through which the mirrored block is stored along rows.
-template <bool CROSS>
 __device__ __forceinline__ void add_block(double* __restrict__ Hacc, int d, double alpha, int a0,
                                           int b0, const double (&sum)[16], double* buf) {
 #pragma clang fp contract(off)
@@ -115,13 +114,11 @@ __device__ __forceinline__ void add_block(double* __restrict__ Hacc, int d, doub
 #pragma unroll
   for (int v = 0; v < 16; ++v) {
     const int a = a0 + 8 * (v / 4) + 4 * kh + (v % 4);
-    const bool in = b < d && a < d && (CROSS || a <= b);
     const double t = alpha * sum[v];
     const double now = old[v] + t;
-    if (in) Hacc[(size_t)a * d + b] = now;
-    if (!CROSS) buf[(a - a0) * 33 + lc] = now;
+    if (b < d && a <= b) Hacc[(size_t)a * d + b] = now;
+    buf[(a - a0) * 33 + lc] = now;
   }
-  if (CROSS) return;
   // (one wavefront: its LDS accesses complete in order)
   asm volatile("" ::: "memory");
 #pragma unroll
@@ -130,6 +127,33 @@ __device__ __forceinline__ void add_block(double* __restrict__ Hacc, int d, doub
     if (a0 + lc < b0 + i && b0 + i < d) Hacc[(size_t)(b0 + i) * d + a0 + lc] = buf[lc * 33 + i];
   }
   asm volatile("" ::: "memory");
+}
+
+// The same for the AB blocks from row a0 on of an accumulator that is not
+// symmetric, every load ahead of the stores (with few tokens a launch lasts as
+// long as these: 60 tokens x 4096 channels 63 us, block by block 69).
+template <int AB>
+__device__ __forceinline__ void add_blocks(double* __restrict__ Dacc, int d, double alpha, int a0,
+                                           int b0, const double (&sum)[AB][16]) {
+#pragma clang fp contract(off)
+  const int lane = threadIdx.x & 63, kh = lane >> 5;
+  const int b = b0 + (lane & 31);
+  double old[AB][16];
+#pragma unroll
+  for (int i = 0; i < AB; ++i)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      const int a = min(a0 + 32 * i + 8 * (v / 4) + 4 * kh + (v % 4), d - 1);
+      old[i][v] = Dacc[(size_t)a * d + min(b, d - 1)];
+    }
+#pragma unroll
+  for (int i = 0; i < AB; ++i)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      const int a = a0 + 32 * i + 8 * (v / 4) + 4 * kh + (v % 4);
+      const double t = alpha * sum[i][v];
+      if (a < d && b < d) Dacc[(size_t)a * d + b] = old[i][v] + t;
+    }
 }
 
 }  // namespace
@@ -282,7 +306,7 @@ __device__ __forceinline__ void syrk_bf16_tile(const __bf16* __restrict__ X, int
   for (int a = 0; a < AB; ++a)
 #pragma unroll
     for (int b = 0; b < AB; ++b)
-      add_block<false>(Hacc, d, alpha, a0 + 32 * (AB * wm + a), b0 + 32 * (AB * wn + b), sum[a][b],
+      add_block(Hacc, d, alpha, a0 + 32 * (AB * wm + a), b0 + 32 * (AB * wn + b), sum[a][b],
                        out);
 }
 
@@ -510,8 +534,9 @@ __device__ __forceinline__ void syrk_f32_tile(const float* __restrict__ Xq,
 #pragma unroll
     for (int v = 0; v < 16; ++v) fine &= isfinite(sum[a][v]);
     if (!__all(fine)) syrk_f32_slow<CROSS>(Xq, X, m, d, ba, bb, sum[a]);
-    add_block<CROSS>(Hacc, d, alpha, ba, bb, sum[a], buf);
+    if (!CROSS) add_block(Hacc, d, alpha, ba, bb, sum[a], buf);
   }
+  if constexpr (CROSS) add_blocks<AB>(Hacc, d, alpha, a0 + 32 * AB * wm, b0 + 32 * wn, sum);
 }
 
 template <bool CROSS>
