@@ -84,7 +84,7 @@ bool valid_params(const jarq_params* p) {
   if (p->rows < 1 || p->cols < 1) return false;
   if (p->group_size != 32 && p->group_size != 64 && p->group_size != 128) return false;
   if (p->cols % p->group_size != 0) return false;
-  if (p->cols / p->group_size > 128) return false;   // G x G fp64 solve must fit in LDS
+  if (p->cols / p->group_size > 128) return false;   // the scale solve holds two rows of the system a lane
   if (p->bits < 1 || p->bits > 8) return false;
   if (p->sweeps < 0 || p->sweeps > 4096) return false;
   if (!(p->ridge_lambda >= 0.f) || !isfinite(p->ridge_lambda)) return false;

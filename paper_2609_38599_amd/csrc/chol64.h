@@ -81,11 +81,10 @@ __device__ __forceinline__ void store_c(double* m, int r0, int c0, f64x4 c) {
   for (int v = 0; v < 4; ++v) m[(r0 + 4 * v + (l >> 4)) * kCholLd + c0 + (l & 15)] = c[v];
 }
 
-// A = L L^T in place for the n x n block (n a multiple of 16, at most 64; the
-// lower triangle is read; the diagonal blocks' upper parts are written as 0),
-// dinv[k] = 1 / L(k, k).  A pivot that is not positive and finite is replaced
-// by 1 and sets *fail.  col: 128 doubles of LDS scratch.  All 256 threads call
-// it; A is complete on return.
+// A = L L^T in place for the n x n block (n = 32 or 64; the lower triangle is
+// read; the diagonal blocks' upper parts are written as 0), dinv[k] = 1 / L(k, k).
+// A pivot that is not positive and finite is replaced by 1 and sets *fail.  col:
+// 128 doubles of LDS scratch.  All 256 threads call it; A is complete on return.
 //
 // Panel (one wavefront, lane = row): column k stays unscaled while it updates
 // the later ones, a_j -= (a_k / pivot) a_k[row j].  The chain from a pivot to
@@ -157,9 +156,9 @@ __device__ __forceinline__ void chol64_factor(double* A, int n, double* dinv, do
   }
 }
 
-// X = L^{-1} (lower triangle; the blocks above the diagonal blocks are not
-// written) from the factor chol64_factor left in L and dinv.  All 256 threads
-// call it; X is complete on return.
+// X = L^{-1} (n = 32 or 64; lower triangle; the blocks above the diagonal blocks
+// are not written) from the factor chol64_factor left in L and dinv.  All 256
+// threads call it; X is complete on return.
 __device__ __forceinline__ void chol64_invert(const double* L, int n, const double* dinv,
                                               double* X) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;

@@ -3,7 +3,8 @@
 // (H e)_i for every row and group, used in the coordinates of eq. (10)).
 // split3_kernel (three products of two-term planes of both operands) forms
 // the layer's fixed T = W M^T once per layer; resid_kernel (further below)
-// forms every sweep's U = T - What M^T with the exact q - z as one operand.
+// forms every sweep's U = T - What M^T with the exact q - z as one operand;
+// wh_kernel (at the end) forms W H of the scale update from three-term planes.
 //
 // Operands arrive as two-term fp16 planes with power-of-two scales (split.hip):
 // A = (Ah + Al) ra_m per row m, B(k, n) = Bt(n, k) with Bt = (Bh + Bl) rb_n per
@@ -14,8 +15,7 @@
 // i's columns of row j L_i^{-1} (H e_j)_i, the u of eq. (10) before division
 // by the scale.
 //
-// Epilogues: store C = A B, or subtract, C -= A B.  The objective that
-// follows the residual product is in objective.hip.
+// The objective that follows the residual product is in objective.hip.
 //
 // Tiling: 256 x BN output tile per 512-thread work-group, 2 x 4 waves of
 // 128 x BN/4 (two waves per SIMD, so one wave's waits are covered by the
@@ -72,7 +72,7 @@ __device__ __forceinline__ void dma16(const _Float16* src, _Float16* lds) {
 }
 }  // namespace
 
-template <int BN, int kMode>
+template <int BN>
 __global__ __launch_bounds__(512, 1) void split3_kernel(
     int M, int N, int K, int lda, int ldb, int ldc, const _Float16* __restrict__ Ah,
     const _Float16* __restrict__ Al, const float* __restrict__ arow_inv,
@@ -245,33 +245,16 @@ __global__ __launch_bounds__(512, 1) void split3_kernel(
     for (int b = 0; b < NB; ++b) {
       const int col = n0 + wn * WN + b * 32 + lm;
       const float cs = bcol_inv[min(col, N - 1)];
-      if (kMode == 1) {
-        // All loads of the block before its stores: the compiler cannot prove
-        // the addresses distinct and would otherwise serialise the round trips.
-        float old[16];
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const int row = rb0 + 8 * (v / 4) + (v % 4);
-          old[v] = C[(size_t)min(row, M - 1) * ldc + min(col, N - 1)];
-        }
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const int row = rb0 + 8 * (v / 4) + (v % 4);
-          if (row < M && col < N)
-            C[(size_t)row * ldc + col] = old[v] - acc[a][b][v] * (rsc[v] * cs);
-        }
-      } else {
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const int row = rb0 + 8 * (v / 4) + (v % 4);
-          if (row < M && col < N) C[(size_t)row * ldc + col] = acc[a][b][v] * (rsc[v] * cs);
-        }
+      for (int v = 0; v < 16; ++v) {
+        const int row = rb0 + 8 * (v / 4) + (v % 4);
+        if (row < M && col < N) C[(size_t)row * ldc + col] = acc[a][b][v] * (rsc[v] * cs);
       }
     }
   }
 }
 
-template <int BN, int kMode>
+template <int BN>
 static hipError_t launch_split3_t(hipStream_t st, int M, int N, int K, int lda, int ldb,
                                   int ldc, const _Float16* ah, const _Float16* al,
                                   const float* arow, const _Float16* bh, const _Float16* bl,
@@ -279,7 +262,7 @@ static hipError_t launch_split3_t(hipStream_t st, int M, int N, int K, int lda, 
   if (M <= 0 || N <= 0) return hipSuccess;
   if (K % BK != 0) return hipErrorInvalidValue;
   const int tiles = ((M + BM - 1) / BM) * ((N + BN - 1) / BN);
-  hipLaunchKernelGGL((split3_kernel<BN, kMode>), dim3(tiles), dim3(512), 0, st, M, N, K, lda, ldb,
+  hipLaunchKernelGGL((split3_kernel<BN>), dim3(tiles), dim3(512), 0, st, M, N, K, lda, ldb,
                      ldc, ah, al, arow, bh, bl, bcol, C, m_dev);
   return hipGetLastError();
 }
@@ -374,7 +357,7 @@ hipError_t launch_wm_product(hipStream_t st, int rows, int cols, const char* ws,
                        wlo, wrow_inv, bh, bl, bc, (float*)(ws + lay.tm));
     return hipGetLastError();
   }
-  return launch_split3_t<256, 0>(st, rows, cols, cols, cols, cols, cols, whi, wlo, wrow_inv, bh,
+  return launch_split3_t<256>(st, rows, cols, cols, cols, cols, cols, whi, wlo, wrow_inv, bh,
                                  bl, bc, (float*)(ws + lay.tm), nullptr);
 }
 

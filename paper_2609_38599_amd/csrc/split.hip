@@ -96,6 +96,7 @@ static int form_span(int cols, int g) {
   return span;
 }
 
+// (g = 128 keeps five registers a lane in scratch around the column loop.)
 template <int G_SIZE>
 __global__ __launch_bounds__(512) void form_m_kernel(const float* __restrict__ H, int cols,
                                                      const double* __restrict__ linv,
