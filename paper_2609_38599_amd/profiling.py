@@ -40,16 +40,18 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 def short_name(name: str) -> str:
     """Readable kernel name: the jarq:: function with its template arguments."""
-    m = re.match(r"_ZN4jarq\d+(\w+?)I((?:Li\d+E)+)E", name)
+    anon = r"(?:12_GLOBAL__N_1)?"
+    m = re.match(rf"_ZN4jarq{anon}\d+(\w+?)I((?:L[ib]\d+E)+)E", name)
     if m:
-        args = re.findall(r"Li(\d+)E", m.group(2))
+        args = [v if kind == "i" else ("false", "true")[int(v)]
+                for kind, v in re.findall(r"L([ib])(\d+)E", m.group(2))]
         return f"{m.group(1)}<{','.join(args)}>"
-    m = re.match(r"_ZN4jarq\d+(\w+?)E", name)
+    m = re.match(rf"_ZN4jarq{anon}\d+(\w+?)E", name)
     if m:
         return m.group(1)
-    m = re.match(r"(?:void )?jarq::(\w+)(<[^>]*>)?", name)
+    m = re.match(r"(?:void )?jarq::(?:\(anonymous namespace\)::)?(\w+)(<[^>]*>)?", name)
     if m:
-        return m.group(1) + (m.group(2) or "")
+        return m.group(1) + (m.group(2) or "").replace(", ", ",")
     return name[:48]
 
 

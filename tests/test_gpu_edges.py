@@ -260,7 +260,7 @@ def test_act_order_sizes(d):
     assert np.array_equal(perm, np.argsort(-diag, kind="stable"))
 
 
-# both tile sizes of the residual product and of W M~^T, at and beside the lines
+# both tile sizes of the residual product and of W M^T, at and beside the lines
 # between them, the same rows in a layer of either kind: the same bits
 @pytest.mark.parametrize("few,many,cols,g", [(63, 4100, 1024, 64), (65, 4097, 1056, 32),
                                              (300, 8200, 640, 128), (1000, 3841, 1536, 128)])
@@ -279,7 +279,7 @@ def test_small_and_large_tiles_agree(few, many, cols, g):
 
 
 # the walk of a pair of groups in one part and in many, odd and even numbers of
-# groups, and the span of M~'s formation: the same bits as in a layer of many rows
+# groups, and the span of M's formation: the same bits as in a layer of many rows
 @pytest.mark.parametrize("G", [1, 2, 3, 4, 5, 16, 31, 33, 64, 67])
 def test_gram_walk_parts_agree(G):
     g = 32
