@@ -310,7 +310,7 @@ __device__ __forceinline__ void syrk_bf16_tile(const __bf16* __restrict__ X, int
                        out);
 }
 
-// WHOLE: 128-wide tiles among them (their 128 registers of fp64 sums leave 220
+// WHOLE: 128-wide tiles among them (their 128 registers of fp64 sums leave 228
 // bytes a lane in scratch: in the epilogue, once a tile, but for one pair around
 // each 256-token addition); otherwise 64-wide ones alone, whose stages leave room
 // for four work-groups on a CU.
@@ -539,7 +539,9 @@ __device__ __forceinline__ void syrk_f32_tile(const float* __restrict__ Xq,
   if constexpr (CROSS) add_blocks<AB>(Hacc, d, alpha, a0 + 32 * AB * wm, b0 + 32 * wn, sum);
 }
 
-template <bool CROSS>
+// HALVES: 128 x 64 tiles among them (an instance of its own: their code in the
+// other one costs its whole tiles 2 % by the registers they get).
+template <bool CROSS, bool HALVES>
 __global__ __launch_bounds__(512, 1) void syrk_f32_kernel(const float* __restrict__ Xq,
                                                           const float* __restrict__ X, int m,
                                                           int d, double alpha,
@@ -547,14 +549,31 @@ __global__ __launch_bounds__(512, 1) void syrk_f32_kernel(const float* __restric
   extern __shared__ __attribute__((aligned(16))) char smem[];
   int a0, b0;
   const Tile tile = tile_of<CROSS>(blockIdx.x, s, a0, b0);   // uniform
-  if (tile == kWhole)
+  if (tile == kWhole) {
     syrk_f32_tile<CROSS, 128, 128>(Xq, X, m, d, alpha, Hacc, a0, b0, smem);
-  else if (a0 >= d || b0 >= d)
-    return;
-  else if (tile == kHalf)
-    syrk_f32_tile<CROSS, 128, 64>(Xq, X, m, d, alpha, Hacc, a0, b0, smem);
-  else
+  } else if (a0 < d && b0 < d) {
+    if constexpr (HALVES) {
+      if (tile == kHalf) {
+        syrk_f32_tile<CROSS, 128, 64>(Xq, X, m, d, alpha, Hacc, a0, b0, smem);
+        return;
+      }
+    }
     syrk_f32_tile<CROSS, 64, 64>(Xq, X, m, d, alpha, Hacc, a0, b0, smem);
+  }
+}
+
+template <bool CROSS, bool HALVES>
+static hipError_t launch_syrk_f32_split(hipStream_t st, const float* Xq, const float* X, int m,
+                                        int d, double alpha, double* Hacc, const Split& s) {
+  // whole: 2 stages x 3 planes x 256 rows of 80 bytes; quarter: 128 rows of 144
+  constexpr size_t lds = 2 * 3 * 256 * 80;
+  static_assert(lds >= 2 * 3 * 128 * 144 && lds >= (4096 + 4 * 32 * 33) * sizeof(double), "LDS");
+  static std::atomic<unsigned long long> lds_set{0};
+  const hipError_t e = allow_dynamic_lds((const void*)syrk_f32_kernel<CROSS, HALVES>, lds, lds_set);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((syrk_f32_kernel<CROSS, HALVES>), dim3(s.big + s.small), dim3(512), lds, st,
+                     Xq, X, m, d, alpha, Hacc, s);
+  return hipGetLastError();
 }
 
 template <bool CROSS>
@@ -574,15 +593,8 @@ static hipError_t launch_syrk_f32(hipStream_t st, const float* Xq, const float* 
     cut_last(s, last, 4);
   else if (half < whole)
     cut_last(s, last, 2);
-  // whole: 2 stages x 3 planes x 256 rows of 80 bytes; quarter: 128 rows of 144
-  constexpr size_t lds = 2 * 3 * 256 * 80;
-  static_assert(lds >= 2 * 3 * 128 * 144 && lds >= (4096 + 4 * 32 * 33) * sizeof(double), "LDS");
-  static std::atomic<unsigned long long> lds_set{0};
-  const hipError_t e = allow_dynamic_lds((const void*)syrk_f32_kernel<CROSS>, lds, lds_set);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(syrk_f32_kernel<CROSS>, dim3(s.big + s.small), dim3(512), lds, st, Xq, X, m,
-                     d, alpha, Hacc, s);
-  return hipGetLastError();
+  if (s.parts == 2) return launch_syrk_f32_split<CROSS, true>(st, Xq, X, m, d, alpha, Hacc, s);
+  return launch_syrk_f32_split<CROSS, false>(st, Xq, X, m, d, alpha, Hacc, s);
 }
 
 hipError_t launch_hessian_update(hipStream_t st, const float* X, int m, int d, double alpha,
