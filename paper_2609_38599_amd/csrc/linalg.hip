@@ -199,9 +199,9 @@ hipError_t launch_gemm_nn_f64(hipStream_t st, int M, int N, int K, double alpha,
 // with 512 columns updates the rest of the lower triangle: with every update
 // carried through the whole triangle, 64 columns at a time, the first half of
 // the steps were bound by reading and writing it (52 us for the first, 5 TB/s).
-// 4096 channels: 64 diagonal steps of 22 to 27 us and as many panels of 6 us;
+// 4096 channels: 64 diagonal steps of 16 to 25 us (mean 20) and 63 panels of 6 us;
 // 84 us for the diagonal block alone before.  The serial part bounds it: of a
-// step's 22 us, 11 factor the block and 3 invert it.
+// step's 20 us, 11 factor the block and 3 invert it.
 
 // 64 x 64 part of a row-major matrix into an LDS block (rows past `rows` repeat
 // the last one; `cols` is 32 or 64).
