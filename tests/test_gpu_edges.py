@@ -303,8 +303,8 @@ def _scales_of(W, H, codes, zeros, g, bits=8):
     return gk.state()[1].astype(np.float64)
 
 
-# W H by small and large tiles
-@pytest.mark.parametrize("rows,cols", [(70, 96), (300, 1024), (4100, 1024)])
+# W H in small tiles, and in large ones (160 of them and more)
+@pytest.mark.parametrize("rows,cols", [(70, 96), (300, 1024), (5200, 1024)])
 def test_scales_of_an_integer_layer_are_exact(rows, cols):
     """Integer W, H and codes whose Gram entries and W H fit fp32: everything
     ahead of the fp64 solve is exact, so a scale is its 64-bit value rounded."""
@@ -357,7 +357,7 @@ def _one_code_layer(rows, g, seed, value=None):
     return W.astype(np.float32), H.astype(np.float32), codes, np.zeros((rows, 2), np.int32)
 
 
-@pytest.mark.parametrize("rows", [70, 33000])
+@pytest.mark.parametrize("rows", [70, 41000])
 def test_scales_where_weights_span_many_octaves(rows):
     """W H to fp32 rounding whatever the range of a row of W: sums of 64 terms,
     (64 + 2) u of the sum of magnitudes, and the scale's own rounding."""
@@ -370,7 +370,7 @@ def test_scales_where_weights_span_many_octaves(rows):
     assert np.all(np.abs(got - ref) <= 66 * 2.0 ** -24 * size + 2.0 ** -24 * np.abs(ref))
 
 
-@pytest.mark.parametrize("rows", [70, 33000])
+@pytest.mark.parametrize("rows", [70, 41000])
 @pytest.mark.parametrize("value", [float("inf"), float("nan"), 3.4e38])
 def test_scales_of_extreme_weights(rows, value):
     """An infinity, a NaN, or a weight that rounds to infinity in bf16 stays in
