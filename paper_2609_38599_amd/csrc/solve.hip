@@ -103,8 +103,9 @@ struct Panels {
 };
 
 // T = ceil(G / 16) panels.  Row i of the system is lane i % 64, slot i / 64;
-// rows and columns from G to 16 T are zero but for a diagonal of kPadPivot, large
-// enough never to be the smallest pivot.
+// rows and columns from G to 16 T are zero but for a diagonal of kPadPivot, and
+// their columns are left out.  (No step reads that diagonal; with 0 in its place the
+// same steps come out slower as compiled: 4096 rows of G = 64 80 us instead of 69.)
 //
 // LDS.  Rows are kSolveLd doubles (17: the 16 rows and the k-pairs of a fragment
 // read cover the 64 banks once), first of the Schur complement's columns, then of
